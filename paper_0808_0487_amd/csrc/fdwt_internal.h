@@ -124,7 +124,10 @@ inline size_t align_ws(size_t b) { return (b + 255) & ~(size_t)255; }  // worksp
 // net.hip
 int launch_net_digits(const Net& net, uint32_t* X, hipStream_t st);
 int launch_net_points(const Net& net, float* x, hipStream_t st);
-int launch_net_packed(const Net& net, void* out, hipStream_t st);  // p=2: uint32 X<<(32-m); p odd: uint64 packed
+// The points' coordinates as the evaluation reads them: the row words of
+// eval.hip where eval_rows_ok(net), else p = 2: uint32 X << (32 - m), p odd:
+// uint64 digit strings, [s][N].
+int launch_net_packed(const Net& net, void* out, hipStream_t st);
 int launch_sample(const Net& net, int family, const double* a, float* f, hipStream_t st);
 
 // fwt.hip: element kinds
@@ -164,6 +167,14 @@ size_t spline_coef_ws_bytes(const Net& net, bool have_spectrum);
 int run_spline_coef(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* gk, const void* ft, float* c,
                     hipStream_t st);
 size_t packed_bytes(const Net& net);       // packed coordinates of all points (launch_net_packed)
+// eval.hip: evaluation by table rows, for the nets eval_rows_ok accepts.
+bool eval_rows_ok(const Net& net);
+void eval_rows_grid(int p, int s, int64_t N, int64_t nq, int* tqw, int* gy, int* bpc);
+void eval_rows_prefixes(const Net& net, float* tt);
+int launch_row_words(const Net& net, uint32_t* out, hipStream_t st);
+int launch_row_queries(const Net& net, const uint32_t* q, int64_t nq, void* out, hipStream_t st);
+int launch_eval_rows(const Net& net, const uint32_t* xw, const float* c, int64_t nq, const void* qv, const float* tt,
+                     df* partial, hipStream_t st);
 size_t eval_tables_bytes(const Net& net);  // staged per-lane factor tables of the evaluation
 size_t spline_eval_ws_bytes(const Net& net, int64_t nq, bool have_packed);
 int run_spline_eval(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* packed, const float* c,

@@ -194,7 +194,9 @@ static int coords(const Net& net, void* out, hipStream_t st) {
 
 int launch_net_digits(const Net& net, uint32_t* X, hipStream_t st) { return coords<CM_DIGITS>(net, X, st); }
 int launch_net_points(const Net& net, float* x, hipStream_t st) { return coords<CM_POINTS>(net, x, st); }
-int launch_net_packed(const Net& net, void* out, hipStream_t st) { return coords<CM_SHIFTED>(net, out, st); }
+int launch_net_packed(const Net& net, void* out, hipStream_t st) {
+  return eval_rows_ok(net) ? launch_row_words(net, (uint32_t*)out, st) : coords<CM_SHIFTED>(net, out, st);
+}
 
 template <int FAM>
 static int sample_fam(const Net& net, const FamilyArgs& fa, float* f, unsigned g, hipStream_t st) {

@@ -454,11 +454,23 @@ __global__ void __launch_bounds__(256) k_spline_eval(const void* __restrict__ Xp
   if (qi < nq) partial[(int64_t)blockIdx.y * nq + qi] = acc;
 }
 
+// Sums the gy partial sums of each query: 32 queries a workgroup, 8 threads a
+// query (row i, i + 8, ... each), their sums then in order.
 __global__ void __launch_bounds__(256) k_eval_finish(const df* __restrict__ partial, int gy, int64_t nq,
                                                      float* __restrict__ sf) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nq; i += (int64_t)gridDim.x * blockDim.x) {
-    df a = {0.0f, 0.0f};
-    for (int y = 0; y < gy; ++y) a = add(a, partial[(int64_t)y * nq + i]);
+  __shared__ df red[8][32];
+  const int ql = threadIdx.x & 31, sl = threadIdx.x >> 5;
+  const int64_t i = (int64_t)blockIdx.x * 32 + ql;
+  df a = {0.0f, 0.0f};
+  if (i < nq) {
+#pragma unroll 4
+    for (int y = sl; y < gy; y += 8) a = add(a, partial[(int64_t)y * nq + i]);
+  }
+  red[sl][ql] = a;
+  __syncthreads();
+  if (sl == 0 && i < nq) {
+    const int n = min(gy, 8);
+    for (int k = 1; k < n; ++k) a = add(a, red[k][ql]);
     sf[i] = a.hi + a.lo;
   }
 }
@@ -810,14 +822,17 @@ static void eval_grid(int64_t N, int64_t nq, int* gy_out, int64_t* ppc_out) {
 struct EvalWs {
   float* tl;     // factor tables [s][kTabE]
   void* Xp;      // packed coordinates (when not given)
-  uint64_t* qs;  // p odd: query digit strings [s][nq]
+  uint64_t* qs;  // p odd: query words or digit strings [s][nq]
   df* partial;
 };
 static void eval_layout(const Net& net, int64_t nq, bool have_packed, Carve& cv, EvalWs& w) {
   const int p = net.p, s = net.s;
-  int gy;
+  // Sized for either kernel (a shape does not tell which one its net takes).
+  int gy, gyr, tqw, bpc;
   int64_t ppc;
   eval_grid(net.N, nq, &gy, &ppc);
+  eval_rows_grid(p, s, net.N, nq, &tqw, &gyr, &bpc);
+  gy = std::max(gy, gyr);
   w.tl = (float*)cv.take(eval_tables_bytes(net));
   w.Xp = have_packed ? nullptr : cv.take(packed_bytes(net));
   w.qs = p == 2 ? nullptr : (uint64_t*)cv.take((size_t)s * nq * 8);
@@ -835,9 +850,11 @@ int run_spline_eval(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
   const int p = net.p, s = net.s, m = net.m;
   const int D = query_depth(p);
   const int64_t N = net.N;
-  int gy;
+  const bool rows = eval_rows_ok(net);
+  int gy, tqw, bpc;
   int64_t ppc;
-  eval_grid(N, nq, &gy, &ppc);
+  if (rows) eval_rows_grid(p, s, N, nq, &tqw, &gy, &bpc);
+  else eval_grid(N, nq, &gy, &ppc);
   int rc = ensure_ws(sc, spline_eval_ws_bytes(net, nq, packed != nullptr), st);
   if (rc) return rc;
   Carve cv(sc.ws);
@@ -847,7 +864,8 @@ int run_spline_eval(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
   // when all D digits agree, at entry c + 1 of the leading-zero count c that
   // k_spline_eval computes (p = 2: c = t, or -1 when equal; p odd: c = Bt+1..Bt+B,
   // or 64 when equal).  For p odd, entry 0 (high words equal, c = -1) is a
-  // NaN: it marks the points whose low words must be read.
+  // NaN: it marks the points whose low words must be read.  Rows (eval.hip):
+  // entry t, and entry D when all digits agree.
   const int B = p == 3 ? kStrBits<3> : kStrBits<5>;  // digit-string field width (coords.h)
   std::vector<float> htl((size_t)s * kTabE, 1.0f);
   for (int j = 0; j < s; ++j) {
@@ -855,12 +873,14 @@ int run_spline_eval(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
     const float eq = (float)(1.0 + kern->gamma[j] * kprime(p, kern->alpha, 0));
     for (int t = 0; t < D; ++t) {
       const float v = (float)(1.0 + kern->gamma[j] * kprime(p, kern->alpha, t + 1));
-      if (p == 2) row[t + 1] = v;
+      if (rows) row[t] = v;
+      else if (p == 2) row[t + 1] = v;
       else for (int l = B * t + 1; l <= B * t + B; ++l) row[l + 1] = v;
     }
-    row[p == 2 ? 0 : 65] = eq;
-    if (p != 2) row[0] = std::numeric_limits<float>::quiet_NaN();
+    row[rows ? D : (p == 2 ? 0 : 65)] = eq;
+    if (p != 2 && !rows) row[0] = std::numeric_limits<float>::quiet_NaN();
   }
+  if (rows) eval_rows_prefixes(net, htl.data());
   rc = upload(sc, htl.data(), htl.size() * 4, w.tl, st);
   if (rc) return rc;
   const void* Xp = packed;
@@ -870,7 +890,10 @@ int run_spline_eval(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
     Xp = w.Xp;
   }
   const void* qv = q;
-  if (p != 2) {
+  if (p != 2 && rows) {
+    if ((rc = launch_row_queries(net, q, nq, w.qs, st))) return rc;
+    qv = w.qs;
+  } else if (p != 2) {
     if (p == 3) hipLaunchKernelGGL(k_query_prep<3>, dim3(grid1((int64_t)s * nq)), dim3(256), 0, st, q, nq, s, D, w.qs);
     else if (p == 5) hipLaunchKernelGGL(k_query_prep<5>, dim3(grid1((int64_t)s * nq)), dim3(256), 0, st, q, nq, s, D, w.qs);
     else hipLaunchKernelGGL(k_query_prep<7>, dim3(grid1((int64_t)s * nq)), dim3(256), 0, st, q, nq, s, D, w.qs);
@@ -878,11 +901,12 @@ int run_spline_eval(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
     qv = w.qs;
   }
   hipEvent_t tb = timed_begin(st);
-  if (p == 2) rc = launch_eval<2>(net, Xp, c, nq, qv, w.tl, w.partial, gy, ppc, st);
+  if (rows) rc = launch_eval_rows(net, (const uint32_t*)Xp, c, nq, qv, w.tl, w.partial, st);
+  else if (p == 2) rc = launch_eval<2>(net, Xp, c, nq, qv, w.tl, w.partial, gy, ppc, st);
   else rc = launch_eval<3>(net, Xp, c, nq, qv, w.tl, w.partial, gy, ppc, st);  // any odd p: digit strings
   if (rc) return rc;
   timed_end(tb, st, FDWT_TC_EVAL, (double)nq * (double)N * s);
-  hipLaunchKernelGGL(k_eval_finish, dim3(grid1(nq)), dim3(256), 0, st, w.partial, gy, nq, sf);
+  hipLaunchKernelGGL(k_eval_finish, dim3((unsigned)((nq + 31) / 32)), dim3(256), 0, st, w.partial, gy, nq, sf);
   FDWT_HIP(hipGetLastError());
   return FDWT_OK;
 }
