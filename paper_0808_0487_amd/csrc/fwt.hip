@@ -521,12 +521,15 @@ __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS))
 // a_j (1 + U_{j-1}), one column stored per j).  X_j(n) is the XOR of the
 // generator columns of the set bits of n (Definition of a digital net,
 // p = 2); the columns and the tables are staged in LDS, so the loop's only
-// memory accesses are its stores.
+// memory accesses are its stores.  With few tiles the columns of a tile are
+// divided among nch workgroups, each of which runs the products from d = 1
+// but transforms and stores its own columns only.
 struct ColGen {
   const uint32_t* xtab;  // [s][nbytes][256]: X_j of byte value v at byte b
   const double* tab;     // [s][ktab]
   int nbytes, s, m, ktab;
   int d0, d1;            // truncation columns U_{d0+1}..U_{d1} are stored (out column d - 1 - d0)
+  int nch, per;          // ... by nch workgroups a tile, `per` columns each
 };
 
 template <int LOGE, bool KCOL>
@@ -553,6 +556,7 @@ __global__ void __launch_bounds__((P2Shape<LOGE, 0>::THREADS)) fwt_p2_gen(ColGen
   double* lrowS = lds + cpad(lane + 1024 * wv);
   const uint32_t goffS = (uint32_t)(lane + 1024 * wv);
   const int sh = 32 - m;
+  int tile = 0;
   // Pass over one generated column of the tile: the same stage groups as
   // fwt_p2's first pass, then a coalesced store.
   auto transform_store = [&](const double (&u)[EPT], int col) {
@@ -570,22 +574,24 @@ __global__ void __launch_bounds__((P2Shape<LOGE, 0>::THREADS)) fwt_p2_gen(ColGen
     if (d.oblk) {  // blocked layout (PassDesc::oblk)
       const int64_t rs = d.oblk;
       const gptr<double> dst =
-          to_global(out + (int64_t)col * d.col_out + ((lane >> 4) + 64 * wv) * rs + (int64_t)lb * 16 + (lane & 15));
+          to_global(out + (int64_t)col * d.col_out + ((lane >> 4) + 64 * wv) * rs + (int64_t)tile * 16 + (lane & 15));
 #pragma unroll
       for (int k = 0; k < EPT; ++k) dst[k * 4 * rs] = v[k];
     } else {
-      const gptr<double> dst = to_global(out + (int64_t)col * d.col_out + ((int64_t)lb << LOGE) + goffS);
+      const gptr<double> dst = to_global(out + (int64_t)col * d.col_out + ((int64_t)tile << LOGE) + goffS);
 #pragma unroll
       for (int k = 0; k < EPT; ++k) dst[k * 64] = v[k];
     }
     lds_barrier();
   };
-  for (; lb < d.ntiles; lb += G) {
-    const uint32_t n0 = (uint32_t)lb << LOGE;
+  for (; lb < d.ntiles * g.nch; lb += G) {
+    tile = lb / g.nch;
+    const int jfirst = g.d0 + (lb - tile * g.nch) * g.per;
+    const uint32_t n0 = (uint32_t)tile << LOGE;
     double u[EPT];
 #pragma unroll
     for (int k = 0; k < EPT; ++k) u[k] = KCOL ? 1.0 : 0.0;
-    const int jend = KCOL ? s : g.d1;
+    const int jend = KCOL ? s : min(g.d1, jfirst + g.per);
     for (int j = 0; j < jend; ++j) {
       const uint32_t* cj = cl + j * m;
       uint32_t xt = 0;  // X_j(tid) ^ X_j(n0)
@@ -608,7 +614,7 @@ __global__ void __launch_bounds__((P2Shape<LOGE, 0>::THREADS)) fwt_p2_gen(ColGen
         u[k] = KCOL ? u[k] * a : fma(a, 1.0 + u[k], u[k]);
       }
       if constexpr (!KCOL) {
-        if (j >= g.d0) transform_store(u, j - g.d0);
+        if (j >= jfirst) transform_store(u, j - g.d0);
       }
     }
     if constexpr (KCOL) transform_store(u, 0);
@@ -930,8 +936,23 @@ static std::vector<P2Pass> plan_p2_e(int m, int emax, size_t bytes = 4) {
   return v;
 }
 
+// First-pass bound of one transform: the largest tile (2^14) where the
+// transform fits one tile or needs it to stay at two passes, and smaller
+// tiles where two passes hold anyway: their workgroups are more than the CUs
+// at fewer points, and several share a CU (a 2^14-element float64 tile takes
+// a whole one).  Measured per call, 2^14 against this bound (us): float
+// m = 19 12.1 / 11.3, m = 20 14.4 / 12.9, m = 22 27.3 / 23.4 (m = 23 29.0 /
+// 43.0: three passes); float64 m = 17 13.8 / 11.0, m = 19 16.3 / 12.0, m = 20
+// 21.0 / 16.1, m = 21 30.7 / 28.0 with 2^13 (m = 22 31.0 / 32.9).
+static int p2_emax(int m, size_t bytes) {
+  if (m <= 14) return 14;
+  if (bytes < 8) return m <= 22 ? 13 : 14;
+  return m <= 20 ? 12 : (m <= 21 ? 13 : 14);
+}
+
 static std::vector<P2Pass> plan_p2(int m, size_t bytes) {
-  return plan_p2_e(m, (bytes >= 8 && lds_budget(bytes) < 136 * 1024) ? 13 : 14, bytes);
+  const int e = p2_emax(m, bytes);
+  return plan_p2_e(m, (bytes >= 8 && lds_budget(bytes) < 136 * 1024) ? std::min(e, 13) : e, bytes);
 }
 
 template <class Tin, class T, class Tout, int WDIG, int EPI>
@@ -1356,9 +1377,12 @@ int fwt_p2_gen_first(int m, int s, const uint32_t* xtab, int nbytes, const doubl
                      (size_t)s * m * sizeof(uint32_t);
   if (int rc = allow_lds(fn, lds)) return rc;
   int64_t G = (int64_t)occupancy(fn, threads, lds) * device_cus();
-  if (G >= d.ntiles) G = d.ntiles;
+  // Columns of a tile divided so that the workgroups fill the device once.
+  const int nch0 = (int)std::max<int64_t>(1, std::min<int64_t>(ncol, G / d.ntiles));
+  const int per = (ncol + nch0 - 1) / nch0, nch = (ncol + per - 1) / per;
+  if (G >= (int64_t)d.ntiles * nch) G = (int64_t)d.ntiles * nch;
   d.xcd = G >= 64 ? 1 : 0;
-  ColGen cg{xtab, tab, nbytes, s, m, ktab, kcol ? 0 : d0, kcol ? s : d1};
+  ColGen cg{xtab, tab, nbytes, s, m, ktab, kcol ? 0 : d0, kcol ? s : d1, nch, per};
   void* args[] = {(void*)&cg, (void*)&out, (void*)&d};
   return launch_timed(fn, dim3((unsigned)G), dim3(threads), args, lds, st, FDWT_TC_PASS_F64,
                       (double)N * ncol * sizeof(double));
