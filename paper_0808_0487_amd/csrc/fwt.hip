@@ -24,17 +24,6 @@
 
 namespace fdwt {
 
-// First logical block of workgroup hw.  Workgroups are dispatched round-robin
-// over the 8 XCDs (hw mod 8); XCD x gets the contiguous range of the
-// ceil((G - x) / 8) logical blocks starting at x floor(G/8) + min(x, G mod 8),
-// so neighbouring tiles (which share cache lines and DRAM pages) meet in the
-// same L2.  A bijection of [0, G) for any G, so a grid need not be a multiple
-// of 8 (3^14 points make 729 tiles: one round, not two).
-__device__ __forceinline__ int xcd_first(int hw, int G) {
-  const int x = hw & 7, q = G >> 3, r = G & 7;
-  return x * q + (x < r ? x : r) + (hw >> 3);
-}
-
 size_t kind_bytes(Kind k) {
   switch (k) {
     case K_F32: return 4;
@@ -191,139 +180,6 @@ __global__ void __launch_bounds__((PassShape<P, KMAX, sizeof(T)>::THREADS))
       }
     }
     lds_barrier();
-  }
-}
-
-// -------------------------------------------- p = 3 passes, static shape
-// Float-complex passes of p = 3 with the tile geometry fixed at compile time:
-// every tile holds 3^8 = 6561 elements, 3^RD rows (the RD digits of the
-// pass) of W = 3^(8 - RD) contiguous elements (the lowest digits), 52.5 KiB
-// of LDS.  Each of TH = 3^(8 - KT) threads takes 3^KT elements: element
-// e = tid + k TH lies in row tid / W + k 3^(RD - KT), so the values a thread
-// loads differ exactly in the KT top digits of the pass (k = j0 + 3 j1 + ...),
-// whose radix-3 stages run in registers before the tile goes to LDS; the
-// other digits go through LDS in groups of up to KT digits.  With KT = 3
-// (243 threads, 27 elements each) three workgroups share a CU, so the 729
-// tiles of a 3^14-point transform run in one round; KT = 2 (729 threads)
-// serves passes of two digits.  All LDS offsets of a group are compile-time
-// strides from a per-thread base; the strides W 3^q are odd multiples of the
-// row length, so the tile needs no padding.
-template <int RD, int KT>
-struct P3Shape {
-  static constexpr int E = 6561;
-  static constexpr int EPT = PowC<3, KT>::v;  // elements per thread
-  static constexpr int TH = E / EPT;
-  static constexpr int WDIG = 8 - RD;
-  static constexpr int W = PowC<3, WDIG>::v;
-  static constexpr int RSTEP = TH / W;         // rows between a thread's elements, 3^(RD - KT)
-  static_assert(RD >= KT && RD <= 8 && RD != 7 && TH % W == 0, "unsupported p = 3 shape");
-};
-
-// Radix-3 stages over the digits 0..KG-1 of the index of x (3^KG values).
-template <int KG, bool INV, class T, int N>
-__device__ __forceinline__ void dft3_digits(T (&x)[N]) {
-  static_assert(PowC<3, KG>::v == N, "3^KG values");
-#pragma unroll
-  for (int t = 0, st = 1; t < KG; ++t, st *= 3) {
-#pragma unroll
-    for (int j0 = 0; j0 < N; ++j0)
-      if ((j0 / st) % 3 == 0) Dft<3, INV>::run(x + j0, st);
-  }
-}
-
-// Register groups over row digits [Q, Q + KG) for Q < LIM, then the next.
-template <int RD, int KT, int Q, bool INV, class T, int LIM = RD - KT, bool DONE = (Q >= LIM)>
-struct P3Groups {
-  static __device__ __forceinline__ void run(T* lds, int tid) {
-    using S = P3Shape<RD, KT>;
-    constexpr int KG = (LIM - Q) >= KT ? KT : (LIM - Q);
-    constexpr int R = PowC<3, KG>::v;
-    constexpr int PQ = PowC<3, Q>::v;
-    constexpr int STQ = S::W * PQ;          // element stride of digit Q
-    constexpr int GPT = S::E / R / S::TH;   // groups per thread
-    const int c = tid % S::W;
-    const int u0 = tid / S::W;
-#pragma unroll
-    for (int g = 0; g < GPT; ++g) {
-      // group tid + g TH: rows u = lo + PQ (j + R hi), lo < PQ
-      const int u = u0 + g * S::RSTEP;
-      const int lo = u % PQ, hi = u / PQ;
-      T* base = lds + c + S::W * (lo + PQ * R * hi);
-      T x[R];
-#pragma unroll
-      for (int j = 0; j < R; ++j) x[j] = base[j * STQ];
-      dft3_digits<KG, INV>(x);
-#pragma unroll
-      for (int j = 0; j < R; ++j) base[j * STQ] = x[j];
-    }
-    lds_barrier();
-    P3Groups<RD, KT, Q + KG, INV, T, LIM>::run(lds, tid);
-  }
-};
-template <int RD, int KT, int Q, bool INV, class T, int LIM>
-struct P3Groups<RD, KT, Q, INV, T, LIM, true> {
-  static __device__ __forceinline__ void run(T*, int) {}
-};
-
-template <bool INV, class Tin, class T, class Tout, int RD, int KT>
-__global__ void __launch_bounds__((P3Shape<RD, KT>::TH)) fwt_p3s(const Tin* __restrict__ in, Tout* out, PassDesc d) {
-  using S = P3Shape<RD, KT>;
-  constexpr int TH = S::TH, EPT = S::EPT;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* lds = reinterpret_cast<T*>(smem_raw);
-  const int G = gridDim.x;
-  const int nb = d.ntiles * d.batch;
-  const int hw = blockIdx.x;
-  int lb = d.xcd ? xcd_first(hw, G) : hw;
-  const int tid = threadIdx.x;
-  // Global offset of element tid + k TH: goff0 + k gstep.
-  const uint32_t sd0 = (uint32_t)d.sd0;
-  const uint32_t goff0 = (uint32_t)(tid % S::W) + (uint32_t)(tid / S::W) * sd0;
-  const uint32_t gstep = (uint32_t)S::RSTEP * sd0;
-  auto locate = [&](int l, int& col, int& tile) {
-    col = l / d.ntiles;
-    tile = l % d.ntiles;
-  };
-  auto tile_base = [&](int tile) {
-    const int lo = tile % d.nlo;
-    const int hi = tile / d.nlo;
-    return (int64_t)lo * S::W + (int64_t)hi * d.shi;
-  };
-  Tin pre[EPT];
-  // live false: every load reads the tile's first element (one cache line), a
-  // stand-in that keeps the loads unconditional when there is no next tile.
-  auto prefetch = [&](int l, bool live) {
-    int col, tile;
-    locate(l, col, tile);
-    const Tin* src = in + (int64_t)col * d.col_in + tile_base(tile) + (live ? goff0 : 0u);
-    const uint32_t st = live ? gstep : 0u;
-#pragma unroll
-    for (int k = 0; k < EPT; ++k) pre[k] = src[k * st];
-  };
-  if (lb < nb) prefetch(lb, true);
-  for (; lb < nb; lb += G) {
-    T v[EPT];
-#pragma unroll
-    for (int k = 0; k < EPT; ++k) v[k] = cvt_in<Tin, T>(pre[k]);
-    dft3_digits<KT, INV>(v);  // the KT top digits of the pass
-    int col, tile;
-    locate(lb, col, tile);
-    Tout* dst = out + (int64_t)col * d.col_out + tile_base(tile) + goff0;
-    if constexpr (RD == KT) {
-      // The pass has no other digits: straight back to memory.
-      prefetch(lb + G < nb ? lb + G : lb, lb + G < nb);  // unconditional: exact wait counts
-#pragma unroll
-      for (int k = 0; k < EPT; ++k) dst[k * gstep] = cvt_out<T, Tout>(v[k], d.scale, d.scale64);
-    } else {
-#pragma unroll
-      for (int k = 0; k < EPT; ++k) lds[tid + k * TH] = v[k];
-      lds_barrier();
-      prefetch(lb + G < nb ? lb + G : lb, lb + G < nb);  // unconditional: exact wait counts
-      P3Groups<RD, KT, 0, INV, T>::run(lds, tid);
-#pragma unroll
-      for (int k = 0; k < EPT; ++k) dst[k * gstep] = cvt_out<T, Tout>(lds[tid + k * TH], d.scale, d.scale64);
-      lds_barrier();
-    }
   }
 }
 
@@ -702,10 +558,6 @@ __global__ void __launch_bounds__((P2Shape<LOGE, 0>::THREADS)) fwt_p2_fam(FamGen
 
 
 // ----------------------------------------------------------------- planner
-struct PassGeom {
-  int d0, r, wdig;
-};
-
 // LDS per workgroup: 80 KiB lets two workgroups share a CU (160 KiB of LDS).
 // Elements of 8 bytes or more take a whole CU so that m = 24 still needs only
 // two passes (measured faster at m = 24 than three passes with two
@@ -763,7 +615,7 @@ static std::vector<PassGeom> plan(int p, int m, size_t bytes, Kind work) {
 static int set_lds_attr(const void* fn, size_t bytes) { return allow_lds(fn, bytes); }
 
 // Compute units of the current device (cached per device).
-static int device_cus() {
+int device_cus() {
   static std::mutex mu;
   static std::vector<int> cache;
   int dev = 0;
@@ -777,14 +629,6 @@ static int device_cus() {
   }
   return cache[dev];
 }
-
-// Optional grouped-sum epilogue of the last pass.
-struct ReduceArgs {
-  const float2* wts;
-  double* partial;  // [batch][fwt_reduce_parts]
-  double* h0_out;
-  int h0_col;
-};
 
 template <int P, bool INV, class Tin, class T, class Tout>
 static int launch_pass(const void* in, void* out, const PassGeom& g, int m, int batch, double scale,
@@ -815,6 +659,7 @@ static int launch_pass(const void* in, void* out, const PassGeom& g, int m, int 
     d.partial = red->partial;
     d.h0_out = red->h0_out;
     d.h0_col = red->h0_col;
+    d.ncols = red->ncols;
   } else {
     d.h0_col = -1;
   }
@@ -848,54 +693,16 @@ static int launch_pass(const void* in, void* out, const PassGeom& g, int m, int 
   return launch_timed(fn, dim3((unsigned)G), dim3(threads), args, lds, st, cls, alg);
 }
 
-// Dispatch on (p, direction, in/work/out kinds).
-template <int P, bool INV>
-static int pass_dispatch(Kind ik, Kind wk, Kind ok, const void* in, void* out, const PassGeom& g,
-                         int m, int batch, double scale, int64_t ci, int64_t co, const ReduceArgs* red,
-                         hipStream_t st) {
-#define FDWT_PASS(TIN, T, TOUT) \
-  return launch_pass<P, INV, TIN, T, TOUT>(in, out, g, m, batch, scale, ci, co, wk, red, st)
-  if constexpr (P == 2) {
-    if (!red) {
-      if (wk == K_F32 && ik == K_F32 && ok == K_F32) FDWT_PASS(float, float, float);
-      if (wk == K_U32 && ik == K_U32 && ok == K_U32) FDWT_PASS(uint32_t, uint32_t, uint32_t);
-    }
-    if (wk == K_F64 && ik == K_F64 && ok == K_F64) FDWT_PASS(double, double, double);
-  } else {
-    if (wk == K_CF32 && !red) {
-      if (ik == K_F32 && ok == K_CF32) FDWT_PASS(float, float2, float2);
-      if (ik == K_F32 && ok == K_F32) FDWT_PASS(float, float2, float);
-      if (ik == K_CF32 && ok == K_CF32) FDWT_PASS(float2, float2, float2);
-      if (ik == K_CF32 && ok == K_F32) FDWT_PASS(float2, float2, float);
-    }
-    if (wk == K_CF64) {
-      if (ik == K_F64 && ok == K_CF64) FDWT_PASS(double, double2, double2);
-      if (ik == K_CF64 && ok == K_CF64) FDWT_PASS(double2, double2, double2);
-      if (!red && ik == K_CF64 && ok == K_F64) FDWT_PASS(double2, double2, double);
-    }
-  }
-#undef FDWT_PASS
+// A generic pass of a small p = 2 transform (forward and inverse coincide up
+// to the scale).
+static int p2_generic(Kind k, const void* in, void* out, const PassGeom& g, int m, int batch, double scale,
+                      const ReduceArgs* red, hipStream_t st) {
+  const int64_t N = int64_t(1) << m;
+  if (k == K_F32 && !red) return launch_pass<2, false, float, float, float>(in, out, g, m, batch, scale, N, N, k, red, st);
+  if (k == K_U32 && !red)
+    return launch_pass<2, false, uint32_t, uint32_t, uint32_t>(in, out, g, m, batch, scale, N, N, k, red, st);
+  if (k == K_F64) return launch_pass<2, false, double, double, double>(in, out, g, m, batch, scale, N, N, k, red, st);
   return fail(FDWT_EINVAL, "unsupported transform element types");
-}
-
-static int pass_any(int p, bool inv, Kind ik, Kind wk, Kind ok, const void* in, void* out,
-                    const PassGeom& g, int m, int batch, double scale, int64_t ci, int64_t co,
-                    const ReduceArgs* red, hipStream_t st) {
-  switch (p) {
-    case 2:
-      return inv ? pass_dispatch<2, true>(ik, wk, ok, in, out, g, m, batch, scale, ci, co, red, st)
-                 : pass_dispatch<2, false>(ik, wk, ok, in, out, g, m, batch, scale, ci, co, red, st);
-    case 3:
-      return inv ? pass_dispatch<3, true>(ik, wk, ok, in, out, g, m, batch, scale, ci, co, red, st)
-                 : pass_dispatch<3, false>(ik, wk, ok, in, out, g, m, batch, scale, ci, co, red, st);
-    case 5:
-      return inv ? pass_dispatch<5, true>(ik, wk, ok, in, out, g, m, batch, scale, ci, co, red, st)
-                 : pass_dispatch<5, false>(ik, wk, ok, in, out, g, m, batch, scale, ci, co, red, st);
-    case 7:
-      return inv ? pass_dispatch<7, true>(ik, wk, ok, in, out, g, m, batch, scale, ci, co, red, st)
-                 : pass_dispatch<7, false>(ik, wk, ok, in, out, g, m, batch, scale, ci, co, red, st);
-  }
-  return fail(FDWT_EUNSUPPORTED, "p must be 2, 3, 5 or 7");
 }
 
 // ---------------------------------------------- p = 2 static-shape passes
@@ -936,17 +743,18 @@ static std::vector<P2Pass> plan_p2_e(int m, int emax, size_t bytes = 4) {
   return v;
 }
 
-// First-pass bound of one transform: the largest tile (2^14) where the
+// First-pass bound of a plain transform: the largest tile (2^14) where the
 // transform fits one tile or needs it to stay at two passes, and smaller
 // tiles where two passes hold anyway: their workgroups are more than the CUs
 // at fewer points, and several share a CU (a 2^14-element float64 tile takes
 // a whole one).  Measured per call, 2^14 against this bound (us): float
-// m = 19 12.1 / 11.3, m = 20 14.4 / 12.9, m = 22 27.3 / 23.4 (m = 23 29.0 /
-// 43.0: three passes); float64 m = 17 13.8 / 11.0, m = 19 16.3 / 12.0, m = 20
-// 21.0 / 16.1, m = 21 30.7 / 28.0 with 2^13 (m = 22 31.0 / 32.9).
+// m = 17 11.0 / 10.9, m = 19 12.1 / 11.3, m = 20 14.4 / 12.9, m = 22
+// 27.3 / 23.4 (m = 23 29.0 / 43.0: three passes); float64 m = 17 13.8 / 11.0,
+// m = 19 16.3 / 12.0, m = 20 21.0 / 16.1, m = 21 30.7 / 28.0 with 2^13
+// (m = 22 31.0 / 32.9).
 static int p2_emax(int m, size_t bytes) {
+  if (bytes < 8) return m >= 18 && m <= 22 ? 13 : 14;
   if (m <= 14) return 14;
-  if (bytes < 8) return m <= 22 ? 13 : 14;
   return m <= 20 ? 12 : (m <= 21 ? 13 : 14);
 }
 
@@ -954,6 +762,12 @@ static std::vector<P2Pass> plan_p2(int m, size_t bytes) {
   const int e = p2_emax(m, bytes);
   return plan_p2_e(m, (bytes >= 8 && lds_budget(bytes) < 136 * 1024) ? std::min(e, 13) : e, bytes);
 }
+
+// Plan of the kernel spectrum and of the variance columns (float64): 2^14
+// first-pass tiles at every size.  The spectra's small bins are differences
+// of large sums, so their last digits follow the order of the stages, which
+// a plan fixes; many columns fill the device with any tile.
+static std::vector<P2Pass> plan_p2_cols(int m) { return plan_p2_e(m, lds_budget(8) < 136 * 1024 ? 13 : 14, 8); }
 
 template <class Tin, class T, class Tout, int WDIG, int EPI>
 static const void* p2_kernel(int loge) {
@@ -971,7 +785,7 @@ static const void* p2_kernel(int loge) {
 }
 
 // Workgroups per CU for (kernel, LDS), cached.
-static int occupancy(const void* fn, int threads, size_t lds) {
+int occupancy(const void* fn, int threads, size_t lds) {
   static std::mutex mu;
   static std::map<std::pair<const void*, size_t>, int> cache;
   std::lock_guard<std::mutex> g(mu);
@@ -982,132 +796,6 @@ static int occupancy(const void* fn, int threads, size_t lds) {
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, lds) != hipSuccess || n < 1) n = 1;
   cache[key] = n;
   return n;
-}
-
-// ---------------------------------------------- p = 3 static-shape passes
-// FDWT_P3_STATIC = 0 sends p = 3 float-complex transforms through the
-// generic pass instead (read once per process).
-static bool p3_static_enabled() {
-  static const bool on = [] {
-    const char* e = getenv("FDWT_P3_STATIC");
-    return e ? atoi(e) != 0 : true;
-  }();
-  return on;
-}
-
-// Whether a pass has a shape of fwt_p3s: the first pass of 8 digits, or a
-// strided pass of 2..6 digits over rows of 3^(8 - r) elements.
-static bool p3s_shape(const PassGeom& g) {
-  return (g.d0 == 0 && g.r == 8 && g.wdig == 0) || (g.d0 >= 8 && g.r >= 2 && g.r <= 6 && g.wdig == 8 - g.r);
-}
-
-// The generic plan's digit split (a first pass of 8 digits, the rest split
-// evenly into passes of at most 6), with every strided pass of two or more
-// digits taking rows of 3^(8 - r) elements, so that its tiles hold 3^8.
-static std::vector<PassGeom> plan_p3s(int m) {
-  std::vector<PassGeom> v = plan(3, m, sizeof(float2), K_CF32);
-  for (PassGeom& g : v)
-    if (g.d0 > 0 && g.r >= 2) g.wdig = 8 - g.r;
-  return v;
-}
-
-// FDWT_P3_KT = 2 or 3 fixes the register digits of every static pass of
-// three or more digits (read once per process); 0 or unset: chosen per launch.
-static int p3s_kt_forced() {
-  static const int kt = [] {
-    const char* e = getenv("FDWT_P3_KT");
-    const int v = e ? atoi(e) : 0;
-    return v == 2 || v == 3 ? v : 0;
-  }();
-  return kt;
-}
-
-template <bool INV, class Tin, class Tout, int RD>
-static const void* p3s_kernel(int kt) {
-  if constexpr (RD >= 3) {
-    if (kt == 3) return (const void*)fwt_p3s<INV, Tin, float2, Tout, RD, 3>;
-    return (const void*)fwt_p3s<INV, Tin, float2, Tout, RD, 2>;
-  } else {
-    return kt == 2 ? (const void*)fwt_p3s<INV, Tin, float2, Tout, RD, 2> : nullptr;
-  }
-}
-
-template <bool INV, class Tin, class Tout>
-static const void* p3s_kernel_for(int rd, int kt) {
-  if (rd == 8) return p3s_kernel<INV, Tin, Tout, 8>(kt);
-  if constexpr (std::is_same<Tin, float2>::value) {
-    switch (rd) {
-      case 2: return p3s_kernel<INV, Tin, Tout, 2>(kt);
-      case 3: return p3s_kernel<INV, Tin, Tout, 3>(kt);
-      case 4: return p3s_kernel<INV, Tin, Tout, 4>(kt);
-      case 5: return p3s_kernel<INV, Tin, Tout, 5>(kt);
-      case 6: return p3s_kernel<INV, Tin, Tout, 6>(kt);
-    }
-  }
-  return nullptr;
-}
-
-template <bool INV, class Tin, class Tout>
-static int launch_p3s(const void* in, void* out, const PassGeom& g, int m, int batch, double scale, hipStream_t st) {
-  if (!p3s_shape(g)) return fail(FDWT_EINVAL, "not a static p = 3 pass shape");
-  const int64_t N = ipow(3, m);
-  const int64_t ntiles = N / 6561;
-  const int64_t nb = ntiles * batch;
-  const size_t lds = (size_t)6561 * sizeof(float2);
-  // Two register digits (729 threads, two workgroups per CU) hide memory
-  // latency best; three (243 threads, three per CU) pay when they let every
-  // tile run in one round and two digits would not (3^14 points: 729 tiles).
-  const void* fn = p3s_kernel_for<INV, Tin, Tout>(g.r, 2);
-  int kt = 2;
-  if (!fn) return fail(FDWT_EINVAL, "static p = 3 pass not built for these element types");
-  if (g.r >= 3) {
-    const void* fn3 = p3s_kernel_for<INV, Tin, Tout>(g.r, 3);
-    if (int rc = allow_lds(fn, lds)) return rc;
-    if (int rc = allow_lds(fn3, lds)) return rc;
-    const int64_t g2 = (int64_t)occupancy(fn, 729, lds) * device_cus();
-    const int64_t g3 = (int64_t)occupancy(fn3, 243, lds) * device_cus();
-    const int forced = p3s_kt_forced();
-    if (forced ? forced == 3 : (nb > g2 && nb <= g3)) {
-      fn = fn3;
-      kt = 3;
-    }
-  }
-  PassDesc d{};
-  d.col_in = N;
-  d.col_out = N;
-  d.sd0 = ipow(3, g.d0);
-  d.shi = ipow(3, g.d0 + g.r);
-  d.r = g.r;
-  d.wdig = g.wdig;
-  d.w = (int)ipow(3, g.wdig);
-  d.nlo = (int)ipow(3, g.d0 - g.wdig);
-  d.E = 6561;
-  d.kreg = kt;
-  d.scale = (float)scale;
-  d.scale64 = scale;
-  d.h0_col = -1;
-  d.ntiles = (int)ntiles;
-  d.batch = batch;
-  const int threads = kt == 3 ? 243 : 729;
-  if (int rc = allow_lds(fn, lds)) return rc;
-  int64_t G = (int64_t)occupancy(fn, threads, lds) * device_cus();
-  if (G >= nb) G = nb;
-  d.xcd = G >= 64 ? 1 : 0;
-  const Tin* inp = (const Tin*)in;
-  Tout* outp = (Tout*)out;
-  void* args[] = {(void*)&inp, (void*)&outp, (void*)&d};
-  return launch_timed(fn, dim3((unsigned)G), dim3(threads), args, lds, st, FDWT_TC_PASS_CF32,
-                      (double)N * batch * (sizeof(Tin) + sizeof(Tout)));
-}
-
-template <bool INV>
-static int p3s_pass_dir(Kind ik, Kind ok, const void* in, void* out, const PassGeom& g, int m, int batch,
-                        double scale, hipStream_t st) {
-  if (ik == K_F32 && ok == K_CF32) return launch_p3s<INV, float, float2>(in, out, g, m, batch, scale, st);
-  if (ik == K_F32 && ok == K_F32) return launch_p3s<INV, float, float>(in, out, g, m, batch, scale, st);
-  if (ik == K_CF32 && ok == K_CF32) return launch_p3s<INV, float2, float2>(in, out, g, m, batch, scale, st);
-  if (ik == K_CF32 && ok == K_F32) return launch_p3s<INV, float2, float>(in, out, g, m, batch, scale, st);
-  return fail(FDWT_EINVAL, "unsupported transform element types");
 }
 
 // Partial sums per column written by a reducing static pass: one per wave of
@@ -1169,6 +857,7 @@ static int launch_p2(const void* in, void* out, const P2Pass& g, int m, int batc
     d.partial = red->partial;
     d.h0_out = red->h0_out;
     d.h0_col = red->h0_col;
+    d.ncols = red->ncols;
   } else {
     d.h0_col = -1;
   }
@@ -1214,7 +903,7 @@ static bool p2_static_ok(int p, int m, Kind ik, Kind wk, Kind ok) {
 
 static int run_p2(int m, Kind k, const void* in, void* out, void* tmp, int batch, double scale,
                   const ReduceArgs* red, int64_t* last_parts, hipStream_t st) {
-  const std::vector<P2Pass> passes = plan_p2(m, kind_bytes(k));
+  const std::vector<P2Pass> passes = red ? plan_p2_cols(m) : plan_p2(m, kind_bytes(k));
   const size_t np = passes.size();
   if (last_parts) *last_parts = p2_reduce_parts(m, passes.back());
   if (np == 1) return p2_pass(k, in, out, passes[0], m, batch, scale, red, st);
@@ -1231,11 +920,11 @@ static int run_passes(int p, int m, bool inverse, Kind in_kind, const void* in, 
                       int64_t* last_parts, hipStream_t st) {
   if (p2_static_ok(p, m, in_kind, work_kind, out_kind))
     return run_p2(m, work_kind, in, out, tmp, batch, scale, red, last_parts, st);
+  if (p == 2 && (in_kind != work_kind || out_kind != work_kind))
+    return fail(FDWT_EINVAL, "unsupported transform element types");
   const int64_t N = ipow(p, m);
-  // p = 3 float-complex store passes take the static shapes where the plan
-  // has them (every pass but a strided one of a single digit, for m >= 8).
-  const bool p3s = p == 3 && work_kind == K_CF32 && !red && p3_static_enabled();
-  std::vector<PassGeom> passes = p3s ? plan_p3s(m) : plan(p, m, kind_bytes(work_kind), work_kind);
+  // p = 2 below 2^7 points: the generic pass; p odd: the static shapes of odd.hip.
+  std::vector<PassGeom> passes = p == 2 ? plan(p, m, kind_bytes(work_kind), work_kind) : odd_plan(p, m, work_kind);
   const size_t np = passes.size();
   if (last_parts) {
     const PassGeom& g = passes.back();
@@ -1243,10 +932,8 @@ static int run_passes(int p, int m, bool inverse, Kind in_kind, const void* in, 
   }
   auto one = [&](Kind ik, Kind ok, const void* src, void* dst, const PassGeom& g, double sc,
                  const ReduceArgs* rd) {
-    if (p3s && p3s_shape(g))
-      return inverse ? p3s_pass_dir<true>(ik, ok, src, dst, g, m, batch, sc, st)
-                     : p3s_pass_dir<false>(ik, ok, src, dst, g, m, batch, sc, st);
-    return pass_any(p, inverse, ik, work_kind, ok, src, dst, g, m, batch, sc, N, N, rd, st);
+    if (p == 2) return p2_generic(work_kind, src, dst, g, m, batch, sc, rd, st);
+    return odd_pass(p, inverse, ik, work_kind, ok, src, dst, g, m, batch, sc, rd, st);
   };
   if (np == 1) return one(in_kind, out_kind, in, out, passes[0], scale, red);
   // Intermediate buffer: the output itself when it holds the working type.
@@ -1272,15 +959,19 @@ int fwt_run(int p, int m, bool inverse, Kind in_kind, const void* in, Kind work_
   return fwt_run_tmp(p, m, inverse, in_kind, in, work_kind, out_kind, out, nullptr, batch, scale, st);
 }
 
-// Unnormalised forward transform of `batch` real float64 columns with the
-// grouped-sum epilogue in its last pass (no output stored).  tmp holds the
-// intermediate passes (batch columns of the working type); partial receives
-// [batch][parts] partial sums, parts (fwt_reduce_parts) returned in *parts.
-int fwt_reduce_f64(int p, int m, const double* in, void* tmp, int batch, const float2* wts,
+// Unnormalised forward transform of ncols real float64 columns with the
+// grouped-sum epilogue in its last pass (no output stored).  p = 2: `in` holds
+// the columns and tmp the intermediate passes.  p odd: `in` holds pairs of
+// columns as complex ones, column 2 i as the real part and column 2 i + 1
+// divided by unscale[i] as the imaginary part (both spectra are real: the
+// kernel columns are even functions of the point index), and is overwritten;
+// tmp is not used.  partial receives [ncols][parts] partial sums, parts
+// (fwt_reduce_parts) returned in *parts.
+int fwt_reduce_f64(int p, int m, void* in, void* tmp, int ncols, const float2* wts, const double* unscale,
                    double* partial, double* h0_out, int h0_col, int64_t* parts, hipStream_t st) {
-  ReduceArgs red{wts, partial, h0_out, h0_col};
-  const Kind wk = p == 2 ? K_F64 : K_CF64;
-  return run_passes(p, m, false, K_F64, in, wk, wk, tmp, tmp, batch, 1.0f, &red, parts, st);
+  ReduceArgs red{wts, partial, h0_out, h0_col, unscale, ncols};
+  if (p == 2) return run_passes(p, m, false, K_F64, in, K_F64, K_F64, tmp, tmp, ncols, 1.0, &red, parts, st);
+  return run_passes(p, m, false, K_CF64, in, K_CF64, K_CF64, in, in, (ncols + 1) / 2, 1.0, &red, parts, st);
 }
 
 // Plans of p = 2 float transforms for the batch tuner: the first pass takes
@@ -1316,7 +1007,7 @@ int fwt_p2_group_pass(int m, int emax, int level, const void* const* in_tab, voi
 // epilogue in the last (partial as for fwt_reduce_f64).
 bool fwt_p2_split_ok(int m) {
   if (m < 7) return false;
-  const std::vector<P2Pass> v = plan_p2(m, 8);
+  const std::vector<P2Pass> v = plan_p2_cols(m);
   return v.size() >= 2 && v[0].d0 == 0 && v[0].wdig == 0 && v[0].loge >= 12 && v[0].loge <= 14;
 }
 
@@ -1324,21 +1015,21 @@ bool fwt_p2_split_ok(int m) {
 // PassDesc::oblk (the first pass stores blocks, the grouped-sum pass reads
 // each tile as one contiguous block; its weights then come in the same
 // layout, fwt_p2_blocked_index).
-bool fwt_p2_blocked_ok(int m) { return fwt_p2_split_ok(m) && plan_p2(m, 8).size() == 2; }
+bool fwt_p2_blocked_ok(int m) { return fwt_p2_split_ok(m) && plan_p2_cols(m).size() == 2; }
 
 // Digits of the first pass of the float64 plan for m.
-int fwt_p2_first_loge(int m) { return plan_p2(m, 8)[0].loge; }
+int fwt_p2_first_loge(int m) { return plan_p2_cols(m)[0].loge; }
 
 int fwt_p2_f64_first(int m, const double* in, double* out, int batch, bool blocked, hipStream_t st) {
   if (!fwt_p2_split_ok(m) || (blocked && !fwt_p2_blocked_ok(m))) return fail(FDWT_EINVAL, "no split plan for this m");
-  return p2_pass(K_F64, in, out, plan_p2(m, 8)[0], m, batch, 1.0, nullptr, st, blocked ? 1 : 0);
+  return p2_pass(K_F64, in, out, plan_p2_cols(m)[0], m, batch, 1.0, nullptr, st, blocked ? 1 : 0);
 }
 
 int fwt_p2_f64_reduce_rest(int m, double* data, int batch, const float2* wts, double* partial, double* h0_out,
                            int h0_col, bool blocked, hipStream_t st) {
   if (!fwt_p2_split_ok(m) || (blocked && !fwt_p2_blocked_ok(m))) return fail(FDWT_EINVAL, "no split plan for this m");
-  const std::vector<P2Pass> v = plan_p2(m, 8);
-  const ReduceArgs red{wts, partial, h0_out, h0_col};
+  const std::vector<P2Pass> v = plan_p2_cols(m);
+  const ReduceArgs red{wts, partial, h0_out, h0_col, nullptr, batch};
   int rc = FDWT_OK;
   for (size_t i = 1; !rc && i + 1 < v.size(); ++i) rc = p2_pass(K_F64, data, data, v[i], m, batch, 1.0, nullptr, st);
   if (rc) return rc;
@@ -1353,7 +1044,7 @@ int fwt_p2_gen_first(int m, int s, const uint32_t* xtab, int nbytes, const doubl
                      int d0, int d1, double* out, bool blocked, hipStream_t st) {
   if (!fwt_p2_split_ok(m) || s < 1 || s > 64 || ktab <= m) return fail(FDWT_EINVAL, "bad generated-column pass");
   if (!kcol && (d0 < 0 || d1 > s || d0 >= d1)) return fail(FDWT_EINVAL, "bad generated-column range");
-  const P2Pass g = plan_p2(m, 8)[0];
+  const P2Pass g = plan_p2_cols(m)[0];
   const void* fn = nullptr;
   if (kcol) fn = g.loge == 14 ? (const void*)fwt_p2_gen<14, true>
                  : g.loge == 13 ? (const void*)fwt_p2_gen<13, true> : (const void*)fwt_p2_gen<12, true>;
@@ -1392,7 +1083,7 @@ int fwt_p2_gen_first(int m, int s, const uint32_t* xtab, int nbytes, const doubl
 // place (the first pass's output already in data).
 int fwt_p2_f64_rest(int m, double* data, int batch, hipStream_t st) {
   if (!fwt_p2_split_ok(m)) return fail(FDWT_EINVAL, "no split plan for this m");
-  const std::vector<P2Pass> v = plan_p2(m, 8);
+  const std::vector<P2Pass> v = plan_p2_cols(m);
   int rc = FDWT_OK;
   for (size_t i = 1; !rc && i < v.size(); ++i) rc = p2_pass(K_F64, data, data, v[i], m, batch, 1.0, nullptr, st);
   return rc;
@@ -1451,8 +1142,8 @@ int fwt_p2_forward_family(const Net& net, int family, const FamilyArgs& fa, floa
 }
 
 int64_t fwt_reduce_parts(int p, int m, size_t elem_bytes) {
-  if (p == 2 && m >= 7) return p2_reduce_parts(m, plan_p2(m, elem_bytes).back());
-  std::vector<PassGeom> passes = plan(p, m, elem_bytes, elem_bytes >= 16 ? K_CF64 : K_F64);
+  if (p == 2 && m >= 7) return p2_reduce_parts(m, plan_p2_cols(m).back());
+  const std::vector<PassGeom> passes = p == 2 ? plan(p, m, elem_bytes, K_F64) : odd_plan(p, m, K_CF64);
   const PassGeom& g = passes.back();
   return ipow(p, m) / (ipow(p, g.r) * ipow(p, g.wdig));
 }

@@ -1,0 +1,408 @@
+// Passes of the transforms over Z_p, p = 3, 5, 7, with the tile geometry
+// fixed at compile time (see fwt.hip for the split of a transform into
+// passes).  A tile holds p^LE elements: p^RD rows (the RD digits of the pass)
+// of W = p^(LE - RD) contiguous elements (the lowest digits).  Each of
+// TH = p^(LE - KT) threads takes p^KT elements: element e = tid + k TH lies in
+// row tid / W + k p^(RD - KT), so the values a thread loads differ exactly in
+// the KT top digits of the pass (k = j0 + p j1 + ...), whose radix-p stages
+// run in registers; the other digits go through LDS in groups of up to KT
+// digits, with compile-time strides from a per-thread base.  The strides W p^q
+// are odd multiples of the row length, so the tile needs no padding.  The
+// stages run in ascending order of the digits (the top digits on the values
+// read back for the store), so a transform's rounding does not depend on how
+// it is split into passes; the p = 3 float tiles of 3^8 elements take the top
+// digits first, on the values as loaded.
+#include "pass_core.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace fdwt {
+
+template <int P, int LE, int RD, int KT>
+struct OddShape {
+  static constexpr int E = PowC<P, LE>::v;
+  static constexpr int EPT = PowC<P, KT>::v;  // elements per thread
+  static constexpr int TH = E / EPT;
+  static constexpr int W = PowC<P, LE - RD>::v;
+  static constexpr int RSTEP = PowC<P, RD - KT>::v;  // rows between a thread's elements
+  static_assert(RD >= KT && RD <= LE && TH % W == 0 && TH <= 1024, "unsupported odd-p shape");
+};
+
+// Radix-p stages over the digits 0..KG-1 of the index of x (p^KG values).
+template <int P, int KG, bool INV, class T, int N>
+__device__ __forceinline__ void dft_digits(T (&x)[N]) {
+  static_assert(PowC<P, KG>::v == N, "p^KG values");
+#pragma unroll
+  for (int t = 0, st = 1; t < KG; ++t, st *= P) {
+#pragma unroll
+    for (int j0 = 0; j0 < N; ++j0)
+      if ((j0 / st) % P == 0) Dft<P, INV>::run(x + j0, st);
+  }
+}
+
+// Register groups over row digits [Q, Q + KG) for Q < RD - KT, then the next.
+template <int P, int LE, int RD, int KT, int Q, bool INV, class T, bool DONE = (Q >= RD - KT)>
+struct OddGroups {
+  static __device__ __forceinline__ void run(T* lds, int tid) {
+    using S = OddShape<P, LE, RD, KT>;
+    constexpr int KG = (RD - KT - Q) >= KT ? KT : (RD - KT - Q);
+    constexpr int R = PowC<P, KG>::v;
+    constexpr int PQ = PowC<P, Q>::v;
+    constexpr int STQ = S::W * PQ;          // element stride of digit Q
+    constexpr int GPT = S::E / R / S::TH;   // groups per thread
+    const int c = tid % S::W;
+    const int u0 = tid / S::W;
+#pragma unroll
+    for (int g = 0; g < GPT; ++g) {
+      // group tid + g TH: rows u = lo + PQ (j + R hi), lo < PQ
+      const int u = u0 + g * S::RSTEP;
+      const int lo = u % PQ, hi = u / PQ;
+      T* base = lds + c + S::W * (lo + PQ * R * hi);
+      T x[R];
+#pragma unroll
+      for (int j = 0; j < R; ++j) x[j] = base[j * STQ];
+      dft_digits<P, KG, INV>(x);
+#pragma unroll
+      for (int j = 0; j < R; ++j) base[j * STQ] = x[j];
+    }
+    lds_barrier();
+    OddGroups<P, LE, RD, KT, Q + KG, INV, T>::run(lds, tid);
+  }
+};
+template <int P, int LE, int RD, int KT, int Q, bool INV, class T>
+struct OddGroups<P, LE, RD, KT, Q, INV, T, true> {
+  static __device__ __forceinline__ void run(T*, int) {}
+};
+
+// EPI_REDUCE (complex double): the grouped sums of a pair of real columns
+// carried as one complex column (OddReduce below).
+template <int P, int LE, int RD, int KT, bool INV, class Tin, class T, class Tout, int EPI>
+__global__ void __launch_bounds__((OddShape<P, LE, RD, KT>::TH))
+    fwt_odd(const Tin* __restrict__ in, Tout* out, PassDesc d) {
+  using S = OddShape<P, LE, RD, KT>;
+  constexpr int TH = S::TH, EPT = S::EPT;
+  constexpr bool TOP_FIRST = RD == KT || (P == 3 && LE == 8 && std::is_same<T, float2>::value);
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T* lds = reinterpret_cast<T*>(smem_raw);
+  const int G = gridDim.x;
+  const int nb = d.ntiles * d.batch;
+  const int hw = blockIdx.x;
+  int lb = d.xcd ? xcd_first(hw, G) : hw;
+  const int tid = threadIdx.x;
+  // Global offset of element tid + k TH: goff0 + k gstep.
+  const uint32_t sd0 = (uint32_t)d.sd0;
+  const uint32_t goff0 = (uint32_t)(tid % S::W) + (uint32_t)(tid / S::W) * sd0;
+  const uint32_t gstep = (uint32_t)S::RSTEP * sd0;
+  auto locate = [&](int l, int& col, int& tile) {
+    if (EPI == EPI_REDUCE) {  // neighbours share a tile's weights
+      col = l % d.batch;
+      tile = l / d.batch;
+    } else {
+      col = l / d.ntiles;
+      tile = l % d.ntiles;
+    }
+  };
+  auto tile_base = [&](int tile) {
+    const int lo = tile % d.nlo;
+    const int hi = tile / d.nlo;
+    return (int64_t)lo * S::W + (int64_t)hi * d.shi;
+  };
+  Tin pre[EPT];
+  // live false: every load reads the tile's first element (one cache line), a
+  // stand-in that keeps the loads unconditional when there is no next tile.
+  auto prefetch = [&](int l, bool live) {
+    int col, tile;
+    locate(l, col, tile);
+    const Tin* src = in + (int64_t)col * d.col_in + tile_base(tile) + (live ? goff0 : 0u);
+    const uint32_t st = live ? gstep : 0u;
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) pre[k] = src[k * st];
+  };
+  if (lb < nb) prefetch(lb, true);
+  for (; lb < nb; lb += G) {
+    T v[EPT];
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) v[k] = cvt_in<Tin, T>(pre[k]);
+    if constexpr (TOP_FIRST) dft_digits<P, KT, INV>(v);  // the KT top digits of the pass
+    int col, tile;
+    locate(lb, col, tile);
+    const int64_t base = tile_base(tile) + goff0;
+    if constexpr (RD > KT) {
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) lds[tid + k * TH] = v[k];
+      lds_barrier();
+    }
+    prefetch(lb + G < nb ? lb + G : lb, lb + G < nb);  // unconditional: exact wait counts
+    OddGroups<P, LE, RD, KT, 0, INV, T>::run(lds, tid);
+    if constexpr (RD > KT) {
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) v[k] = lds[tid + k * TH];
+    }
+    if constexpr (!TOP_FIRST) dft_digits<P, KT, INV>(v);
+    if constexpr (EPI == EPI_STORE) {
+      Tout* dst = out + (int64_t)col * d.col_out + base;
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) dst[k * gstep] = cvt_out<T, Tout>(v[k], d.scale, d.scale64);
+      if constexpr (RD > KT) lds_barrier();
+    } else {
+      const double us = d.unscale[col];
+      double2 acc = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) {
+        const float2 wt = d.wts[base + (int64_t)k * gstep];
+        const T y = v[k];
+        const double ra = fmin(fmax(y.x * (double)wt.y, 0.0), 1.0);
+        const double rb = fmin(fmax(y.y * us * (double)wt.y, 0.0), 1.0);
+        const double ta = (double)wt.x * ra, tb = (double)wt.x * rb;
+        acc.x += ta;
+        acc.y += tb;
+        if (base + (int64_t)k * gstep == 0) {
+          if (2 * col == d.h0_col) *d.h0_out = ta;
+          if (2 * col + 1 == d.h0_col) *d.h0_out = tb;
+        }
+      }
+      // The threads' sums in a fixed order.
+      double2* red = reinterpret_cast<double2*>(smem_raw);
+      lds_barrier();
+      red[tid] = acc;
+      lds_barrier();
+      if (tid < 64) {
+        double2 t = red[tid];
+        for (int i = tid + 64; i < TH; i += 64) t = add(t, red[i]);
+        if constexpr (TH >= 64) {
+          for (int off = 32; off > 0; off >>= 1) {
+            t.x += __shfl_xor(t.x, off);
+            t.y += __shfl_xor(t.y, off);
+          }
+        } else if (tid == 0) {
+          for (int i = 1; i < TH; ++i) t = add(t, red[i]);
+        }
+        if (tid == 0) {
+          d.partial[(int64_t)(2 * col) * d.ntiles + tile] = t.x;
+          if (2 * col + 1 < d.ncols) d.partial[(int64_t)(2 * col + 1) * d.ntiles + tile] = t.y;
+        }
+      }
+      lds_barrier();
+    }
+  }
+}
+
+// ----------------------------------------------------------------- planner
+// Tiles as small as two passes allow, with rows of at least 40 bytes: more
+// workgroups at few points, and several per CU, whose loads, arithmetic and
+// stores overlap.
+std::vector<PassGeom> odd_plan(int p, int m, Kind work) {
+  std::vector<PassGeom> out;
+  auto first = [&](int le) { out.push_back({0, le, 0, le}); };
+  auto strided = [&](int le, int r) {
+    const int d0 = out.back().d0 + out.back().r;
+    out.push_back({d0, r, le - r, le});
+  };
+  const bool f64 = work == K_CF64;
+  // The largest net of one tile, and the exponent of every tile beyond it.
+  // Forward + inverse pairs, this choice against the generic passes before it
+  // (us): p = 3 double m = 9 20 / 30, m = 12 33 / 46, m = 14 111 / 153; p = 5
+  // float m = 8 26 / 55, m = 10 142 / 226, m = 11 845 / 1268 (5^5-element
+  // tiles and three passes: 1047); p = 5 double m = 10 309 / 519; p = 7 float
+  // m = 5 20 / 23 (one tile: 34), m = 8 104 / 154 (two passes of 7^5: 149),
+  // m = 9 846 / 1118 (7^4 and three passes: 921); double m = 8 200 / 250.
+  // (p = 3 float, 3^9..3^11 points: tiles of 3^8 elements, 17-20 us against
+  // 17 us with 3^7: their top-digits-first order is that of the larger nets,
+  // and float64 variances are computed from these float coefficients.)
+  int single, le;
+  if (p == 3) {
+    single = 8;
+    le = f64 ? (m <= 12 || m > 14 ? 7 : 8) : (m == 12 ? 7 : 8);
+  } else if (p == 5) {
+    single = f64 ? 5 : 6;
+    le = f64 ? (m <= 6 ? 4 : 5) : (m <= 9 ? 5 : 6);
+  } else {
+    single = 4;
+    le = m <= 5 ? 3 : (f64 || m <= 8 ? 4 : 5);
+  }
+  if (m <= single) {
+    first(m);
+    return out;
+  }
+  first(le);
+  const int rest = m - le;
+  // Digits of a strided pass: rows of 9 (p = 3), 5 or 25 (p = 5) and 7
+  // (p = 7) elements at least.
+  const int cap = p == 3 ? le - 2 : le - 1;
+  if (p == 3 && rest == 1) le = 7;  // 3^9 points, float: one digit needs rows of 3^6
+  const int n = (rest + cap - 1) / cap;
+  for (int i = 0, done = 0; i < n; ++i) {
+    const int r = (rest - done + (n - i) - 1) / (n - i);
+    strided(le, r);
+    done += r;
+  }
+  return out;
+}
+
+// ----------------------------------------------------------------- launch
+template <int P, int LE, int RD, int KT, bool INV, class Tin, class T, class Tout, int EPI>
+static int launch_odd(const void* in, void* out, const PassGeom& g, int m, int batch, double scale,
+                      const ReduceArgs* red, hipStream_t st) {
+  using S = OddShape<P, LE, RD, KT>;
+  const void* fn = (const void*)fwt_odd<P, LE, RD, KT, INV, Tin, T, Tout, EPI>;
+  const int64_t N = ipow(P, m);
+  PassDesc d{};
+  d.col_in = N;
+  d.col_out = N;
+  d.sd0 = ipow(P, g.d0);
+  d.shi = ipow(P, g.d0 + g.r);
+  d.r = g.r;
+  d.wdig = g.wdig;
+  d.w = S::W;
+  d.nlo = (int)(ipow(P, g.d0) / S::W);
+  d.E = S::E;
+  d.scale = (float)scale;
+  d.scale64 = scale;
+  const int64_t ntiles = N / S::E;
+  const int64_t nb = ntiles * batch;
+  d.ntiles = (int)ntiles;
+  d.batch = batch;
+  d.h0_col = -1;
+  if (red) {
+    d.wts = red->wts;
+    d.partial = red->partial;
+    d.h0_out = red->h0_out;
+    d.h0_col = red->h0_col;
+    d.unscale = red->unscale;
+    d.ncols = red->ncols;
+  }
+  const size_t lds = std::max<size_t>(RD > KT ? (size_t)S::E * sizeof(T) : 0, EPI == EPI_REDUCE ? S::TH * sizeof(double2) : 0);
+  if (int rc = allow_lds(fn, lds)) return rc;
+  int64_t G = (int64_t)occupancy(fn, S::TH, lds) * device_cus();
+  if (G >= nb) G = nb;
+  d.xcd = G >= 64 ? 1 : 0;
+  const Tin* inp = (const Tin*)in;
+  Tout* outp = (Tout*)out;
+  void* args[] = {(void*)&inp, (void*)&outp, (void*)&d};
+  const double work = red ? (double)N * (batch * sizeof(Tin) + sizeof(float2))
+                          : (double)N * batch * (sizeof(Tin) + sizeof(Tout));
+  return launch_timed(fn, dim3((unsigned)G), dim3(S::TH), args, lds, st,
+                      std::is_same<T, double2>::value ? FDWT_TC_PASS_F64 : FDWT_TC_PASS_CF32, work);
+}
+
+// Kinds of one shape.  Real input and, for the inverse, real output occur in
+// contiguous first passes and last passes; the grouped sums in last passes of
+// forward double transforms.
+template <int P, int LE, int RD, int KT, class R, class C>
+static int odd_kinds(bool inv, bool in_real, bool out_real, const void* in, void* out, const PassGeom& g, int m,
+                     int batch, double scale, const ReduceArgs* red, hipStream_t st) {
+  if (red) {
+    if constexpr (std::is_same<C, double2>::value)
+      return launch_odd<P, LE, RD, KT, false, C, C, C, EPI_REDUCE>(in, out, g, m, batch, scale, red, st);
+    else return fail(FDWT_EINVAL, "grouped sums are computed in double");
+  }
+  if (!inv) {
+    if (out_real) return fail(FDWT_EINVAL, "unsupported transform element types");
+    if constexpr (RD == LE) {
+      if (in_real) return launch_odd<P, LE, RD, KT, false, R, C, C, EPI_STORE>(in, out, g, m, batch, scale, red, st);
+    }
+    if (!in_real) return launch_odd<P, LE, RD, KT, false, C, C, C, EPI_STORE>(in, out, g, m, batch, scale, red, st);
+  } else if (!in_real) {
+    if (out_real) return launch_odd<P, LE, RD, KT, true, C, C, R, EPI_STORE>(in, out, g, m, batch, scale, red, st);
+    return launch_odd<P, LE, RD, KT, true, C, C, C, EPI_STORE>(in, out, g, m, batch, scale, red, st);
+  }
+  return fail(FDWT_EINVAL, "unsupported transform element types");
+}
+
+// Register digits of a shape: two where the tile's p^(LE - 2) threads still
+// fill waves (p = 5 float, m = 9: 43 against 46 us a pair with one), but one
+// for p = 5 in double (25 complex values and as many prefetched leave few
+// waves: eff_dim at m = 9, s = 20 823 against 729 us).
+constexpr int odd_kt(int p, int le, int rd, bool f64) { return rd >= 2 && le >= 5 && !(p == 5 && f64) ? 2 : 1; }
+
+template <int P, class R, class C>
+static int odd_shape(bool inv, bool in_real, bool out_real, const void* in, void* out, const PassGeom& g, int m,
+                     int batch, double scale, const ReduceArgs* red, hipStream_t st) {
+  constexpr bool D = std::is_same<C, double2>::value;
+#define FDWT_ODD_KT(LE, RD, KT)  \
+  if (g.le == LE && g.r == RD) \
+  return odd_kinds<P, LE, RD, KT, R, C>(inv, in_real, out_real, in, out, g, m, batch, scale, red, st)
+#define FDWT_ODD(LE, RD) FDWT_ODD_KT(LE, RD, odd_kt(P, LE, RD, D))
+  if (g.le < 1 || g.r > g.le || g.wdig != g.le - g.r || g.d0 < g.wdig || (g.d0 == 0) != (g.r == g.le))
+    return fail(FDWT_EINVAL, "not an odd-p pass shape");
+  FDWT_ODD(1, 1);
+  FDWT_ODD(2, 2);
+  FDWT_ODD(3, 3);
+  FDWT_ODD(4, 4);
+  if constexpr (P == 3) {
+    FDWT_ODD(5, 5);
+    FDWT_ODD(6, 6);
+    FDWT_ODD(7, 7);
+    FDWT_ODD(7, 1);
+    FDWT_ODD(7, 2);
+    FDWT_ODD(7, 3);
+    FDWT_ODD(7, 4);
+    FDWT_ODD(7, 5);
+    if constexpr (D) {
+      FDWT_ODD(8, 8);
+      FDWT_ODD(8, 5);
+      FDWT_ODD(8, 6);
+    } else {
+      // Three register digits (243 threads, three workgroups per CU) pay
+      // when they let every tile run in one round and two (729 threads, two
+      // per CU) would not (3^14 points: 729 tiles).
+      const int64_t nb = ipow(3, m) / 6561 * batch;
+      const bool kt3 = g.le == 8 && nb > 2 * (int64_t)device_cus() && nb <= 3 * (int64_t)device_cus();
+#define FDWT_ODD8(RD) \
+  if (kt3) { FDWT_ODD_KT(8, RD, 3); } \
+  FDWT_ODD_KT(8, RD, 2)
+      FDWT_ODD8(8);
+      FDWT_ODD_KT(8, 2, 2);
+      FDWT_ODD8(4);
+      FDWT_ODD8(5);
+      FDWT_ODD8(6);
+      FDWT_ODD8(3);
+#undef FDWT_ODD8
+    }
+  } else if constexpr (P == 5) {
+    FDWT_ODD(5, 5);
+    FDWT_ODD(5, 2);
+    FDWT_ODD(5, 3);
+    FDWT_ODD(5, 4);
+    if constexpr (D) {
+      FDWT_ODD(4, 2);
+    } else {
+      FDWT_ODD(6, 6);
+      FDWT_ODD(6, 4);
+      FDWT_ODD(6, 5);
+    }
+  } else {
+    FDWT_ODD(3, 2);
+    FDWT_ODD(4, 2);
+    FDWT_ODD(4, 3);
+    if constexpr (!D) {
+      FDWT_ODD(5, 5);
+      FDWT_ODD(5, 4);
+    }
+  }
+#undef FDWT_ODD
+#undef FDWT_ODD_KT
+  return fail(FDWT_EINVAL, "not an odd-p pass shape");
+}
+
+// One pass of a p = 3, 5, 7 transform in working type `work` (K_CF32, K_CF64).
+int odd_pass(int p, bool inv, Kind ik, Kind work, Kind ok, const void* in, void* out, const PassGeom& g, int m,
+             int batch, double scale, const ReduceArgs* red, hipStream_t st) {
+  if (work == K_CF32) {
+    const bool ir = ik == K_F32, orl = ok == K_F32;
+    if ((!ir && ik != K_CF32) || (!orl && ok != K_CF32)) return fail(FDWT_EINVAL, "unsupported transform element types");
+    if (p == 3) return odd_shape<3, float, float2>(inv, ir, orl, in, out, g, m, batch, scale, red, st);
+    if (p == 5) return odd_shape<5, float, float2>(inv, ir, orl, in, out, g, m, batch, scale, red, st);
+    if (p == 7) return odd_shape<7, float, float2>(inv, ir, orl, in, out, g, m, batch, scale, red, st);
+  } else if (work == K_CF64) {
+    const bool ir = ik == K_F64, orl = ok == K_F64;
+    if ((!ir && ik != K_CF64) || (!orl && ok != K_CF64)) return fail(FDWT_EINVAL, "unsupported transform element types");
+    if (p == 3) return odd_shape<3, double, double2>(inv, ir, orl, in, out, g, m, batch, scale, red, st);
+    if (p == 5) return odd_shape<5, double, double2>(inv, ir, orl, in, out, g, m, batch, scale, red, st);
+    if (p == 7) return odd_shape<7, double, double2>(inv, ir, orl, in, out, g, m, batch, scale, red, st);
+  }
+  return fail(FDWT_EUNSUPPORTED, "p must be 3, 5 or 7");
+}
+
+}  // namespace fdwt

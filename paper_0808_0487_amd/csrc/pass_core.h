@@ -47,7 +47,49 @@ struct PassDesc {
   // c times the column stride (a group of equal-size jobs anywhere in memory).
   const void* const* in_tab;
   void* const* out_tab;
+
+  // Grouped sums of paired columns (odd p): the imaginary part of column c is
+  // multiplied by unscale[c]; ncols real columns in all.
+  const double* unscale;
+  int32_t ncols;
 };
+
+// One pass of a plan: digits [d0, d0 + r), rows of p^wdig elements; le: the
+// tile exponent of an odd-p pass (wdig + r).
+struct PassGeom {
+  int d0, r, wdig, le;
+};
+
+// Optional grouped-sum epilogue of the last pass.
+struct ReduceArgs {
+  const float2* wts;
+  double* partial;  // [ncols][fwt_reduce_parts]
+  double* h0_out;
+  int h0_col;
+  const double* unscale;  // p odd: per pair of columns
+  int ncols;
+};
+
+// fwt.hip: compute units of the current device, and workgroups per CU of a
+// kernel (both cached).
+int device_cus();
+int occupancy(const void* fn, int threads, size_t lds);
+// odd.hip: the plan of a p = 3, 5, 7 transform in working type K_CF32 or
+// K_CF64, and one pass of it.
+std::vector<PassGeom> odd_plan(int p, int m, Kind work);
+int odd_pass(int p, bool inv, Kind ik, Kind work, Kind ok, const void* in, void* out, const PassGeom& g, int m,
+             int batch, double scale, const ReduceArgs* red, hipStream_t st);
+
+// First logical block of workgroup hw.  Workgroups are dispatched round-robin
+// over the 8 XCDs (hw mod 8); XCD x gets the contiguous range of the
+// ceil((G - x) / 8) logical blocks starting at x floor(G/8) + min(x, G mod 8),
+// so neighbouring tiles (which share cache lines and DRAM pages) meet in the
+// same L2.  A bijection of [0, G) for any G, so a grid need not be a multiple
+// of 8 (3^14 points make 729 tiles: one round, not two).
+__device__ __forceinline__ int xcd_first(int hw, int G) {
+  const int x = hw & 7, q = G >> 3, r = G & 7;
+  return x * q + (x < r ? x : r) + (hw >> 3);
+}
 
 enum Epilogue { EPI_STORE = 0, EPI_REDUCE = 1 };
 

@@ -47,11 +47,15 @@ struct NetArgs {
 // Column layout: 0 = K, 1..s = U_d (d = 1..s), s+1..2s = Q_j (j = 1..s).
 // Writes columns [c0, c1) to out[(c - c0) * N + n].  The elementary symmetric
 // polynomials e_0..e_SMAX live in registers (updates unrolled, truncated per
-// chunk of coordinates where the higher ones are still zero).
+// chunk of coordinates where the higher ones are still zero).  p odd: the
+// columns from U_1 on are written as pairs, columns c0 + 2 i and c0 + 2 i + 1
+// as the parts of complex column i, the second times pscale[(column - 1) / 2]
+// (zero when there is none); c0 is odd.
 template <int P, int SMAX>
 __global__ void __launch_bounds__(kChunk) k_kernel_cols(NetArgs na, const double* __restrict__ tk,
                                                         const double* __restrict__ tr, int c0, int c1,
-                                                        double* __restrict__ out) {
+                                                        double* __restrict__ out,
+                                                        const double* __restrict__ pscale) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int s = na.s;
   double* ltk = reinterpret_cast<double*>(smem);       // [s][kTab]
@@ -79,7 +83,22 @@ __global__ void __launch_bounds__(kChunk) k_kernel_cols(NetArgs na, const double
     const int64_t nn = n < N ? n : N - 1;
     int orr = 0, ok = 0;
     if constexpr (P != 2) oc.split(nn, orr, ok);
-    double K = 1.0, u = 0.0;
+    double K = 1.0, u = 0.0, held = 0.0;
+    auto emit = [&](int c, double v) {  // column c of [c0, c1)
+      if constexpr (P == 2) {
+        if (n < N) out[(int64_t)(c - c0) * N + n] = v;
+      } else {
+        const int i = c - c0;
+        if (i & 1) {
+          v *= pscale[(c - 1) >> 1];
+        } else {
+          held = v;
+          v = 0.0;
+        }
+        if (((i & 1) || c + 1 == c1) && n < N)
+          reinterpret_cast<double2*>(out)[(int64_t)(i >> 1) * N + n] = make_double2(held, v);
+      }
+    };
     double e[SMAX + 1];
 #pragma unroll
     for (int i = 0; i <= SMAX; ++i) e[i] = i == 0 ? 1.0 : 0.0;
@@ -100,7 +119,7 @@ __global__ void __launch_bounds__(kChunk) k_kernel_cols(NetArgs na, const double
           const double r = ltr[j * kTab + t];
           u = u + r + u * r;  // (1 + u)(1 + r) - 1
           const int c = 1 + j;
-          if (c >= c0 && c < c1 && n < N) out[(int64_t)(c - c0) * N + n] = u;
+          if (c >= c0 && c < c1) emit(c, u);
           if (need_q) {
 #pragma unroll
             for (int i = 4 * q + 4; i >= 1; --i) e[i] += r * e[i - 1];
@@ -108,14 +127,12 @@ __global__ void __launch_bounds__(kChunk) k_kernel_cols(NetArgs na, const double
         }
       }
     }
-    if (n < N) {
-      if (c0 == 0) out[n] = K;
-      if (need_q) {
+    if (c0 == 0 && n < N) out[n] = K;
+    if (need_q) {
 #pragma unroll
-        for (int j = 1; j <= SMAX; ++j) {
-          const int c = s + j;
-          if (j <= s && c >= c0 && c < c1) out[(int64_t)(c - c0) * N + n] = e[j];
-        }
+      for (int j = 1; j <= SMAX; ++j) {
+        const int c = s + j;
+        if (j <= s && c >= c0 && c < c1) emit(c, e[j]);
       }
     }
   }
@@ -547,9 +564,13 @@ static NetArgs net_args(const Net& net) {
 
 // Kernel-data tables: tk[j][t] = 1 + gamma_j K'(t+1) for t < m, 1 + gamma_j for
 // t >= m (x = 0); tr[j][t] = gamma_j^2 R'(t+1), gamma_j^2 R'(0).  Laid out as
-// tk then tr, each [s][kTab].
+// tk then tr, each [s][kTab], then (p odd) the pair scales [s] and their
+// inverses [s]: the variance columns U_1..U_s, Q_1..Q_{s-1} are transformed
+// two to a complex column, and a power of two brings the second of a pair to
+// the first one's magnitude (both at x = 0, their maximum), so that neither
+// loses digits to the other's rounding.
 static std::vector<double> kernel_tables(const Net& net, const fdwt_kernel* k) {
-  std::vector<double> t((size_t)2 * net.s * kTab, 0.0);
+  std::vector<double> t(kernel_tables_bytes(net) / sizeof(double), 0.0);
   for (int j = 0; j < net.s; ++j) {
     const double g = k->gamma[j];
     for (int i = 0; i < kTab; ++i) {
@@ -558,10 +579,38 @@ static std::vector<double> kernel_tables(const Net& net, const fdwt_kernel* k) {
       t[(size_t)(net.s + j) * kTab + i] = g * g * rprime(net.p, k->alpha, dig);
     }
   }
+  if (net.p != 2) {
+    const int s = net.s;
+    std::vector<double> col(2 * s, 0.0), e(s + 1, 0.0);  // U_d, Q_j at x = 0
+    e[0] = 1.0;
+    double u = 0.0;
+    for (int j = 0; j < s; ++j) {
+      const double r = t[(size_t)(s + j) * kTab + net.m];
+      u = u + r + u * r;
+      col[j] = u;
+      for (int i = j + 1; i >= 1; --i) e[i] += r * e[i - 1];
+    }
+    for (int j = 1; j <= s; ++j) col[s + j - 1] = e[j];
+    double* sc = t.data() + (size_t)2 * s * kTab;
+    for (int i = 0; i < s; ++i) {
+      int ea = 0, eb = 0;
+      const double a = col[2 * i], b = col[2 * i + 1];
+      const bool ok = a > 0.0 && b > 0.0 && std::isfinite(a) && std::isfinite(b);
+      if (ok) {
+        (void)std::frexp(a, &ea);
+        (void)std::frexp(b, &eb);
+      }
+      const int sh = std::max(-1000, std::min(1000, ea - eb));
+      sc[i] = std::ldexp(1.0, sh);
+      sc[s + i] = std::ldexp(1.0, -sh);
+    }
+  }
   return t;
 }
 
-size_t kernel_tables_bytes(const Net& net) { return (size_t)2 * net.s * kTab * sizeof(double); }
+size_t kernel_tables_bytes(const Net& net) {
+  return ((size_t)2 * net.s * kTab + (net.p == 2 ? 0 : 2 * net.s)) * sizeof(double);
+}
 
 // Consecutive slices of a workspace; with base == nullptr it only measures.
 struct Carve {
@@ -582,7 +631,8 @@ static int kcols_launch(const Net& net, const double* tk, const double* tr, int 
                      (P == 2 ? (size_t)net.s * 257 * 4 : OddCoords<P == 2 ? 3 : P>::lds_bytes(net.s));
   if (int rc = allow_lds((const void*)k_kernel_cols<P, SMAX>, lds)) return rc;
   NetArgs na = net_args(net);
-  void* args[] = {(void*)&na, (void*)&tk, (void*)&tr, (void*)&c0, (void*)&c1, (void*)&out};
+  const double* pscale = tk + (size_t)2 * net.s * kTab;  // p odd: after the two tables
+  void* args[] = {(void*)&na, (void*)&tk, (void*)&tr, (void*)&c0, (void*)&c1, (void*)&out, (void*)&pscale};
   if constexpr (P == 2) {
     if (net.N % 512 == 0) {
       const size_t lds2 = (size_t)2 * net.s * kTab * 8 + (size_t)net.s * 258 * 4;
@@ -621,8 +671,8 @@ static int launch_kernel_cols(const Net& net, const double* tk, const double* tr
 
 static unsigned grid1(int64_t n) { return (unsigned)std::min<int64_t>((n + 255) / 256, 4096); }
 
-int fwt_reduce_f64(int p, int m, const double* in, void* tmp, int batch, const float2* wts, double* partial,
-                   double* h0_out, int h0_col, int64_t* parts, hipStream_t st);
+int fwt_reduce_f64(int p, int m, void* in, void* tmp, int ncols, const float2* wts, const double* unscale,
+                   double* partial, double* h0_out, int h0_col, int64_t* parts, hipStream_t st);
 int64_t fwt_reduce_parts(int p, int m, size_t elem_bytes);
 bool fwt_p2_split_ok(int m);
 bool fwt_p2_blocked_ok(int m);
@@ -644,7 +694,7 @@ struct SpecWs {
   double* A;    // kernel data (p odd; p = 2 transforms in place in the spectrum)
 };
 static void spec_layout(const Net& net, Carve& cv, SpecWs& w) {
-  w.tab = (double*)cv.take((size_t)2 * net.s * kTab * sizeof(double));
+  w.tab = (double*)cv.take(kernel_tables_bytes(net));
   w.A = net.p == 2 ? nullptr : (double*)cv.take((size_t)net.N * 8);
 }
 size_t spectrum_ws_bytes(const Net& net) {
@@ -912,12 +962,13 @@ int run_spline_eval(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
 }
 
 // -------------------------------------------------- effective dimension
-// Columns of kernel data per chunk so that data (8 B) + intermediate (8 or
-// 16 B) per column stay within `budget` bytes.  The variances do not depend
-// on the chunking: every column is transformed and reduced on its own.
+// Columns of kernel data per chunk so that they stay within `budget` bytes:
+// p = 2, data and intermediate, 16 B per column and point; p odd, whole pairs
+// of 16 B, transformed in place.  The variances do not depend on the
+// chunking: every column (pair) is transformed and reduced on its own.
 int eff_dim_chunk(const Net& net, size_t budget) {
-  const size_t wb = (net.p == 2) ? 8 : 16;
-  const size_t per_col = (size_t)net.N * (8 + wb);
+  const size_t per_col = (size_t)net.N * 16;
+  if (net.p != 2) return 2 * (int)std::max<size_t>(1, std::min<size_t>((size_t)net.s, budget / per_col));
   return (int)std::max<size_t>(1, std::min<size_t>((size_t)2 * net.s, budget / per_col));
 }
 
@@ -953,10 +1004,10 @@ static void eff_layout(const Net& net, bool have_gk, int ch, Carve& cv, EffWs& w
   const int64_t parts = fwt_reduce_parts(net.p, net.m, wb);
   w.gk = have_gk ? nullptr : cv.take(spectrum_bytes(net));
   w.sw = have_gk ? nullptr : cv.take(spectrum_ws_bytes(net));
-  w.tab = (double*)cv.take((size_t)2 * net.s * kTab * sizeof(double));
+  w.tab = (double*)cv.take(kernel_tables_bytes(net));
   w.wts = (float2*)cv.take((size_t)net.N * sizeof(float2));
   w.A = (double*)cv.take((size_t)ch * net.N * 8);
-  w.B = cv.take((size_t)ch * net.N * wb);
+  w.B = net.p == 2 ? cv.take((size_t)ch * net.N * 8) : nullptr;
   w.partial = (double*)cv.take((size_t)ncols * parts * sizeof(double) + kRedBlocks * sizeof(double));
   w.qmc_partial = w.partial ? w.partial + (size_t)ncols * parts : nullptr;
   w.res = (double*)cv.take(eff_dim_res_bytes(net));
@@ -1027,7 +1078,9 @@ int eff_dim_enqueue(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
       rc = launch_kernel_cols(net, w.tab, tr, c0 + 1, c1 + 1, w.A, st);
       if (rc) return rc;
       int64_t t = 0;
-      rc = fwt_reduce_f64(p, net.m, w.A, w.B, c1 - c0, w.wts, w.partial + (size_t)c0 * parts, h0, h0_col, &t, st);
+      const double* unscale = w.tab + (size_t)2 * s * kTab + s + c0 / 2;
+      rc = fwt_reduce_f64(p, net.m, w.A, w.B, c1 - c0, w.wts, p == 2 ? nullptr : unscale,
+                          w.partial + (size_t)c0 * parts, h0, h0_col, &t, st);
     }
     if (rc) return rc;
   }
