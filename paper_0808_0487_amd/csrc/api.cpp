@@ -121,19 +121,12 @@ int launch_timed(const void* fn, dim3 grid, dim3 block, void** args, size_t lds,
 
 int query_depth(int p) { return p == 2 ? 32 : (p == 3 ? 20 : (p == 5 ? 13 : (p == 7 ? 11 : 0))); }
 
-// K'(z,0) and R'(z,0) of Section 4 for z whose first non-zero base-p digit is
-// digit i (i = 0: z = 0).
+// K'(z,0) of Section 4 for z whose first non-zero base-p digit is digit i
+// (i = 0: z = 0).
 double kprime(int p, double alpha, int i) {
   if (i == 0) return 1.0;
   return 1.0 - std::pow((double)p, i * (1.0 - alpha)) * (std::pow((double)p, alpha) - 1.0) / (p - 1.0);
 }
-double rprime(int p, double alpha, int i) {
-  const double pa = std::pow((double)p, alpha), p2a = std::pow((double)p, 2.0 * alpha);
-  const double A = (pa - p) * (pa - p) / ((p - 1.0) * (p2a - p));
-  if (i == 0) return A;
-  return A * (1.0 - std::pow((double)p, i * (1.0 - 2.0 * alpha)) * (p2a - 1.0) / (p - 1.0));
-}
-
 int ensure_ws(Scratch& sc, size_t bytes, hipStream_t st) {
   if (sc.ws_bytes >= bytes) return FDWT_OK;
   if (sc.fixed)

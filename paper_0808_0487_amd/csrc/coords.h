@@ -21,6 +21,30 @@
 
 namespace fdwt {
 
+// Per-coordinate tables of a Walsh kernel in LDS: lk[j][t] = 1 + gamma_j K',
+// lr[j][t] = gamma_j^2 R' (rows of `row` entries, t < row <= kTab; either
+// may be null).  A wave takes every nw-th coordinate, lane t its entry t.
+// Callers put a barrier after.
+__device__ __forceinline__ void stage_kern_tables(const KernTab& kt, int s, int row, double* lk, double* lr) {
+#pragma clang fp contract(off)
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double kv = 0.0, rv = 0.0;
+#pragma unroll
+  for (int t = 0; t < kTab; ++t) {
+    if (lane == t) {
+      kv = kt.kp[t];
+      rv = kt.rp[t];
+    }
+  }
+  for (int j = wv; j < s; j += (int)(blockDim.x + 63) >> 6) {
+    const double g = kt.gamma[j];
+    if (lane < row) {
+      if (lk) lk[j * row + lane] = 1.0 + g * kv;
+      if (lr) lr[j * row + lane] = g * g * rv;
+    }
+  }
+}
+
 constexpr int kChunk = 256;  // points per group (= threads per workgroup)
 
 struct P2Coords {

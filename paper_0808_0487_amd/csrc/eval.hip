@@ -67,12 +67,11 @@ struct RowCfg<7> {
 template <int P>
 constexpr int row_bytes() { return RowCfg<P>::NT * RowCfg<P>::RPT * (16 + RowCfg<P>::R2); }  // LDS per coordinate
 
-// Values of one coordinate's factor, in a row of kRowT floats: entry k < D
-// for first differing digit k, entry D when all D digits agree, and at kRowPfx
-// (an integer) the first K digits of X_j(1), X_j(2) (p = 2: bits 1..0 and
-// 3..2, first digit in the higher bit) or of X_j(1) (p odd).
-constexpr int kRowT = 68;
-constexpr int kRowPfx = 40;
+// Values of one coordinate's factor in LDS after the rows, kRowT floats each:
+// entry k < D for first differing digit k, entry D when all D digits agree.
+// The first K digits of X_j(1) and X_j(2) (p = 2: bits 1..0 and 3..2 of
+// kt.ix[j], first digit in the higher bit) or of X_j(1) (p odd: kt.ix[j]).
+constexpr int kRowT = kTab;
 
 // Leading zero digits of b (-) (first K digits of X_j(r)), K if all are zero.
 template <int P>
@@ -205,17 +204,32 @@ __device__ __forceinline__ void mul_row(float* pr, uint32_t a, uint32_t off) {
 template <int P, int SG, int TH>
 __global__ void __launch_bounds__(TH) k_eval_rows(const uint32_t* __restrict__ xw, const float* __restrict__ c, int nblk,
                                                   int s, const void* __restrict__ qv, int64_t nq,
-                                                  const float* __restrict__ tt, int tqw, int bpc,
-                                                  df* __restrict__ partial) {
+                                                  KernTab kt, int tqw, int bpc, df* __restrict__ partial) {
   using R = RowCfg<P>;
   constexpr int B = R::B, NT = R::NT, JB = row_bytes<P>(), HB = 64 / B;
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x;
+  float* tt = reinterpret_cast<float*>(smem + (size_t)s * JB);  // [s][kRowT]
+  int* pfx = reinterpret_cast<int*>(tt + s * kRowT);           // [s]
+  {
+#pragma clang fp contract(off)
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    double kv = 0.0;
+#pragma unroll
+    for (int t = 0; t < kTab; ++t)
+      if (lane == t) kv = kt.kp[t];
+    for (int j = w; j < s; j += TH / 64) {
+      const double g = kt.gamma[j];
+      if (lane < kTab) tt[j * kRowT + lane] = (float)(1.0 + g * kv);
+      if (lane == kTab) pfx[j] = kt.ix[j];
+    }
+  }
+  __syncthreads();
   // Rows: entry r of row (t, b) of coordinate j.
   for (int i = tid; i < s * NT * R::RPT; i += TH) {
     const int j = i / (NT * R::RPT), e = i - j * (NT * R::RPT), t = e / R::RPT, b = e - t * R::RPT;
     const float* T = tt + j * kRowT;
-    const int pf = __float_as_int(T[kRowPfx]);
+    const int pf = pfx[j];
     const int dg = R::NT < 32 ? t : t / R::DB;  // first non-zero digit: K + dg (K + ND or more: see exact())
     float* row = reinterpret_cast<float*>(smem + (size_t)j * JB + e * 16);
     float* row2 = reinterpret_cast<float*>(smem + (size_t)j * JB + NT * R::RPT * 16 + e * R::R2);
@@ -306,7 +320,7 @@ __global__ void __launch_bounds__(TH) k_eval_rows(const uint32_t* __restrict__ x
       const uint32_t x = xp[j], z = v.x ^ x;
       const int t = __clz(z), dg = t / R::DB;
       const float* T = tt + j * kRowT;
-      const int pf = __float_as_int(T[kRowPfx]);
+      const int pf = pfx[j];
       int b;
       if constexpr (P == 2) b = (int)((z >> 4) & 3u);
       else b = ((int)(v.y & 255u) + P - (int)((x & 7u) - 1u)) % P;
@@ -366,7 +380,9 @@ __global__ void __launch_bounds__(TH) k_eval_rows(const uint32_t* __restrict__ x
 static int row_k(int p) { return p == 2 ? 2 : 1; }
 static int row_bytes_of(int p) { return p == 2 ? row_bytes<2>() : p == 3 ? row_bytes<3>() : p == 5 ? row_bytes<5>() : row_bytes<7>(); }
 
-// Prefix information of coordinate j (kRowPfx), or -1 when the first K columns
+static size_t rows_lds(int p, int s) { return (size_t)s * (row_bytes_of(p) + kRowT * 4 + 4); }
+
+// Prefixes of coordinate j (see kRowT), or -1 when the first K columns
 // of C_j are not a non-singular K x K block over zeros.
 static int row_prefix(const Net& net, int j) {
   auto C = [&](int r, int c) { return (int)net.C[((size_t)j * net.m + r) * net.m + c]; };
@@ -381,9 +397,9 @@ static int row_prefix(const Net& net, int j) {
 // Nets the rows serve: the first K columns of every generator matrix as
 // above, the points have no digits
 // beyond the words' K + ND (p = 5: m <= 10; the other primes' largest nets
-// fit), and the rows of all coordinates fit a CU's LDS (p = 7: s <= 45).
+// fit), and the rows of all coordinates fit a CU's LDS (p = 7: s <= 43).
 bool eval_rows_ok(const Net& net) {
-  if (net.m < row_k(net.p) || (net.p == 5 && net.m > 10) || net.s * row_bytes_of(net.p) > 160 * 1024) return false;
+  if (net.m < row_k(net.p) || (net.p == 5 && net.m > 10) || rows_lds(net.p, net.s) > 160 * 1024) return false;
   for (int j = 0; j < net.s; ++j)
     if (row_prefix(net, j) < 0) return false;
   return true;
@@ -414,12 +430,9 @@ void eval_rows_grid(int p, int s, int64_t N, int64_t nq, int* tqw_out, int* gy_o
   *bpc_out = (int)bpc;
 }
 
-// Fills the rows of tt ([s][kRowT]; entries 0..D hold the factors already).
-void eval_rows_prefixes(const Net& net, float* tt) {
-  for (int j = 0; j < net.s; ++j) {
-    const int pf = row_prefix(net, j);
-    std::memcpy(tt + (size_t)j * kRowT + kRowPfx, &pf, sizeof pf);
-  }
+// The prefixes of every coordinate into kt.ix.
+void eval_rows_prefixes(const Net& net, KernTab& kt) {
+  for (int j = 0; j < net.s; ++j) kt.ix[j] = row_prefix(net, j);
 }
 
 static unsigned rows_grid1(int64_t n) { return (unsigned)std::min<int64_t>((n + 255) / 256, 4096); }
@@ -456,17 +469,17 @@ int launch_row_queries(const Net& net, const uint32_t* q, int64_t nq, void* out,
 
 template <int P, int SG>
 static int launch_rows_sg(const Net& net, const uint32_t* xw, const float* c, int64_t nq, const void* qv,
-                          const float* tt, df* partial, int tqw, int gy, int bpc, hipStream_t st) {
+                          const KernTab& kt, df* partial, int tqw, int gy, int bpc, hipStream_t st) {
   if constexpr ((SG - 3) * row_bytes<P>() > 160 * 1024) {
     return fail(FDWT_EINVAL, "evaluation rows exceed the LDS");
   } else {
     constexpr int TH = row_threads(P, SG);
     auto fn = k_eval_rows<P, SG, TH>;
-    const size_t lds = std::max<size_t>((size_t)net.s * row_bytes<P>(), (size_t)TH * sizeof(df));
+    const size_t lds = std::max<size_t>(rows_lds(P, net.s), (size_t)TH * sizeof(df));
     if (int rc = allow_lds((const void*)fn, lds)) return rc;
     const dim3 grid((unsigned)((nq + 64 * tqw - 1) / (64 * tqw)), (unsigned)gy);
     const int nblk = (int)(net.N / RowCfg<P>::B);
-    hipLaunchKernelGGL(fn, grid, dim3(TH), lds, st, xw, c, nblk, net.s, qv, nq, tt, tqw, bpc, partial);
+    hipLaunchKernelGGL(fn, grid, dim3(TH), lds, st, xw, c, nblk, net.s, qv, nq, kt, tqw, bpc, partial);
     FDWT_HIP(hipGetLastError());
     return FDWT_OK;
   }
@@ -474,10 +487,10 @@ static int launch_rows_sg(const Net& net, const uint32_t* xw, const float* c, in
 
 template <int P>
 static int launch_rows_p(const Net& net, const uint32_t* xw, const float* c, int64_t nq, const void* qv,
-                         const float* tt, df* partial, int tqw, int gy, int bpc, hipStream_t st) {
+                         const KernTab& kt, df* partial, int tqw, int gy, int bpc, hipStream_t st) {
   switch ((net.s + 3) / 4) {
 #define FDWT_ROWS(G) \
-  case G: return launch_rows_sg<P, 4 * G>(net, xw, c, nq, qv, tt, partial, tqw, gy, bpc, st)
+  case G: return launch_rows_sg<P, 4 * G>(net, xw, c, nq, qv, kt, partial, tqw, gy, bpc, st)
     FDWT_ROWS(1); FDWT_ROWS(2); FDWT_ROWS(3); FDWT_ROWS(4); FDWT_ROWS(5); FDWT_ROWS(6); FDWT_ROWS(7); FDWT_ROWS(8);
     FDWT_ROWS(9); FDWT_ROWS(10); FDWT_ROWS(11); FDWT_ROWS(12); FDWT_ROWS(13); FDWT_ROWS(14); FDWT_ROWS(15);
     FDWT_ROWS(16);
@@ -488,16 +501,16 @@ static int launch_rows_p(const Net& net, const uint32_t* xw, const float* c, int
 
 // Partial sums [gy][nq] of Sf at nq queries (p = 2: the queries themselves, p
 // odd: their words from launch_row_queries).
-int launch_eval_rows(const Net& net, const uint32_t* xw, const float* c, int64_t nq, const void* qv, const float* tt,
+int launch_eval_rows(const Net& net, const uint32_t* xw, const float* c, int64_t nq, const void* qv, const KernTab& kt,
                      df* partial, hipStream_t st) {
   int tqw, gy, bpc;
   eval_rows_grid(net.p, net.s, net.N, nq, &tqw, &gy, &bpc);
   switch (net.p) {
-    case 2: return launch_rows_p<2>(net, xw, c, nq, qv, tt, partial, tqw, gy, bpc, st);
-    case 3: return launch_rows_p<3>(net, xw, c, nq, qv, tt, partial, tqw, gy, bpc, st);
-    case 5: return launch_rows_p<5>(net, xw, c, nq, qv, tt, partial, tqw, gy, bpc, st);
+    case 2: return launch_rows_p<2>(net, xw, c, nq, qv, kt, partial, tqw, gy, bpc, st);
+    case 3: return launch_rows_p<3>(net, xw, c, nq, qv, kt, partial, tqw, gy, bpc, st);
+    case 5: return launch_rows_p<5>(net, xw, c, nq, qv, kt, partial, tqw, gy, bpc, st);
   }
-  return launch_rows_p<7>(net, xw, c, nq, qv, tt, partial, tqw, gy, bpc, st);
+  return launch_rows_p<7>(net, xw, c, nq, qv, kt, partial, tqw, gy, bpc, st);
 }
 
 }  // namespace fdwt

@@ -52,6 +52,23 @@ struct Scratch {
   hipEvent_t pin_done = nullptr;  // owned mode: last copy through `pin` finished
 };
 
+// ---------------------------------------------------------- kernel tables
+constexpr int kTab = 33;  // entries per coordinate of the digit-indexed tables
+
+// What the kernels need of a Walsh kernel (alpha, gamma), passed by value:
+// K' and R' by the index t of the first non-zero digit (t >= m, or D for
+// query tables: no digit).  The per-coordinate tables 1 + gamma_j K' and
+// gamma_j^2 R' are formed from it in LDS (stage_kern_tables, coords.h), with
+// the roundings of the same expressions on the host, so that no call uploads
+// tables.
+struct KernTab {
+  double kp[kTab], rp[kTab];
+  double gamma[kMaxS];
+  // Exponents of the paired variance columns (p odd), or the prefixes of the
+  // evaluation rows.
+  int32_t ix[kMaxS];
+};
+
 // ------------------------------------------------------------------- net
 struct Net {
   int p = 0, m = 0, s = 0;
@@ -73,6 +90,9 @@ struct Net {
   size_t spec_bytes = 0;
   std::vector<double> spec_key;
   hipEvent_t spec_ready = nullptr;
+  // Pinned host results of eff_dim and split_cost, written by their last
+  // kernel (allocated on first use, 2 kMaxS + 2 doubles).
+  double* res_host = nullptr;
 };
 
 }  // namespace fdwt
@@ -154,7 +174,9 @@ int fwt_run(int p, int m, bool inverse, Kind in_kind, const void* in, Kind work_
 // spline.hip.  Every step takes an explicit Scratch; *_ws_bytes return the
 // workspace a step needs (the step lays it out the same way), so a caller
 // can lend exactly that much.
-size_t kernel_tables_bytes(const Net& net);  // staged kernel tables (K' and R' per coordinate)
+// K' and R' for indices t < digits, and for no digit from there on.
+KernTab kern_tab(int p, int digits, const fdwt_kernel* kern);
+int ensure_res_host(Net& net);  // net.res_host
 size_t spectrum_bytes(const Net& net);     // kernel spectrum: N doubles (p = 2), N complex doubles
 size_t spectrum_ws_bytes(const Net& net);
 int run_spectrum(Net& net, Scratch& sc, const fdwt_kernel* kern, void* gk, hipStream_t st);
@@ -170,10 +192,10 @@ size_t packed_bytes(const Net& net);       // packed coordinates of all points (
 // eval.hip: evaluation by table rows, for the nets eval_rows_ok accepts.
 bool eval_rows_ok(const Net& net);
 void eval_rows_grid(int p, int s, int64_t N, int64_t nq, int* tqw, int* gy, int* bpc);
-void eval_rows_prefixes(const Net& net, float* tt);
+void eval_rows_prefixes(const Net& net, KernTab& kt);
 int launch_row_words(const Net& net, uint32_t* out, hipStream_t st);
 int launch_row_queries(const Net& net, const uint32_t* q, int64_t nq, void* out, hipStream_t st);
-int launch_eval_rows(const Net& net, const uint32_t* xw, const float* c, int64_t nq, const void* qv, const float* tt,
+int launch_eval_rows(const Net& net, const uint32_t* xw, const float* c, int64_t nq, const void* qv, const KernTab& kt,
                      df* partial, hipStream_t st);
 size_t eval_tables_bytes(const Net& net);  // staged per-lane factor tables of the evaluation
 size_t spline_eval_ws_bytes(const Net& net, int64_t nq, bool have_packed);
@@ -183,7 +205,7 @@ int eff_dim_chunk(const Net& net, size_t budget);
 size_t eff_dim_res_bytes(const Net& net);
 size_t eff_dim_ws_bytes(const Net& net, bool have_spectrum, int chunk);
 int eff_dim_enqueue(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* gk, const void* ft, int chunk,
-                    double* res_host, const double** res_dev, hipStream_t st);
+                    double* res_host, hipStream_t st);
 void eff_dim_finish(int s, const double* res, fdwt_effdim* out);
 int run_eff_dim(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* ft, fdwt_effdim* out, hipStream_t st);
 
@@ -202,10 +224,8 @@ int split_cost_call(const Net& n2, const float* f2, const double prm[3], float* 
 int kernel_tune_call(const Net& n2, const float* f2, const double start[3], int max_evals, fdwt_kernel_fit* out,
                      hipStream_t st);
 
-// Host tables of the kernel closed forms in double, for coordinates j and
-// first-differing-digit index i (0 = no differing digit).
+// K' in double for first-differing-digit index i (0 = no differing digit).
 double kprime(int p, double alpha, int i);
-double rprime(int p, double alpha, int i);
 int query_depth(int p);
 // Queries of q_depth digits lifted to the full depth (spline.hip).
 int lift_queries(const Net& net, const uint32_t* q, int64_t nq, int q_depth, uint32_t* out, hipStream_t st);

@@ -11,6 +11,7 @@
 // held in registers (p^k values per thread, one LDS round trip per group),
 // and writes the tile back in place.  The output is in natural order
 // (h = sum h_i p^i), as in Algorithm 1.
+#include "coords.h"
 #include "family.h"
 #include "p2_stages.h"
 #include "pass_core.h"
@@ -368,8 +369,8 @@ __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS))
 // generated in registers instead of read from memory (p = 2, Section 4):
 //  * truncation columns (KCOL false): U_d = prod_{j<=d} (1 + a_j) - 1,
 //    d = 1..s, with a_j = gamma_j^2 R'(x_{n,j}) = tab[j][t];
-//  * kernel column (KCOL true): K(x_n, 0) = prod_j tab[j][t] with
-//    tab[j][t] = 1 + gamma_j K'(x_{n,j}, 0).
+//  * kernel column (KCOL true): K(x_n, 0) = prod_j rl[j][t] with
+//    rl[j][t] = 1 + gamma_j K'(x_{n,j}, 0).
 // t is the index of the first non-zero digit of x_{n,j} (the leading-zero
 // count of X_j(n) in m bits; t = m for X = 0).  Each workgroup takes whole
 // tiles and runs j = 1..s in order; a thread keeps the running value for its
@@ -382,14 +383,13 @@ __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS))
 // but transforms and stores its own columns only.
 struct ColGen {
   const uint32_t* xtab;  // [s][nbytes][256]: X_j of byte value v at byte b
-  const double* tab;     // [s][ktab]
-  int nbytes, s, m, ktab;
+  int nbytes, s, m;
   int d0, d1;            // truncation columns U_{d0+1}..U_{d1} are stored (out column d - 1 - d0)
   int nch, per;          // ... by nch workgroups a tile, `per` columns each
 };
 
 template <int LOGE, bool KCOL>
-__global__ void __launch_bounds__((P2Shape<LOGE, 0>::THREADS)) fwt_p2_gen(ColGen g, double* out, PassDesc d) {
+__global__ void __launch_bounds__((P2Shape<LOGE, 0>::THREADS)) fwt_p2_gen(ColGen g, double* out, PassDesc d, KernTab kt) {
   using S = P2Shape<LOGE, 0>;
   constexpr int EPT = S::EPT, TH = S::THREADS, TB = LOGE - 4;  // tid has TB bits
   static_assert(LOGE >= 10 && EPT == 16, "16 elements per thread");
@@ -400,7 +400,7 @@ __global__ void __launch_bounds__((P2Shape<LOGE, 0>::THREADS)) fwt_p2_gen(ColGen
   double* rl = lds + ((cpad(S::E) + 1) & ~1);                    // [s][m + 1]
   uint32_t* cl = reinterpret_cast<uint32_t*>(rl + s * (m + 1));   // [s][m]: generator columns
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  for (int i = tid; i < s * (m + 1); i += TH) rl[i] = g.tab[(i / (m + 1)) * g.ktab + i % (m + 1)];
+  stage_kern_tables(kt, s, m + 1, KCOL ? rl : nullptr, KCOL ? nullptr : rl);
   for (int i = tid; i < s * m; i += TH) {
     const int j = i / m, c = i % m;
     cl[i] = g.xtab[((size_t)j * g.nbytes + (c >> 3)) * 256 + (1 << (c & 7))];
@@ -963,13 +963,13 @@ int fwt_run(int p, int m, bool inverse, Kind in_kind, const void* in, Kind work_
 // grouped-sum epilogue in its last pass (no output stored).  p = 2: `in` holds
 // the columns and tmp the intermediate passes.  p odd: `in` holds pairs of
 // columns as complex ones, column 2 i as the real part and column 2 i + 1
-// divided by unscale[i] as the imaginary part (both spectra are real: the
+// times 2^pexp[i] as the imaginary part (both spectra are real: the
 // kernel columns are even functions of the point index), and is overwritten;
 // tmp is not used.  partial receives [ncols][parts] partial sums, parts
 // (fwt_reduce_parts) returned in *parts.
-int fwt_reduce_f64(int p, int m, void* in, void* tmp, int ncols, const float2* wts, const double* unscale,
+int fwt_reduce_f64(int p, int m, void* in, void* tmp, int ncols, const float2* wts, const int32_t* pexp,
                    double* partial, double* h0_out, int h0_col, int64_t* parts, hipStream_t st) {
-  ReduceArgs red{wts, partial, h0_out, h0_col, unscale, ncols};
+  ReduceArgs red{wts, partial, h0_out, h0_col, pexp, ncols};
   if (p == 2) return run_passes(p, m, false, K_F64, in, K_F64, K_F64, tmp, tmp, ncols, 1.0, &red, parts, st);
   return run_passes(p, m, false, K_CF64, in, K_CF64, K_CF64, in, in, (ncols + 1) / 2, 1.0, &red, parts, st);
 }
@@ -1040,9 +1040,9 @@ int fwt_p2_f64_reduce_rest(int m, double* data, int batch, const float2* wts, do
 // truncation columns U_{d0+1}..U_{d1} from the R' table (kcol false: out
 // receives d1 - d0 columns), or the kernel column K from the K' table (kcol
 // true: one column; d0, d1 unused).
-int fwt_p2_gen_first(int m, int s, const uint32_t* xtab, int nbytes, const double* tab, int ktab, bool kcol,
+int fwt_p2_gen_first(int m, int s, const uint32_t* xtab, int nbytes, const KernTab& kt, bool kcol,
                      int d0, int d1, double* out, bool blocked, hipStream_t st) {
-  if (!fwt_p2_split_ok(m) || s < 1 || s > 64 || ktab <= m) return fail(FDWT_EINVAL, "bad generated-column pass");
+  if (!fwt_p2_split_ok(m) || s < 1 || s > 64 || kTab <= m) return fail(FDWT_EINVAL, "bad generated-column pass");
   if (!kcol && (d0 < 0 || d1 > s || d0 >= d1)) return fail(FDWT_EINVAL, "bad generated-column range");
   const P2Pass g = plan_p2_cols(m)[0];
   const void* fn = nullptr;
@@ -1073,8 +1073,8 @@ int fwt_p2_gen_first(int m, int s, const uint32_t* xtab, int nbytes, const doubl
   const int per = (ncol + nch0 - 1) / nch0, nch = (ncol + per - 1) / per;
   if (G >= (int64_t)d.ntiles * nch) G = (int64_t)d.ntiles * nch;
   d.xcd = G >= 64 ? 1 : 0;
-  ColGen cg{xtab, tab, nbytes, s, m, ktab, kcol ? 0 : d0, kcol ? s : d1, nch, per};
-  void* args[] = {(void*)&cg, (void*)&out, (void*)&d};
+  ColGen cg{xtab, nbytes, s, m, kcol ? 0 : d0, kcol ? s : d1, nch, per};
+  void* args[] = {(void*)&cg, (void*)&out, (void*)&d, (void*)&kt};
   return launch_timed(fn, dim3((unsigned)G), dim3(threads), args, lds, st, FDWT_TC_PASS_F64,
                       (double)N * ncol * sizeof(double));
 }

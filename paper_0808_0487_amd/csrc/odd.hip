@@ -146,7 +146,7 @@ __global__ void __launch_bounds__((OddShape<P, LE, RD, KT>::TH))
       for (int k = 0; k < EPT; ++k) dst[k * gstep] = cvt_out<T, Tout>(v[k], d.scale, d.scale64);
       if constexpr (RD > KT) lds_barrier();
     } else {
-      const double us = d.unscale[col];
+      const double us = ldexp(1.0, -d.pexp[col]);
       double2 acc = make_double2(0.0, 0.0);
 #pragma unroll
       for (int k = 0; k < EPT; ++k) {
@@ -269,8 +269,8 @@ static int launch_odd(const void* in, void* out, const PassGeom& g, int m, int b
     d.partial = red->partial;
     d.h0_out = red->h0_out;
     d.h0_col = red->h0_col;
-    d.unscale = red->unscale;
     d.ncols = red->ncols;
+    for (int i = 0; i < batch; ++i) d.pexp[i] = (int16_t)red->pexp[i];
   }
   const size_t lds = std::max<size_t>(RD > KT ? (size_t)S::E * sizeof(T) : 0, EPI == EPI_REDUCE ? S::TH * sizeof(double2) : 0);
   if (int rc = allow_lds(fn, lds)) return rc;

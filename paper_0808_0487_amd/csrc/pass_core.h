@@ -49,9 +49,9 @@ struct PassDesc {
   void* const* out_tab;
 
   // Grouped sums of paired columns (odd p): the imaginary part of column c is
-  // multiplied by unscale[c]; ncols real columns in all.
-  const double* unscale;
+  // multiplied by 2^-pexp[c]; ncols real columns in all.
   int32_t ncols;
+  int16_t pexp[kMaxS];
 };
 
 // One pass of a plan: digits [d0, d0 + r), rows of p^wdig elements; le: the
@@ -66,7 +66,7 @@ struct ReduceArgs {
   double* partial;  // [ncols][fwt_reduce_parts]
   double* h0_out;
   int h0_col;
-  const double* unscale;  // p odd: per pair of columns
+  const int32_t* pexp;  // p odd: per pair of columns (host)
   int ncols;
 };
 

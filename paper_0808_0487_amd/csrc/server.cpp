@@ -75,7 +75,6 @@ Sizes request_sizes(const Request& r, size_t chunk_bytes) {
   z.f = (size_t)n.N * 4;
   z.ft = (size_t)n.N * (r.p == 2 ? 4 : 8);
   size_t ws = spectrum_ws_bytes(n);
-  const size_t tab_pin = align_ws(kernel_tables_bytes(n));
   if (r.kind == FDWT_JOB_INTERP) {
     z.packed = packed_bytes(n);
     z.c = (size_t)n.N * 4;
@@ -83,11 +82,11 @@ Sizes request_sizes(const Request& r, size_t chunk_bytes) {
     z.sf = (size_t)r.nq * 4;
     ws = std::max(ws, spline_coef_ws_bytes(n, true));
     ws = std::max(ws, spline_eval_ws_bytes(n, r.nq, true));
-    z.pin = tab_pin + align_ws(eval_tables_bytes(n)) + align_ws(z.qd) + align_ws(z.sf);
+    z.pin = align_ws(eval_tables_bytes(n)) + align_ws(z.qd) + align_ws(z.sf);
   } else {
     z.chunk = eff_dim_chunk(n, chunk_bytes);
     ws = std::max(ws, eff_dim_ws_bytes(n, true, z.chunk));
-    z.pin = 2 * tab_pin + align_ws(eff_dim_res_bytes(n));
+    z.pin = align_ws(eff_dim_res_bytes(n));
   }
   z.ws = ws;
   z.job = align_ws(z.f) + align_ws(z.ft) + align_ws(z.c) + align_ws(z.qd) + align_ws(z.sf) + align_ws(z.ws);
@@ -448,7 +447,7 @@ int fdwt_server::enqueue(Job& j, Lane& L) {
     FDWT_HIP(hipMemcpyAsync(j.pin_out, sf, (size_t)r.nq * 4, hipMemcpyDeviceToHost, st));
   } else {
     if ((rc = pin_take(sc, eff_dim_res_bytes(net), &j.pin_out))) return rc;
-    if ((rc = eff_dim_enqueue(net, sc, &kern, gk, ft, j.z.chunk, (double*)j.pin_out, nullptr, st))) return rc;
+    if ((rc = eff_dim_enqueue(net, sc, &kern, gk, ft, j.z.chunk, (double*)j.pin_out, st))) return rc;
   }
   return FDWT_OK;
 }

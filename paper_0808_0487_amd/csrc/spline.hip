@@ -32,8 +32,6 @@
 
 namespace fdwt {
 
-constexpr int kTab = 33;  // entries per coordinate of the digit-indexed tables
-
 __host__ __device__ static inline size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct NetArgs {
@@ -49,22 +47,17 @@ struct NetArgs {
 // polynomials e_0..e_SMAX live in registers (updates unrolled, truncated per
 // chunk of coordinates where the higher ones are still zero).  p odd: the
 // columns from U_1 on are written as pairs, columns c0 + 2 i and c0 + 2 i + 1
-// as the parts of complex column i, the second times pscale[(column - 1) / 2]
+// as the parts of complex column i, the second times 2^kt.ix[(column - 1) / 2]
 // (zero when there is none); c0 is odd.
 template <int P, int SMAX>
-__global__ void __launch_bounds__(kChunk) k_kernel_cols(NetArgs na, const double* __restrict__ tk,
-                                                        const double* __restrict__ tr, int c0, int c1,
-                                                        double* __restrict__ out,
-                                                        const double* __restrict__ pscale) {
+__global__ void __launch_bounds__(kChunk) k_kernel_cols(NetArgs na, KernTab kt, int c0, int c1,
+                                                        double* __restrict__ out) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int s = na.s;
   double* ltk = reinterpret_cast<double*>(smem);       // [s][kTab]
   double* ltr = ltk + s * kTab;                         // [s][kTab]
   uint32_t* lt0 = reinterpret_cast<uint32_t*>(ltr + s * kTab);
-  for (int i = threadIdx.x; i < s * kTab; i += blockDim.x) {
-    ltk[i] = tk[i];
-    ltr[i] = tr[i];
-  }
+  stage_kern_tables(kt, s, kTab, ltk, ltr);
   P2Coords pc{na.xtab, na.nbytes, s, lt0, lt0 + s * 256};
   uint64_t* lodd = reinterpret_cast<uint64_t*>(ltr + s * kTab);
   OddCoords<P == 2 ? 3 : P> oc{na.ptab, s, na.m, lodd, lodd + s * OddCoords<P == 2 ? 3 : P>::PK};
@@ -90,7 +83,7 @@ __global__ void __launch_bounds__(kChunk) k_kernel_cols(NetArgs na, const double
       } else {
         const int i = c - c0;
         if (i & 1) {
-          v *= pscale[(c - 1) >> 1];
+          v = ldexp(v, kt.ix[(c - 1) >> 1]);
         } else {
           held = v;
           v = 0.0;
@@ -144,8 +137,7 @@ __global__ void __launch_bounds__(kChunk) k_kernel_cols(NetArgs na, const double
 // A 512-point group is two 256-point halves, each with its own XOR of the
 // upper-byte tables.
 template <int SMAX>
-__global__ void __launch_bounds__(kChunk) k_kernel_cols2(NetArgs na, const double* __restrict__ tk,
-                                                         const double* __restrict__ tr, int c0, int c1,
+__global__ void __launch_bounds__(kChunk) k_kernel_cols2(NetArgs na, KernTab kt, int c0, int c1,
                                                          double* __restrict__ out) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int s = na.s;
@@ -153,10 +145,7 @@ __global__ void __launch_bounds__(kChunk) k_kernel_cols2(NetArgs na, const doubl
   double* ltr = ltk + s * kTab;
   uint32_t* lt0 = reinterpret_cast<uint32_t*>(ltr + s * kTab);  // [s][256]
   uint32_t* lu = lt0 + s * 256;                                  // [2][s]
-  for (int i = threadIdx.x; i < s * kTab; i += blockDim.x) {
-    ltk[i] = tk[i];
-    ltr[i] = tr[i];
-  }
+  stage_kern_tables(kt, s, kTab, ltk, ltr);
   P2Coords pc{na.xtab, na.nbytes, s, lt0, lu};
   pc.stage_tables();
   const bool need_r = c1 > 1;
@@ -294,20 +283,43 @@ __global__ void __launch_bounds__(256) k_effdim_weights(const void* __restrict__
   if (threadIdx.x == 0) qmc_partial[blockIdx.x] = red[0];
 }
 
-// Sum nblk partials per row in a fixed order: out[row] = sum_b in[row*nblk + b].
+// Sum of n partials by a workgroup in a fixed order (the result in thread 0).
 constexpr int kSumThreads = 1024;
-__global__ void __launch_bounds__(kSumThreads) k_sum_rows(const double* __restrict__ in, int nblk,
-                                                          double* __restrict__ out) {
-  __shared__ double red[kSumThreads];
+__device__ __forceinline__ double sum_row(const double* __restrict__ in, int n, double* red) {
   double a = 0.0;
-  for (int b = threadIdx.x; b < nblk; b += kSumThreads) a += in[(int64_t)blockIdx.x * nblk + b];
+  for (int b = threadIdx.x; b < n; b += kSumThreads) a += in[b];
   red[threadIdx.x] = a;
   __syncthreads();
   for (int off = kSumThreads / 2; off > 0; off >>= 1) {
     if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+  return red[0];
+}
+
+// One row: the split cost.
+__global__ void __launch_bounds__(kSumThreads) k_sum_rows(const double* __restrict__ in, int nblk,
+                                                          double* __restrict__ out) {
+  __shared__ double red[kSumThreads];
+  const double a = sum_row(in + (int64_t)blockIdx.x * nblk, nblk, red);
+  if (threadIdx.x == 0) out[blockIdx.x] = a;
+}
+
+// The results of eff_dim straight into pinned host memory: workgroup c < ncols
+// sums column c's partials into out[c], the last one the sample variance into
+// out[at], and copies the h = 0 share to out[at + 1].
+__global__ void __launch_bounds__(kSumThreads) k_effdim_sums(const double* __restrict__ partial, int parts, int ncols,
+                                                             const double* __restrict__ qmc, int nqmc,
+                                                             const double* __restrict__ h0, double* __restrict__ out,
+                                                             int at) {
+  __shared__ double red[kSumThreads];
+  const int c = blockIdx.x;
+  const bool col = c < ncols;
+  const double a = sum_row(col ? partial + (int64_t)c * parts : qmc, col ? parts : nqmc, red);
+  if (threadIdx.x == 0) {
+    out[col ? c : at] = a;
+    if (!col) out[at + 1] = *h0;
+  }
 }
 
 // --------------------------------------------------------- evaluation
@@ -496,18 +508,16 @@ __global__ void __launch_bounds__(256) k_eval_finish(const df* __restrict__ part
 // Section 5.1, p = 2.  g(u) = K(x_u (+) x_N, 0) over the first half (an
 // m-digit net, tables of `na`): coordinate j of x_u (+) x_N as an
 // (m+1)-digit integer is (X_j(u) << 1) ^ delta_j; the factor comes from its
-// first non-zero digit, tk2[j][t] = 1 + gamma_j K'(t+1) (t < m+1) and
-// tk2[j][m+1] = 1 + gamma_j (all digits zero).
-__global__ void __launch_bounds__(kChunk) k_kernel_shift_p2(NetArgs na, const uint32_t* __restrict__ delta,
-                                                            const double* __restrict__ tk2, int m2,
+// first non-zero digit t < m2 = m + 1, or none; delta_j = kt.ix[j].
+__global__ void __launch_bounds__(kChunk) k_kernel_shift_p2(NetArgs na, KernTab kt, int m2,
                                                             double* __restrict__ out) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int s = na.s;
   double* ltk = reinterpret_cast<double*>(smem);                       // [s][kTab]
   uint32_t* ld = reinterpret_cast<uint32_t*>(ltk + s * kTab);           // [s]
   uint32_t* lt0 = ld + ((s + 1) & ~1);
-  for (int i = threadIdx.x; i < s * kTab; i += blockDim.x) ltk[i] = tk2[i];
-  for (int i = threadIdx.x; i < s; i += blockDim.x) ld[i] = delta[i];
+  stage_kern_tables(kt, s, kTab, ltk, nullptr);
+  for (int i = threadIdx.x; i < s; i += blockDim.x) ld[i] = (uint32_t)kt.ix[i];
   P2Coords pc{na.xtab, na.nbytes, s, lt0, lt0 + s * 256};
   pc.stage_tables();
   const int64_t N = na.N;
@@ -562,54 +572,56 @@ static NetArgs net_args(const Net& net) {
   return NetArgs{net.d_xtab, net.d_ptab, net.nbytes, net.s, net.m, net.N};
 }
 
-// Kernel-data tables: tk[j][t] = 1 + gamma_j K'(t+1) for t < m, 1 + gamma_j for
-// t >= m (x = 0); tr[j][t] = gamma_j^2 R'(t+1), gamma_j^2 R'(0).  Laid out as
-// tk then tr, each [s][kTab], then (p odd) the pair scales [s] and their
-// inverses [s]: the variance columns U_1..U_s, Q_1..Q_{s-1} are transformed
-// two to a complex column, and a power of two brings the second of a pair to
-// the first one's magnitude (both at x = 0, their maximum), so that neither
-// loses digits to the other's rounding.
-static std::vector<double> kernel_tables(const Net& net, const fdwt_kernel* k) {
-  std::vector<double> t(kernel_tables_bytes(net) / sizeof(double), 0.0);
-  for (int j = 0; j < net.s; ++j) {
-    const double g = k->gamma[j];
-    for (int i = 0; i < kTab; ++i) {
-      const int dig = i < net.m ? i + 1 : 0;
-      t[(size_t)j * kTab + i] = 1.0 + g * kprime(net.p, k->alpha, dig);
-      t[(size_t)(net.s + j) * kTab + i] = g * g * rprime(net.p, k->alpha, dig);
-    }
+KernTab kern_tab(int p, int digits, const fdwt_kernel* k) {
+  KernTab t{};
+  // Section 4's closed forms at digit index t + 1 (K'(0) = 1, R'(0) = A for
+  // no digit), with their common powers taken once.  A table per coordinate,
+  // every entry from scratch, took the host 40 us and more per call.
+  const double al = k->alpha, pa = std::pow((double)p, al), p2a = std::pow((double)p, 2.0 * al);
+  const double A = (pa - p) * (pa - p) / ((p - 1.0) * (p2a - p));
+  for (int i = 0; i < kTab; ++i) {
+    const int dig = i + 1;
+    t.kp[i] = i < digits ? 1.0 - std::pow((double)p, dig * (1.0 - al)) * (pa - 1.0) / (p - 1.0) : 1.0;
+    t.rp[i] = i < digits ? A * (1.0 - std::pow((double)p, dig * (1.0 - 2.0 * al)) * (p2a - 1.0) / (p - 1.0)) : A;
   }
-  if (net.p != 2) {
-    const int s = net.s;
-    std::vector<double> col(2 * s, 0.0), e(s + 1, 0.0);  // U_d, Q_j at x = 0
-    e[0] = 1.0;
-    double u = 0.0;
-    for (int j = 0; j < s; ++j) {
-      const double r = t[(size_t)(s + j) * kTab + net.m];
-      u = u + r + u * r;
-      col[j] = u;
-      for (int i = j + 1; i >= 1; --i) e[i] += r * e[i - 1];
-    }
-    for (int j = 1; j <= s; ++j) col[s + j - 1] = e[j];
-    double* sc = t.data() + (size_t)2 * s * kTab;
-    for (int i = 0; i < s; ++i) {
-      int ea = 0, eb = 0;
-      const double a = col[2 * i], b = col[2 * i + 1];
-      const bool ok = a > 0.0 && b > 0.0 && std::isfinite(a) && std::isfinite(b);
-      if (ok) {
-        (void)std::frexp(a, &ea);
-        (void)std::frexp(b, &eb);
-      }
-      const int sh = std::max(-1000, std::min(1000, ea - eb));
-      sc[i] = std::ldexp(1.0, sh);
-      sc[s + i] = std::ldexp(1.0, -sh);
-    }
-  }
+  for (int j = 0; j < k->s; ++j) t.gamma[j] = k->gamma[j];
   return t;
 }
 
-size_t kernel_tables_bytes(const Net& net) {
-  return ((size_t)2 * net.s * kTab + (net.p == 2 ? 0 : 2 * net.s)) * sizeof(double);
+// Pair exponents (p odd): the variance columns U_1..U_s, Q_1..Q_{s-1} are
+// transformed two to a complex column, and a power of two brings the second of
+// a pair to the first one's magnitude (both at x = 0, their maximum), so that
+// neither loses digits to the other's rounding.
+static void pair_exponents(int s, int m, KernTab& t) {
+  std::vector<double> col(2 * s, 0.0), e(s + 1, 0.0);  // U_d, Q_j at x = 0
+  e[0] = 1.0;
+  double u = 0.0;
+  for (int j = 0; j < s; ++j) {
+    const double r = t.gamma[j] * t.gamma[j] * t.rp[m];
+    u = u + r + u * r;
+    col[j] = u;
+    for (int i = j + 1; i >= 1; --i) e[i] += r * e[i - 1];
+  }
+  for (int j = 1; j <= s; ++j) col[s + j - 1] = e[j];
+  for (int i = 0; i < s; ++i) {
+    int ea = 0, eb = 0;
+    const double a = col[2 * i], b = col[2 * i + 1];
+    if (a > 0.0 && b > 0.0 && std::isfinite(a) && std::isfinite(b)) {
+      (void)std::frexp(a, &ea);
+      (void)std::frexp(b, &eb);
+    }
+    t.ix[i] = std::max(-1000, std::min(1000, ea - eb));
+  }
+}
+
+int ensure_res_host(Net& net) {
+  if (net.res_host) return FDWT_OK;
+  if (hipHostMalloc((void**)&net.res_host, (2 * kMaxS + 2) * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    net.res_host = nullptr;
+    return fail(FDWT_ENOMEM, "pinned result allocation failed");
+  }
+  return FDWT_OK;
 }
 
 // Consecutive slices of a workspace; with base == nullptr it only measures.
@@ -625,14 +637,13 @@ struct Carve {
 };
 
 template <int P, int SMAX>
-static int kcols_launch(const Net& net, const double* tk, const double* tr, int c0, int c1, double* out,
+static int kcols_launch(const Net& net, const KernTab& kt, int c0, int c1, double* out,
                         hipStream_t st) {
   const size_t lds = (size_t)2 * net.s * kTab * 8 +
                      (P == 2 ? (size_t)net.s * 257 * 4 : OddCoords<P == 2 ? 3 : P>::lds_bytes(net.s));
   if (int rc = allow_lds((const void*)k_kernel_cols<P, SMAX>, lds)) return rc;
   NetArgs na = net_args(net);
-  const double* pscale = tk + (size_t)2 * net.s * kTab;  // p odd: after the two tables
-  void* args[] = {(void*)&na, (void*)&tk, (void*)&tr, (void*)&c0, (void*)&c1, (void*)&out, (void*)&pscale};
+  void* args[] = {(void*)&na, (void*)&kt, (void*)&c0, (void*)&c1, (void*)&out};
   if constexpr (P == 2) {
     if (net.N % 512 == 0) {
       const size_t lds2 = (size_t)2 * net.s * kTab * 8 + (size_t)net.s * 258 * 4;
@@ -650,28 +661,28 @@ static int kcols_launch(const Net& net, const double* tk, const double* tr, int 
 // SMAX: register length of the symmetric-polynomial state (>= s; 8 when only
 // K and the U_d columns are wanted).
 template <int P>
-static int kcols_p(const Net& net, const double* tk, const double* tr, int c0, int c1, double* out,
+static int kcols_p(const Net& net, const KernTab& kt, int c0, int c1, double* out,
                    hipStream_t st) {
   const int s = net.s;
-  if (c1 <= s + 1 || s <= 8) return kcols_launch<P, 8>(net, tk, tr, c0, c1, out, st);
-  if (s <= 16) return kcols_launch<P, 16>(net, tk, tr, c0, c1, out, st);
-  if (s <= 24) return kcols_launch<P, 24>(net, tk, tr, c0, c1, out, st);
-  if (s <= 32) return kcols_launch<P, 32>(net, tk, tr, c0, c1, out, st);
-  if (s <= 48) return kcols_launch<P, 48>(net, tk, tr, c0, c1, out, st);
-  return kcols_launch<P, 64>(net, tk, tr, c0, c1, out, st);
+  if (c1 <= s + 1 || s <= 8) return kcols_launch<P, 8>(net, kt, c0, c1, out, st);
+  if (s <= 16) return kcols_launch<P, 16>(net, kt, c0, c1, out, st);
+  if (s <= 24) return kcols_launch<P, 24>(net, kt, c0, c1, out, st);
+  if (s <= 32) return kcols_launch<P, 32>(net, kt, c0, c1, out, st);
+  if (s <= 48) return kcols_launch<P, 48>(net, kt, c0, c1, out, st);
+  return kcols_launch<P, 64>(net, kt, c0, c1, out, st);
 }
 
-static int launch_kernel_cols(const Net& net, const double* tk, const double* tr, int c0, int c1, double* out,
+static int launch_kernel_cols(const Net& net, const KernTab& kt, int c0, int c1, double* out,
                               hipStream_t st) {
-  if (net.p == 2) return kcols_p<2>(net, tk, tr, c0, c1, out, st);
-  if (net.p == 3) return kcols_p<3>(net, tk, tr, c0, c1, out, st);
-  if (net.p == 5) return kcols_p<5>(net, tk, tr, c0, c1, out, st);
-  return kcols_p<7>(net, tk, tr, c0, c1, out, st);
+  if (net.p == 2) return kcols_p<2>(net, kt, c0, c1, out, st);
+  if (net.p == 3) return kcols_p<3>(net, kt, c0, c1, out, st);
+  if (net.p == 5) return kcols_p<5>(net, kt, c0, c1, out, st);
+  return kcols_p<7>(net, kt, c0, c1, out, st);
 }
 
 static unsigned grid1(int64_t n) { return (unsigned)std::min<int64_t>((n + 255) / 256, 4096); }
 
-int fwt_reduce_f64(int p, int m, void* in, void* tmp, int ncols, const float2* wts, const double* unscale,
+int fwt_reduce_f64(int p, int m, void* in, void* tmp, int ncols, const float2* wts, const int32_t* pexp,
                    double* partial, double* h0_out, int h0_col, int64_t* parts, hipStream_t st);
 int64_t fwt_reduce_parts(int p, int m, size_t elem_bytes);
 bool fwt_p2_split_ok(int m);
@@ -680,7 +691,7 @@ int fwt_p2_first_loge(int m);
 int fwt_p2_f64_first(int m, const double* in, double* out, int batch, bool blocked, hipStream_t st);
 int fwt_p2_f64_reduce_rest(int m, double* data, int batch, const float2* wts, double* partial, double* h0_out,
                            int h0_col, bool blocked, hipStream_t st);
-int fwt_p2_gen_first(int m, int s, const uint32_t* xtab, int nbytes, const double* tab, int ktab, bool kcol,
+int fwt_p2_gen_first(int m, int s, const uint32_t* xtab, int nbytes, const KernTab& kt, bool kcol,
                      int d0, int d1, double* out, bool blocked, hipStream_t st);
 int fwt_p2_f64_rest(int m, double* data, int batch, hipStream_t st);
 
@@ -689,46 +700,22 @@ int fwt_p2_f64_rest(int m, double* data, int batch, hipStream_t st);
 // doubles; p odd, N complex doubles.
 size_t spectrum_bytes(const Net& net) { return (size_t)net.N * (net.p == 2 ? 8 : 16); }
 
-struct SpecWs {
-  double* tab;  // kernel tables
-  double* A;    // kernel data (p odd; p = 2 transforms in place in the spectrum)
-};
-static void spec_layout(const Net& net, Carve& cv, SpecWs& w) {
-  w.tab = (double*)cv.take(kernel_tables_bytes(net));
-  w.A = net.p == 2 ? nullptr : (double*)cv.take((size_t)net.N * 8);
-}
-size_t spectrum_ws_bytes(const Net& net) {
-  Carve cv(nullptr);
-  SpecWs w;
-  spec_layout(net, cv, w);
-  return cv.off;
-}
+// Workspace of the spectrum: p odd, the kernel data (p = 2 transforms in
+// place in the spectrum).
+size_t spectrum_ws_bytes(const Net& net) { return net.p == 2 ? 0 : align_up((size_t)net.N * 8); }
 
-// Computes the spectrum into gk (spectrum_bytes); the tables and, for p odd,
-// the data go through the first spectrum_ws_bytes of ws.  tab_dev: tables
-// already on the device (then they are not staged again), or nullptr.
-static int spectrum_into(Net& net, Scratch& sc, const fdwt_kernel* kern, void* ws, void* gk, hipStream_t st,
-                         const double* tab_dev = nullptr) {
-  Carve cv(ws);
-  SpecWs w;
-  spec_layout(net, cv, w);
+// Computes the spectrum into gk (spectrum_bytes); p odd: the kernel data go
+// through the first spectrum_ws_bytes of ws.
+static int spectrum_into(Net& net, const KernTab& kt, void* ws, void* gk, hipStream_t st) {
   int rc = FDWT_OK;
-  const double* tab = tab_dev;
-  if (!tab) {
-    const std::vector<double> htab = kernel_tables(net, kern);
-    rc = upload(sc, htab.data(), htab.size() * sizeof(double), w.tab, st);
-    if (rc) return rc;
-    tab = w.tab;
-  }
   if (net.p == 2 && fwt_p2_split_ok(net.m)) {
     // K generated inside the first pass of its transform (no column in memory).
-    if ((rc = fwt_p2_gen_first(net.m, net.s, net.d_xtab, net.nbytes, tab, kTab, true, 0, 0, (double*)gk, false,
-                               st)))
+    if ((rc = fwt_p2_gen_first(net.m, net.s, net.d_xtab, net.nbytes, kt, true, 0, 0, (double*)gk, false, st)))
       return rc;
     return fwt_p2_f64_rest(net.m, (double*)gk, 1, st);
   }
-  double* A = net.p == 2 ? (double*)gk : w.A;
-  rc = launch_kernel_cols(net, tab, tab + (size_t)net.s * kTab, 0, 1, A, st);
+  double* A = net.p == 2 ? (double*)gk : (double*)ws;
+  rc = launch_kernel_cols(net, kt, 0, 1, A, st);
   if (rc) return rc;
   if (net.p == 2) return fwt_run_tmp(2, net.m, false, K_F64, A, K_F64, K_F64, A, nullptr, 1, 1.0, st);
   return fwt_run_tmp(net.p, net.m, false, K_F64, A, K_CF64, K_CF64, gk, nullptr, 1, 1.0, st);
@@ -737,7 +724,7 @@ static int spectrum_into(Net& net, Scratch& sc, const fdwt_kernel* kern, void* w
 int run_spectrum(Net& net, Scratch& sc, const fdwt_kernel* kern, void* gk, hipStream_t st) {
   int rc = ensure_ws(sc, spectrum_ws_bytes(net), st);
   if (rc) return rc;
-  return spectrum_into(net, sc, kern, sc.ws, gk, st);
+  return spectrum_into(net, kern_tab(net.p, net.m, kern), sc.ws, gk, st);
 }
 
 int cached_spectrum(Net& net, const fdwt_kernel* kern, const void** gk, hipStream_t st) {
@@ -775,11 +762,11 @@ int cached_spectrum(Net& net, const fdwt_kernel* kern, const void** gk, hipStrea
 void drop_spectrum(Net& net) { net.spec_key.clear(); }
 
 void release_spectrum(Net& net) {
-  if (net.spec) {
-    (void)hipDeviceSynchronize();
-    (void)hipFree(net.spec);
-  }
+  if (net.spec || net.res_host) (void)hipDeviceSynchronize();
+  if (net.spec) (void)hipFree(net.spec);
   if (net.spec_ready) (void)hipEventDestroy(net.spec_ready);
+  if (net.res_host) (void)hipHostFree(net.res_host);
+  net.res_host = nullptr;
   net.spec = nullptr;
   net.spec_bytes = 0;
   net.spec_ready = nullptr;
@@ -814,7 +801,7 @@ int run_spline_coef(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
   coef_layout(net, gk_given != nullptr, cv, w);
   const void* GK = gk_given;
   if (!GK) {
-    rc = spectrum_into(net, sc, kern, w.sw, w.gk, st);
+    rc = spectrum_into(net, kern_tab(net.p, net.m, kern), w.sw, w.gk, st);
     if (rc) return rc;
     GK = w.gk;
   }
@@ -910,29 +897,31 @@ int run_spline_eval(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
   Carve cv(sc.ws);
   EvalWs w;
   eval_layout(net, nq, packed != nullptr, cv, w);
-  // Factor 1 + gamma_j K'(t+1) of first differing digit t < D, and 1 + gamma_j
-  // when all D digits agree, at entry c + 1 of the leading-zero count c that
-  // k_spline_eval computes (p = 2: c = t, or -1 when equal; p odd: c = Bt+1..Bt+B,
-  // or 64 when equal).  For p odd, entry 0 (high words equal, c = -1) is a
-  // NaN: it marks the points whose low words must be read.  Rows (eval.hip):
-  // entry t, and entry D when all digits agree.
-  const int B = p == 3 ? kStrBits<3> : kStrBits<5>;  // digit-string field width (coords.h)
-  std::vector<float> htl((size_t)s * kTabE, 1.0f);
-  for (int j = 0; j < s; ++j) {
-    float* row = htl.data() + (size_t)j * kTabE;
-    const float eq = (float)(1.0 + kern->gamma[j] * kprime(p, kern->alpha, 0));
-    for (int t = 0; t < D; ++t) {
-      const float v = (float)(1.0 + kern->gamma[j] * kprime(p, kern->alpha, t + 1));
-      if (rows) row[t] = v;
-      else if (p == 2) row[t + 1] = v;
-      else for (int l = B * t + 1; l <= B * t + B; ++l) row[l + 1] = v;
+  // Rows (eval.hip) make their tables from K' by value.  k_spline_eval reads
+  // the factor 1 + gamma_j K'(t+1) of first differing digit t < D, and
+  // 1 + gamma_j when all D digits agree, at entry c + 1 of the leading-zero
+  // count c that it computes (p = 2: c = t, or -1 when equal; p odd:
+  // c = Bt+1..Bt+B, or 64 when equal).  For p odd, entry 0 (high words equal,
+  // c = -1) is a NaN: it marks the points whose low words must be read.
+  KernTab kt = kern_tab(p, D, kern);
+  if (rows) {
+    eval_rows_prefixes(net, kt);
+  } else {
+    const int B = p == 3 ? kStrBits<3> : kStrBits<5>;  // digit-string field width (coords.h)
+    std::vector<float> htl((size_t)s * kTabE, 1.0f);
+    for (int j = 0; j < s; ++j) {
+      float* row = htl.data() + (size_t)j * kTabE;
+      for (int t = 0; t < D; ++t) {
+        const float v = (float)(1.0 + kern->gamma[j] * kt.kp[t]);
+        if (p == 2) row[t + 1] = v;
+        else for (int l = B * t + 1; l <= B * t + B; ++l) row[l + 1] = v;
+      }
+      row[p == 2 ? 0 : 65] = (float)(1.0 + kern->gamma[j] * kprime(p, kern->alpha, 0));
+      if (p != 2) row[0] = std::numeric_limits<float>::quiet_NaN();
     }
-    row[rows ? D : (p == 2 ? 0 : 65)] = eq;
-    if (p != 2 && !rows) row[0] = std::numeric_limits<float>::quiet_NaN();
+    rc = upload(sc, htl.data(), htl.size() * 4, w.tl, st);
+    if (rc) return rc;
   }
-  if (rows) eval_rows_prefixes(net, htl.data());
-  rc = upload(sc, htl.data(), htl.size() * 4, w.tl, st);
-  if (rc) return rc;
   const void* Xp = packed;
   if (!Xp) {
     rc = launch_net_packed(net, w.Xp, st);
@@ -951,7 +940,7 @@ int run_spline_eval(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
     qv = w.qs;
   }
   hipEvent_t tb = timed_begin(st);
-  if (rows) rc = launch_eval_rows(net, (const uint32_t*)Xp, c, nq, qv, w.tl, w.partial, st);
+  if (rows) rc = launch_eval_rows(net, (const uint32_t*)Xp, c, nq, qv, kt, w.partial, st);
   else if (p == 2) rc = launch_eval<2>(net, Xp, c, nq, qv, w.tl, w.partial, gy, ppc, st);
   else rc = launch_eval<3>(net, Xp, c, nq, qv, w.tl, w.partial, gy, ppc, st);  // any odd p: digit strings
   if (rc) return rc;
@@ -985,7 +974,6 @@ static bool effdim_blocked() {  // read at each call
 struct EffWs {
   void* gk;
   void* sw;
-  double* tab;
   float2* wts;
   double* A;
   void* B;
@@ -1004,7 +992,6 @@ static void eff_layout(const Net& net, bool have_gk, int ch, Carve& cv, EffWs& w
   const int64_t parts = fwt_reduce_parts(net.p, net.m, wb);
   w.gk = have_gk ? nullptr : cv.take(spectrum_bytes(net));
   w.sw = have_gk ? nullptr : cv.take(spectrum_ws_bytes(net));
-  w.tab = (double*)cv.take(kernel_tables_bytes(net));
   w.wts = (float2*)cv.take((size_t)net.N * sizeof(float2));
   w.A = (double*)cv.take((size_t)ch * net.N * 8);
   w.B = net.p == 2 ? cv.take((size_t)ch * net.N * 8) : nullptr;
@@ -1021,12 +1008,11 @@ size_t eff_dim_ws_bytes(const Net& net, bool have_spectrum, int chunk) {
 
 // Enqueues the whole variance computation on st; the 2s + 2 result doubles
 // (sigma^2_trc(d) for d = 1..s, the superposition increments for j = 1..s-1,
-// an unused slot, sigma^2_QMC and the h = 0 share) land in res_host (pinned)
-// when st reaches this point (when res_host is given; *res_dev receives their
-// device copy).
+// an unused slot, sigma^2_QMC and the h = 0 share) are in res_host (pinned
+// memory, written by the last kernel) when st reaches this point.
 // gk_given: a cached spectrum, or nullptr to compute it here.
 int eff_dim_enqueue(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* gk_given, const void* ft, int ch,
-                    double* res_host, const double** res_dev, hipStream_t st) {
+                    double* res_host, hipStream_t st) {
   const int p = net.p, s = net.s;
   const int64_t N = net.N;
   const size_t wb = (p == 2) ? sizeof(double) : sizeof(double2);
@@ -1037,15 +1023,14 @@ int eff_dim_enqueue(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
   Carve cv(sc.ws);
   EffWs w;
   eff_layout(net, gk_given != nullptr, ch, cv, w);
-  const std::vector<double> htab = kernel_tables(net, kern);
-  rc = upload(sc, htab.data(), htab.size() * sizeof(double), w.tab, st);
-  if (rc) return rc;
+  KernTab kt = kern_tab(p, net.m, kern);
   const void* GK = gk_given;
   if (!GK) {
-    rc = spectrum_into(net, sc, kern, w.sw, w.gk, st, w.tab);
+    rc = spectrum_into(net, kt, w.sw, w.gk, st);
     if (rc) return rc;
     GK = w.gk;
   }
+  if (p != 2) pair_exponents(s, net.m, kt);
   double* h0 = w.res + 2 * s + 1;  // h = 0 share of the total
   const double pm = (double)N;
   // p = 2 two-pass plans keep the intermediate columns in the blocked layout
@@ -1056,7 +1041,6 @@ int eff_dim_enqueue(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
   else hipLaunchKernelGGL(k_effdim_weights<3>, dim3(kRedBlocks), dim3(256), 0, st, ft, GK, N, pm, w.wts, w.qmc_partial, 0, net.m);  // any odd p
   FDWT_HIP(hipGetLastError());
   const int h0c = s - 1;  // U_s: its h = 0 term is the h = 0 share of the total
-  const double* tr = w.tab + (size_t)s * kTab;
   for (int c0 = 0; c0 < ncols; c0 += ch) {
     const int c1 = std::min(ncols, c0 + ch);
     const int h0_col = (h0c >= c0 && h0c < c1) ? h0c - c0 : -1;
@@ -1066,29 +1050,26 @@ int eff_dim_enqueue(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
       // through memory (kernel data in A, first pass into B after the U_d).
       double* B = (double*)w.B;
       const int u1 = std::min(c1, s), nu = std::max(0, u1 - c0);
-      if (nu > 0 && (rc = fwt_p2_gen_first(net.m, s, net.d_xtab, net.nbytes, tr, kTab, false, c0, u1, B, blk, st)))
+      if (nu > 0 && (rc = fwt_p2_gen_first(net.m, s, net.d_xtab, net.nbytes, kt, false, c0, u1, B, blk, st)))
         return rc;
       const int q0 = std::max(c0, s);
       if (q0 < c1) {
-        if ((rc = launch_kernel_cols(net, w.tab, tr, q0 + 1, c1 + 1, w.A, st))) return rc;
+        if ((rc = launch_kernel_cols(net, kt, q0 + 1, c1 + 1, w.A, st))) return rc;
         if ((rc = fwt_p2_f64_first(net.m, w.A, B + (size_t)nu * N, c1 - q0, blk, st))) return rc;
       }
       rc = fwt_p2_f64_reduce_rest(net.m, B, c1 - c0, w.wts, w.partial + (size_t)c0 * parts, h0, h0_col, blk, st);
     } else {
-      rc = launch_kernel_cols(net, w.tab, tr, c0 + 1, c1 + 1, w.A, st);
+      rc = launch_kernel_cols(net, kt, c0 + 1, c1 + 1, w.A, st);
       if (rc) return rc;
       int64_t t = 0;
-      const double* unscale = w.tab + (size_t)2 * s * kTab + s + c0 / 2;
-      rc = fwt_reduce_f64(p, net.m, w.A, w.B, c1 - c0, w.wts, p == 2 ? nullptr : unscale,
+      rc = fwt_reduce_f64(p, net.m, w.A, w.B, c1 - c0, w.wts, p == 2 ? nullptr : kt.ix + c0 / 2,
                           w.partial + (size_t)c0 * parts, h0, h0_col, &t, st);
     }
     if (rc) return rc;
   }
-  hipLaunchKernelGGL(k_sum_rows, dim3(ncols), dim3(kSumThreads), 0, st, w.partial, (int)parts, w.res);
-  hipLaunchKernelGGL(k_sum_rows, dim3(1), dim3(kSumThreads), 0, st, w.qmc_partial, kRedBlocks, w.res + 2 * s);
+  hipLaunchKernelGGL(k_effdim_sums, dim3(ncols + 1), dim3(kSumThreads), 0, st, w.partial, (int)parts, ncols,
+                     w.qmc_partial, kRedBlocks, h0, res_host, 2 * s);
   FDWT_HIP(hipGetLastError());
-  if (res_dev) *res_dev = w.res;
-  if (res_host) FDWT_HIP(hipMemcpyAsync(res_host, w.res, eff_dim_res_bytes(net), hipMemcpyDeviceToHost, st));
   return FDWT_OK;
 }
 
@@ -1132,16 +1113,15 @@ static size_t effdim_budget() {
 
 int run_eff_dim(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* ft, fdwt_effdim* out, hipStream_t st) {
   const int ch = eff_dim_chunk(net, effdim_budget());
-  const double* res_dev = nullptr;
   const void* gk = nullptr;
-  int rc = cached_spectrum(net, kern, &gk, st);
+  int rc = ensure_res_host(net);
   if (rc) return rc;
-  rc = eff_dim_enqueue(net, sc, kern, gk, ft, ch, nullptr, &res_dev, st);
+  rc = cached_spectrum(net, kern, &gk, st);
   if (rc) return rc;
-  std::vector<double> res(2 * net.s + 2);
+  rc = eff_dim_enqueue(net, sc, kern, gk, ft, ch, net.res_host, st);
+  if (rc) return rc;
   FDWT_HIP(hipStreamSynchronize(st));
-  FDWT_HIP(hipMemcpy(res.data(), res_dev, eff_dim_res_bytes(net), hipMemcpyDeviceToHost));
-  eff_dim_finish(net.s, res.data(), out);
+  eff_dim_finish(net.s, net.res_host, out);
   return FDWT_OK;
 }
 
@@ -1176,42 +1156,34 @@ int run_split_cost(Net& tr, Scratch& sc, const uint32_t* delta, const float* ft,
   Carve need(nullptr);
   need.take(spectrum_bytes(tr));
   need.take(spectrum_ws_bytes(tr));
-  need.take((size_t)s * kTab * sizeof(double));
-  need.take((size_t)s * 4);
   need.take((size_t)N * 8);
   need.take(kRedBlocks * sizeof(double));
-  need.take(sizeof(double));
   if (int rc = ensure_ws(sc, need.off, st)) return rc;
   Carve cv(sc.ws);
   double* gk = (double*)cv.take(spectrum_bytes(tr));
   void* sw = cv.take(spectrum_ws_bytes(tr));
-  double* tk2 = (double*)cv.take((size_t)s * kTab * sizeof(double));
-  uint32_t* dd = (uint32_t*)cv.take((size_t)s * 4);
   double* g = (double*)cv.take((size_t)N * 8);
   double* partial = (double*)cv.take(kRedBlocks * sizeof(double));
-  double* res = (double*)cv.take(sizeof(double));
-  int rc = spectrum_into(tr, sc, kern, sw, gk, st);  // K_u, unnormalised
+  int rc = ensure_res_host(tr);
   if (rc) return rc;
-  std::vector<double> h2((size_t)s * kTab, 1.0);
-  for (int j = 0; j < s; ++j)
-    for (int t = 0; t <= m2; ++t)
-      h2[(size_t)j * kTab + t] = 1.0 + kern->gamma[j] * kprime(2, kern->alpha, t < m2 ? t + 1 : 0);
-  if ((rc = upload(sc, h2.data(), h2.size() * sizeof(double), tk2, st))) return rc;
-  if ((rc = upload(sc, delta, (size_t)s * 4, dd, st))) return rc;
+  rc = spectrum_into(tr, kern_tab(2, tr.m, kern), sw, gk, st);  // K_u, unnormalised
+  if (rc) return rc;
+  KernTab kt = kern_tab(2, m2, kern);
+  std::memcpy(kt.ix, delta, (size_t)s * 4);
   const size_t lds = (size_t)s * kTab * 8 + (size_t)((s + 1) & ~1) * 4 + (size_t)s * 257 * 4;
   if ((rc = allow_lds((const void*)k_kernel_shift_p2, lds))) return rc;
   const unsigned grid = (unsigned)std::min<int64_t>((N + kChunk - 1) / kChunk, 2048);
-  hipLaunchKernelGGL(k_kernel_shift_p2, dim3(grid), dim3(kChunk), lds, st, net_args(tr), dd, tk2, m2, g);
+  hipLaunchKernelGGL(k_kernel_shift_p2, dim3(grid), dim3(kChunk), lds, st, net_args(tr), kt, m2, g);
   FDWT_HIP(hipGetLastError());
   if ((rc = fwt_run_tmp(2, tr.m, false, K_F64, g, K_F64, K_F64, g, nullptr, 1, 1.0, st))) return rc;
   hipLaunchKernelGGL(k_split_combine, dim3(grid1(N)), dim3(256), 0, st, ft, gk, g, N);
   FDWT_HIP(hipGetLastError());
   if ((rc = fwt_run_tmp(2, tr.m, true, K_F64, g, K_F64, K_F64, g, nullptr, 1, 1.0, st))) return rc;
   hipLaunchKernelGGL(k_sq_diff, dim3(kRedBlocks), dim3(256), 0, st, fval, g, N, partial, sf_out);
-  hipLaunchKernelGGL(k_sum_rows, dim3(1), dim3(kSumThreads), 0, st, partial, kRedBlocks, res);
+  hipLaunchKernelGGL(k_sum_rows, dim3(1), dim3(kSumThreads), 0, st, partial, kRedBlocks, tr.res_host);
   FDWT_HIP(hipGetLastError());
   FDWT_HIP(hipStreamSynchronize(st));
-  FDWT_HIP(hipMemcpy(cost, res, sizeof(double), hipMemcpyDeviceToHost));
+  *cost = tr.res_host[0];
   return FDWT_OK;
 }
 

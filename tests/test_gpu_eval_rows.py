@@ -46,7 +46,7 @@ def check(p, m, s, nq, C, seed):
     (2, 2, 1, 1), (2, 3, 5, 64), (2, 7, 4, 65), (2, 9, 13, 129), (2, 12, 3, 300), (2, 13, 33, 40), (2, 5, 64, 257),
     (3, 1, 1, 3), (3, 2, 4, 66), (3, 4, 9, 128), (3, 7, 14, 70), (3, 8, 2, 300), (3, 3, 64, 20),
     (5, 1, 2, 5), (5, 2, 8, 65), (5, 4, 25, 129), (5, 5, 3, 260), (5, 2, 64, 33),
-    (7, 1, 3, 2), (7, 3, 6, 67), (7, 4, 2, 130), (7, 2, 45, 40), (7, 2, 46, 40)])
+    (7, 1, 3, 2), (7, 3, 6, 67), (7, 4, 2, 130), (7, 2, 43, 40), (7, 2, 44, 40)])
 def test_rows_against_the_direct_sum(p, m, s, nq):
     announce("eval rows", p, m, s, nq)
     check(p, m, s, nq, inputs.upper_triangular_generators(p, m, s, 100 * p + m + s), m + s + nq)
