@@ -614,7 +614,7 @@ int fdwt_split_cost(const fdwt_net* h, const float* f2_dev, double alpha, double
     return fail(FDWT_EINVAL, "need alpha > 1, beta > 0 and finite q");
   DeviceGuard g(h->n.device);
   const double prm[3] = {alpha, beta, q};
-  return split_cost_call(h->n, f2_dev, prm, sf_dev, cost, (hipStream_t)stream);
+  return split_cost_call(const_cast<Net&>(h->n), f2_dev, prm, sf_dev, cost, (hipStream_t)stream);
   FDWT_GUARD_END
 }
 
@@ -628,7 +628,7 @@ int fdwt_kernel_tune(const fdwt_net* h, const float* f2_dev, const double* start
     return fail(FDWT_EINVAL, "need alpha > 1, beta > 0 and finite q at the start");
   if (max_evals < 4 || max_evals > 100000) return fail(FDWT_EINVAL, "max_evals must be in 4..100000");
   DeviceGuard g(h->n.device);
-  return kernel_tune_call(h->n, f2_dev, start, max_evals, out, (hipStream_t)stream);
+  return kernel_tune_call(const_cast<Net&>(h->n), f2_dev, start, max_evals, out, (hipStream_t)stream);
   FDWT_GUARD_END
 }
 

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -70,6 +71,7 @@ struct KernTab {
 };
 
 // ------------------------------------------------------------------- net
+struct SplitPlan;
 struct Net {
   int p = 0, m = 0, s = 0;
   int64_t N = 0;
@@ -93,6 +95,8 @@ struct Net {
   // Pinned host results of eff_dim and split_cost, written by their last
   // kernel (allocated on first use, 2 kMaxS + 2 doubles).
   double* res_host = nullptr;
+  // The split of the points in halves (tune.cpp; p = 2, on first use).
+  std::shared_ptr<SplitPlan> split;
 };
 
 }  // namespace fdwt
@@ -220,8 +224,8 @@ int run_split_cost(Net& tr, Scratch& sc, const uint32_t* delta, const float* ft,
 
 // tune.cpp (Section 5.1): cost of (alpha, beta, q) = prm, and the
 // Nelder-Mead selection from `start`, for a p = 2 net of m + 1 digits.
-int split_cost_call(const Net& n2, const float* f2, const double prm[3], float* sf, double* cost, hipStream_t st);
-int kernel_tune_call(const Net& n2, const float* f2, const double start[3], int max_evals, fdwt_kernel_fit* out,
+int split_cost_call(Net& n2, const float* f2, const double prm[3], float* sf, double* cost, hipStream_t st);
+int kernel_tune_call(Net& n2, const float* f2, const double start[3], int max_evals, fdwt_kernel_fit* out,
                      hipStream_t st);
 
 // K' in double for first-differing-digit index i (0 = no differing digit).

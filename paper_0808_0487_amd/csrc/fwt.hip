@@ -478,6 +478,110 @@ __global__ void __launch_bounds__((P2Shape<LOGE, 0>::THREADS)) fwt_p2_gen(ColGen
 }
 
 
+// One evaluation of the split cost (Section 5.1, run_split_cost) for a first
+// half of 2^LOGE points, by one workgroup: K and G generated as fwt_p2_gen
+// generates K, transformed in the tile (the stages of a single fwt_p2 tile),
+// combined to f~ G / K_u, transformed back, compared with the second half.
+// z = (X_j(n) << 1) ^ delta_j has m + 1 digits (delta 0: the first half).
+// A search makes 100 to 200 of these calls one after another, so what counts
+// is their latency: one launch (about 20 us for 2^13 points) instead of nine
+// of 2 to 8 us and the gaps between them.
+struct SplitTile {
+  const uint32_t* xtab;
+  int nbytes, s, m;
+  const float *ft, *fval;
+  double* ku;        // K_u in passing, N
+  float* sf;         // nullable
+  double* cost;      // pinned host memory
+};
+
+template <int LOGE>
+__global__ void __launch_bounds__((P2Shape<LOGE, 0>::THREADS)) fwt_p2_split(SplitTile g, KernTab kt) {
+  using S = P2Shape<LOGE, 0>;
+  constexpr int EPT = S::EPT, TH = S::THREADS, TB = LOGE - 4;
+  static_assert(LOGE >= 10 && EPT == 16, "16 elements per thread");
+  constexpr int NS = (LOGE - 10) < 4 ? (LOGE - 10) : 4;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double* lds = reinterpret_cast<double*>(smem_raw);
+  const int s = g.s, m2 = LOGE + 1;
+  double* rl = lds + ((cpad(S::E) + 1) & ~1);                     // [s][m2 + 1]
+  uint32_t* cl = reinterpret_cast<uint32_t*>(rl + s * (m2 + 1));  // [s][LOGE]: generator columns
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  stage_kern_tables(kt, s, m2 + 1, rl, nullptr);
+  for (int i = tid; i < s * LOGE; i += TH) {
+    const int j = i / LOGE, c = i % LOGE;
+    cl[i] = g.xtab[((size_t)j * g.nbytes + (c >> 3)) * 256 + (1 << (c & 7))];
+  }
+  double* lrow = lds + cpad(tid);
+  double* lrowS = lds + cpad(lane + 1024 * wv);
+  const int e0 = lane + 1024 * wv;  // stored element k: e0 + 64 k
+  __syncthreads();
+  auto generate = [&](bool shifted, double (&u)[EPT]) {
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) u[k] = 1.0;
+    for (int j = 0; j < s; ++j) {
+      const uint32_t* cj = cl + j * LOGE;
+      uint32_t xt = 0;
+#pragma unroll
+      for (int c = 0; c < TB; ++c) xt ^= cj[c] & (0u - (((uint32_t)tid >> c) & 1u));
+      xt = (xt << 1) ^ (shifted ? (uint32_t)kt.ix[j] : 0u);
+      uint32_t kx[EPT];
+      kx[0] = 0;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const uint32_t cb = cj[TB + b] << 1;
+#pragma unroll
+        for (int k = 0; k < (1 << b); ++k) kx[k + (1 << b)] = kx[k] ^ cb;
+      }
+      const double* rj = rl + j * (m2 + 1);
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) u[k] *= rj[(int)__clz(xt ^ kx[k]) - (32 - m2)];
+    }
+  };
+  // In: element tid + k TH in v[k]; out: element e0 + 64 k.
+  auto transform = [&](double (&v)[EPT]) {
+    reg_bfly<4>(v);
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) lrow[cpad(k * TH)] = v[k];
+    lds_barrier();
+    P2Groups<LOGE, 0, 0, double, 4, 6>::run(lds, tid);
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) v[k] = lrowS[66 * k];
+    reg_bfly<NS>(v);
+    lds_barrier();
+  };
+  double v[EPT];
+  generate(false, v);
+  transform(v);
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) g.ku[e0 + 64 * k] = v[k];  // read back by this thread
+  generate(true, v);
+  transform(v);
+#pragma unroll
+  for (int k = 0; k < EPT; ++k)
+    lrowS[66 * k] = (double)g.ft[e0 + 64 * k] * v[k] / fmax(g.ku[e0 + 64 * k], 1e-300);
+  lds_barrier();
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) v[k] = lrow[cpad(k * TH)];
+  lds_barrier();
+  transform(v);
+  double acc = 0.0;
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    const double d = (double)g.fval[e0 + 64 * k] - v[k];
+    acc += d * d;
+    if (g.sf) g.sf[e0 + 64 * k] = (float)v[k];
+  }
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+  if (lane == 0) lds[wv] = acc;
+  lds_barrier();
+  if (tid == 0) {
+    for (int w = 1; w < TH / 64; ++w) acc += lds[w];
+    *g.cost = acc;
+  }
+}
+
+
 // First pass of the forward transform of a test function sampled at the
 // net (p = 2, fdwt_dwt_forward_family): the 16 values each thread would load
 // are generated instead, f(x_n) at n = tile E + tid + k TH, with the sampling
@@ -1017,6 +1121,9 @@ bool fwt_p2_split_ok(int m) {
 // layout, fwt_p2_blocked_index).
 bool fwt_p2_blocked_ok(int m) { return fwt_p2_split_ok(m) && plan_p2_cols(m).size() == 2; }
 
+// The whole transform is one tile that can generate its own column.
+bool fwt_p2_single_ok(int m) { return m >= 10 && plan_p2_cols(m).size() == 1; }
+
 // Digits of the first pass of the float64 plan for m.
 int fwt_p2_first_loge(int m) { return plan_p2_cols(m)[0].loge; }
 
@@ -1039,15 +1146,19 @@ int fwt_p2_f64_reduce_rest(int m, double* data, int batch, const float2* wts, do
 // First pass of the transforms of generated columns (fwt_p2_gen): the
 // truncation columns U_{d0+1}..U_{d1} from the R' table (kcol false: out
 // receives d1 - d0 columns), or the kernel column K from the K' table (kcol
-// true: one column; d0, d1 unused).
+// true: one column; d0, d1 unused; a net of one tile gets its whole spectrum).
 int fwt_p2_gen_first(int m, int s, const uint32_t* xtab, int nbytes, const KernTab& kt, bool kcol,
                      int d0, int d1, double* out, bool blocked, hipStream_t st) {
-  if (!fwt_p2_split_ok(m) || s < 1 || s > 64 || kTab <= m) return fail(FDWT_EINVAL, "bad generated-column pass");
+  const bool single = kcol && fwt_p2_single_ok(m);
+  if ((!single && !fwt_p2_split_ok(m)) || s < 1 || s > 64 || kTab <= m) return fail(FDWT_EINVAL, "bad generated-column pass");
   if (!kcol && (d0 < 0 || d1 > s || d0 >= d1)) return fail(FDWT_EINVAL, "bad generated-column range");
   const P2Pass g = plan_p2_cols(m)[0];
   const void* fn = nullptr;
-  if (kcol) fn = g.loge == 14 ? (const void*)fwt_p2_gen<14, true>
-                 : g.loge == 13 ? (const void*)fwt_p2_gen<13, true> : (const void*)fwt_p2_gen<12, true>;
+  if (kcol) fn = g.loge == 14   ? (const void*)fwt_p2_gen<14, true>
+                 : g.loge == 13 ? (const void*)fwt_p2_gen<13, true>
+                 : g.loge == 12 ? (const void*)fwt_p2_gen<12, true>
+                 : g.loge == 11 ? (const void*)fwt_p2_gen<11, true>
+                                : (const void*)fwt_p2_gen<10, true>;
   else fn = g.loge == 14 ? (const void*)fwt_p2_gen<14, false>
             : g.loge == 13 ? (const void*)fwt_p2_gen<13, false> : (const void*)fwt_p2_gen<12, false>;
   const int64_t N = int64_t(1) << m;
@@ -1077,6 +1188,30 @@ int fwt_p2_gen_first(int m, int s, const uint32_t* xtab, int nbytes, const KernT
   void* args[] = {(void*)&cg, (void*)&out, (void*)&d, (void*)&kt};
   return launch_timed(fn, dim3((unsigned)G), dim3(threads), args, lds, st, FDWT_TC_PASS_F64,
                       (double)N * ncol * sizeof(double));
+}
+
+// The split cost in one launch (fwt_p2_split): first halves of 2^10..2^14
+// points.
+bool fwt_p2_split_tile_ok(int m) { return m >= 10 && m <= 14; }
+
+int fwt_p2_split_tile(const Net& tr, const KernTab& kt, const float* ft, const float* fval, double* ku, float* sf,
+                      double* cost, hipStream_t st) {
+  const int m = tr.m, E = 1 << m;
+  const void* fn = m == 10   ? (const void*)fwt_p2_split<10>
+                   : m == 11 ? (const void*)fwt_p2_split<11>
+                   : m == 12 ? (const void*)fwt_p2_split<12>
+                   : m == 13 ? (const void*)fwt_p2_split<13>
+                   : m == 14 ? (const void*)fwt_p2_split<14>
+                             : nullptr;
+  if (!fn) return fail(FDWT_EINVAL, "no one-launch split cost for this m");
+  const size_t lds = (size_t)((cpad(E) + 1) & ~1) * sizeof(double) + (size_t)tr.s * (m + 2) * sizeof(double) +
+                     (size_t)tr.s * m * sizeof(uint32_t);
+  if (int rc = allow_lds(fn, lds)) return rc;
+  SplitTile g{tr.d_xtab, tr.nbytes, tr.s, m, ft, fval, ku, sf, cost};
+  KernTab k = kt;
+  void* args[] = {(void*)&g, (void*)&k};
+  FDWT_HIP(hipLaunchKernel(fn, dim3(1), dim3(E / 16), args, lds, st));
+  return FDWT_OK;
 }
 
 // The passes after the first of an unnormalised p = 2 float64 transform, in

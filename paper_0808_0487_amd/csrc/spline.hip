@@ -694,6 +694,10 @@ int fwt_p2_f64_reduce_rest(int m, double* data, int batch, const float2* wts, do
 int fwt_p2_gen_first(int m, int s, const uint32_t* xtab, int nbytes, const KernTab& kt, bool kcol,
                      int d0, int d1, double* out, bool blocked, hipStream_t st);
 int fwt_p2_f64_rest(int m, double* data, int batch, hipStream_t st);
+bool fwt_p2_single_ok(int m);
+bool fwt_p2_split_tile_ok(int m);
+int fwt_p2_split_tile(const Net& tr, const KernTab& kt, const float* ft, const float* fval, double* ku, float* sf,
+                      double* cost, hipStream_t st);
 
 // ------------------------------------------------------ kernel spectrum
 // Unnormalised float64 spectrum of the kernel data K(x_n, 0): p = 2, N
@@ -708,11 +712,12 @@ size_t spectrum_ws_bytes(const Net& net) { return net.p == 2 ? 0 : align_up((siz
 // through the first spectrum_ws_bytes of ws.
 static int spectrum_into(Net& net, const KernTab& kt, void* ws, void* gk, hipStream_t st) {
   int rc = FDWT_OK;
-  if (net.p == 2 && fwt_p2_split_ok(net.m)) {
-    // K generated inside the first pass of its transform (no column in memory).
+  if (net.p == 2 && (fwt_p2_split_ok(net.m) || fwt_p2_single_ok(net.m))) {
+    // K generated inside the first (or only) pass of its transform (no column
+    // in memory).
     if ((rc = fwt_p2_gen_first(net.m, net.s, net.d_xtab, net.nbytes, kt, true, 0, 0, (double*)gk, false, st)))
       return rc;
-    return fwt_p2_f64_rest(net.m, (double*)gk, 1, st);
+    return fwt_p2_single_ok(net.m) ? FDWT_OK : fwt_p2_f64_rest(net.m, (double*)gk, 1, st);
   }
   double* A = net.p == 2 ? (double*)gk : (double*)ws;
   rc = launch_kernel_cols(net, kt, 0, 1, A, st);
@@ -1166,10 +1171,16 @@ int run_split_cost(Net& tr, Scratch& sc, const uint32_t* delta, const float* ft,
   double* partial = (double*)cv.take(kRedBlocks * sizeof(double));
   int rc = ensure_res_host(tr);
   if (rc) return rc;
-  rc = spectrum_into(tr, kern_tab(2, tr.m, kern), sw, gk, st);  // K_u, unnormalised
-  if (rc) return rc;
   KernTab kt = kern_tab(2, m2, kern);
   std::memcpy(kt.ix, delta, (size_t)s * 4);
+  if (fwt_p2_split_tile_ok(tr.m)) {
+    if ((rc = fwt_p2_split_tile(tr, kt, ft, fval, gk, sf_out, tr.res_host, st))) return rc;
+    FDWT_HIP(hipStreamSynchronize(st));
+    *cost = tr.res_host[0];
+    return FDWT_OK;
+  }
+  rc = spectrum_into(tr, kern_tab(2, tr.m, kern), sw, gk, st);  // K_u, unnormalised
+  if (rc) return rc;
   const size_t lds = (size_t)s * kTab * 8 + (size_t)((s + 1) & ~1) * 4 + (size_t)s * 257 * 4;
   if ((rc = allow_lds((const void*)k_kernel_shift_p2, lds))) return rc;
   const unsigned grid = (unsigned)std::min<int64_t>((N + kChunk - 1) / kChunk, 2048);

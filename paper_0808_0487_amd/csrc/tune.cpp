@@ -13,33 +13,42 @@
 #include <algorithm>
 #include <array>
 #include <cmath>
+#include <memory>
 
 #include "fdwt_internal.h"
 
 namespace fdwt {
 
-namespace {
-
-struct Split {
-  fdwt_net* tr = nullptr;        // the first half as an m-digit net
-  std::vector<uint32_t> delta;   // x_N per coordinate, (m + 1)-digit integers
-  float* ft = nullptr;           // forward transform of the first half's values
-  const float* fval = nullptr;   // values at the second half
-  hipStream_t st = nullptr;
-  ~Split() {
+// What the split of a net's points needs besides the data: the first half as
+// a net of its own, with its workspace, and the shift.  Kept in the handle of
+// the whole net (it depends on the generators alone), so that a call neither
+// builds tables nor allocates.
+struct SplitPlan {
+  fdwt_net* tr = nullptr;       // the first half as an m-digit net
+  std::vector<uint32_t> delta;  // x_N per coordinate, (m + 1)-digit integers
+  float* ft = nullptr;          // forward transform of the first half's values
+  ~SplitPlan() {
     if (ft) {
-      (void)hipStreamSynchronize(st);
+      (void)hipDeviceSynchronize();
       (void)hipFree(ft);
     }
     if (tr) fdwt_net_free(tr);
   }
 };
 
-int split_setup(const Net& n2, const float* f2, Split& sp, hipStream_t st) {
+namespace {
+
+struct Split {
+  SplitPlan* plan = nullptr;
+  const float* fval = nullptr;  // values at the second half
+  hipStream_t st = nullptr;
+};
+
+int split_plan(Net& n2) {
+  if (n2.split) return FDWT_OK;
   if (n2.p != 2) return fail(FDWT_EUNSUPPORTED, "kernel-parameter selection is defined for p = 2 (Section 5.1)");
   if (n2.m < 2) return fail(FDWT_EINVAL, "the net needs m >= 2 digits (two halves of at least 2 points)");
   const int m2 = n2.m, m = m2 - 1, s = n2.s;
-  const int64_t N = int64_t(1) << m;
   auto C = [&](int j, int r, int c) { return (int)n2.C[((size_t)j * m2 + r) * m2 + c]; };
   for (int j = 0; j < s; ++j)
     for (int c = 0; c < m; ++c)
@@ -48,24 +57,33 @@ int split_setup(const Net& n2, const float* f2, Split& sp, hipStream_t st) {
   for (int j = 0; j < s; ++j)
     for (int r = 0; r < m; ++r)
       for (int c = 0; c < m; ++c) lead[((size_t)j * m + r) * m + c] = (uint8_t)C(j, r, c);
-  if (int rc = fdwt_net_generate(2, m, s, lead.data(), &sp.tr)) return rc;
-  sp.delta.assign(s, 0u);
+  auto plan = std::make_shared<SplitPlan>();
+  if (int rc = fdwt_net_generate(2, m, s, lead.data(), &plan->tr)) return rc;
+  plan->delta.assign(s, 0u);
   for (int j = 0; j < s; ++j)
     for (int r = 0; r < m2; ++r)
-      if (C(j, r, m)) sp.delta[j] |= 1u << (m2 - 1 - r);
+      if (C(j, r, m)) plan->delta[j] |= 1u << (m2 - 1 - r);
+  FDWT_HIP(hipMalloc(&plan->ft, (size_t)plan->tr->n.N * sizeof(float)));
+  n2.split = plan;
+  return FDWT_OK;
+}
+
+int split_setup(Net& n2, const float* f2, Split& sp, hipStream_t st) {
+  if (int rc = split_plan(n2)) return rc;
+  sp.plan = n2.split.get();
+  const int64_t N = sp.plan->tr->n.N;
   sp.st = st;
-  FDWT_HIP(hipMalloc(&sp.ft, (size_t)N * sizeof(float)));
-  if (int rc = fwt_run(2, m, false, K_F32, f2, K_F32, K_F32, sp.ft, 1, 1.0 / (double)N, st)) return rc;
+  if (int rc = fwt_run(2, n2.m - 1, false, K_F32, f2, K_F32, K_F32, sp.plan->ft, 1, 1.0 / (double)N, st)) return rc;
   sp.fval = f2 + N;
   return FDWT_OK;
 }
 
 int split_eval(Split& sp, const double prm[3], float* sf, double* cost) {
-  Net& tr = sp.tr->n;
+  Net& tr = sp.plan->tr->n;
   std::vector<double> gam(tr.s);
   for (int j = 0; j < tr.s; ++j) gam[j] = prm[1] * std::pow((double)(j + 1), prm[2]);  // gamma_j = beta j^q
   const fdwt_kernel kern{prm[0], gam.data(), tr.s};
-  return run_split_cost(tr, tr.sc, sp.delta.data(), sp.ft, sp.fval, &kern, sf, cost, sp.st);
+  return run_split_cost(tr, tr.sc, sp.plan->delta.data(), sp.plan->ft, sp.fval, &kern, sf, cost, sp.st);
 }
 
 std::array<double, 3> to_params(const std::array<double, 3>& th) {
@@ -74,13 +92,13 @@ std::array<double, 3> to_params(const std::array<double, 3>& th) {
 
 }  // namespace
 
-int split_cost_call(const Net& n2, const float* f2, const double prm[3], float* sf, double* cost, hipStream_t st) {
+int split_cost_call(Net& n2, const float* f2, const double prm[3], float* sf, double* cost, hipStream_t st) {
   Split sp;
   if (int rc = split_setup(n2, f2, sp, st)) return rc;
   return split_eval(sp, prm, sf, cost);
 }
 
-int kernel_tune_call(const Net& n2, const float* f2, const double start[3], int max_evals, fdwt_kernel_fit* out,
+int kernel_tune_call(Net& n2, const float* f2, const double start[3], int max_evals, fdwt_kernel_fit* out,
                      hipStream_t st) {
   Split sp;
   if (int rc = split_setup(n2, f2, sp, st)) return rc;
