@@ -1,6 +1,7 @@
 // C ABI of libfdwt: argument validation, net handles, workspace ownership and
 // dispatch to the HIP kernels.  Every entry point returns a status code and
 // never lets an exception escape.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <exception>
@@ -376,11 +377,10 @@ int fdwt_net_generate(int p, int m, int s, const uint8_t* C_host, fdwt_net** out
         for (int r = 0; r < m; ++r)
           if (C(j, r, c) & 1) col[c] |= 1u << (m - 1 - r);
       for (int b = 0; b < net.nbytes; ++b)
-        for (int v = 0; v < 256; ++v) {
-          uint32_t x = 0;
-          for (int t = 0; t < 8; ++t)
-            if ((v >> t) & 1 && 8 * b + t < m) x ^= col[8 * b + t];
-          tab[((size_t)j * net.nbytes + b) * 256 + v] = x;
+        for (int v = 1; v < 256; ++v) {
+          const int c = 8 * b + __builtin_ctz(v);
+          uint32_t* t = tab.data() + ((size_t)j * net.nbytes + b) * 256;
+          t[v] = t[v & (v - 1)] ^ (c < m ? col[c] : 0u);
         }
     }
     if (hipMalloc(&net.d_xtab, tab.size() * 4) != hipSuccess) {
@@ -393,15 +393,28 @@ int fdwt_net_generate(int p, int m, int s, const uint8_t* C_host, fdwt_net** out
       return fail(FDWT_EDEVICE, "table upload failed");
     }
   } else {
-    // Packed digits of v * (column c of C_j) mod p, digit y_{r+1} at bits 4(m-1-r).
-    std::vector<uint64_t> tab((size_t)s * m * p, 0);
+    // Packed digits (digit y_{r+1} at bits 4(m-1-r)) of the sum, mod p, of the
+    // generator columns' multiples selected by each value of each group of
+    // odd_digits(p) index digits.
+    const int K = odd_digits(p), pk = (int)ipow(p, K), nch = (m + K - 1) / K;
+    std::vector<uint64_t> tab((size_t)s * nch * pk, 0);
+    // Field-wise sum mod p of packed digits (fields below 8, as on the device).
+    const uint64_t ones = 0x1111111111111111ull;
+    auto addmod = [&](uint64_t x, uint64_t y) {
+      const uint64_t t = x + y;
+      return t - (uint64_t)p * (((t + (8 - p) * ones) >> 3) & ones);
+    };
     for (int j = 0; j < s; ++j)
-      for (int c = 0; c < m; ++c)
-        for (int v = 0; v < p; ++v) {
-          uint64_t x = 0;
-          for (int r = 0; r < m; ++r) x |= (uint64_t)((v * C(j, r, c)) % p) << (4 * (m - 1 - r));
-          tab[((size_t)j * m + c) * p + v] = x;
-        }
+      for (int g = 0; g < nch; ++g) {
+        uint64_t* t = tab.data() + ((size_t)j * nch + g) * pk;
+        int64_t n = 1;  // entries done: the values of the digits before c
+        for (int c = g * K; c < std::min(m, (g + 1) * K); ++c, n *= p)
+          for (int v = 1; v < p; ++v) {
+            uint64_t x = 0;
+            for (int r = 0; r < m; ++r) x |= (uint64_t)((v * C(j, r, c)) % p) << (4 * (m - 1 - r));
+            for (int64_t w = 0; w < n; ++w) t[v * n + w] = addmod(t[w], x);
+          }
+      }
     if (hipMalloc(&net.d_ptab, tab.size() * 8) != hipSuccess) {
       delete h;
       return fail(FDWT_ENOMEM, "table allocation failed");

@@ -9,12 +9,13 @@
 //   group into LDS, and each thread adds only its low-byte table entry (also
 //   in LDS).
 // p odd: digits are packed in 4-bit fields, digit y_{r+1} at bits 4(m-1-r);
-//   the contribution v * (column c of C_j) mod p of each index digit v comes
-//   from a table and is added field-wise modulo p.  OddCoords splits the
-//   index as n = h p^K + r: a workgroup table (LDS) holds the packed sum over
-//   the K low digits for every r < p^K, and per group of 256 consecutive
-//   points the few high parts h that occur are summed once into LDS, so a
-//   coordinate costs one field-wise addition.
+//   the handle's tables hold the packed sum over each group of K index digits
+//   (4 for p = 3, 2 for p = 5, 7) for every value of the group, and the
+//   groups' sums are added field-wise modulo p.  A workgroup keeps the lowest
+//   group's table in LDS, and per 256 consecutive points the few values of
+//   the index above it are summed once into LDS, so a coordinate costs one
+//   field-wise addition.  (With tables of single digits every workgroup
+//   formed these sums itself, a chain of lookups: 8 us at its start.)
 #pragma once
 
 #include "fdwt_internal.h"
@@ -47,6 +48,17 @@ __device__ __forceinline__ void stage_kern_tables(const KernTab& kt, int s, int 
 
 constexpr int kChunk = 256;  // points per group (= threads per workgroup)
 
+// XOR of the tables of the bytes above the lowest at point n (nbytes <= 4):
+// unconditional loads (a missing byte reads entry 0 of a present one, X of 0),
+// so that the three are in flight together.
+__device__ __forceinline__ uint32_t upper_x(const uint32_t* xtab, int nbytes, int j, int64_t n) {
+  const uint32_t* tj = xtab + (int64_t)j * nbytes * 256;
+  uint32_t v = 0;
+#pragma unroll
+  for (int b = 1; b < 4; ++b) v ^= tj[b < nbytes ? b * 256 + (int)((n >> (8 * b)) & 255) : 0];
+  return v;
+}
+
 struct P2Coords {
   const uint32_t* xtab;  // [s][nbytes][256]
   int nbytes, s;
@@ -55,6 +67,7 @@ struct P2Coords {
 
   // Low-byte tables into LDS (call once per workgroup; ends with a barrier).
   __device__ __forceinline__ void stage_tables() const {
+#pragma unroll 4
     for (int i = threadIdx.x; i < s * 256; i += blockDim.x)
       t0[i] = xtab[(int64_t)(i >> 8) * nbytes * 256 + (i & 255)];
     __syncthreads();
@@ -62,12 +75,7 @@ struct P2Coords {
   // XOR of the upper-byte tables for the group starting at `base` (a multiple
   // of 256).  Callers put a barrier before (LDS reuse) and after.
   __device__ __forceinline__ void stage_group(int64_t base) const {
-    for (int j = threadIdx.x; j < s; j += blockDim.x) {
-      uint32_t v = 0;
-      const uint32_t* tj = xtab + (int64_t)j * nbytes * 256;
-      for (int b = 1; b < nbytes; ++b) v ^= tj[b * 256 + (int)((base >> (8 * b)) & 255)];
-      u[j] = v;
-    }
+    for (int j = threadIdx.x; j < s; j += blockDim.x) u[j] = upper_x(xtab, nbytes, j, base);
   }
   __device__ __forceinline__ uint32_t X(int j, int64_t n) const { return t0[j * 256 + (int)(n & 255)] ^ u[j]; }
 };
@@ -84,32 +92,41 @@ __device__ __forceinline__ uint64_t addmod_packed(uint64_t a, uint64_t b) {
 }
 
 // Packed digits of X_j(n) through workgroup tables (see the file comment).
-// Layout in LDS: t0 [s][PK] then u [s][NH] (uint64).
+// Layout in LDS: t0 [s][PK], u [s][NH] (uint64).
 template <int P>
 struct OddCoords {
-  static constexpr int K = P == 3 ? 4 : 2;               // low digits per table entry
+  static constexpr int K = odd_digits(P);                // index digits per table entry
   static constexpr int PK = P == 3 ? 81 : P * P;         // P^K
   static constexpr int NH = kChunk / PK + 2;             // high parts per group (at most)
+  static constexpr int NG = P == 3 ? 4 : (P == 5 ? 6 : 5);  // groups of the largest net
   static constexpr size_t lds_bytes(int s) { return (size_t)s * (PK + NH) * 8; }
-  const uint64_t* ptab;  // [s][m][P] (global)
+  const uint64_t* ptab;  // [s][groups][PK] (global)
   int s, m;
   uint64_t* t0;          // LDS [s][PK]
   uint64_t* u;           // LDS [s][NH]
   uint32_t hi0 = 0;
 
-  // Low-digit tables (once per workgroup; ends with a barrier).
-  __device__ __forceinline__ void stage_tables() const {
-    for (int i = threadIdx.x; i < s * PK; i += blockDim.x) {
-      const int j = i / PK;
-      int r = i - j * PK;
-      const uint64_t* t = ptab + (int64_t)j * m * P;
-      uint64_t acc = 0;
-      for (int c = 0; c < K && c < m; ++c) {
-        acc = addmod_packed<P>(acc, t[c * P + r % P]);
-        r /= P;
-      }
-      t0[i] = acc;
+  static __device__ __forceinline__ int groups(int m) { return (m + K - 1) / K; }
+  // Sum over the groups from the second on, at index h of those digits
+  // (unconditional loads: a missing group reads entry 0 of the first, zero).
+  static __device__ __forceinline__ uint64_t upper(const uint64_t* ptab, int m, int j, uint32_t h) {
+    const int ng = groups(m);
+    const uint64_t* t = ptab + (int64_t)j * ng * PK;
+    uint64_t v[NG - 1];
+#pragma unroll
+    for (int g = 1; g < NG; ++g) {
+      v[g - 1] = t[g < ng ? g * PK + (int)(h % PK) : 0];
+      h /= PK;
     }
+#pragma unroll
+    for (int g = 1; g < NG - 1; ++g) v[0] = addmod_packed<P>(v[0], v[g]);
+    return v[0];
+  }
+  // Low-group tables (once per workgroup; ends with a barrier).
+  __device__ __forceinline__ void stage_tables() const {
+    const int ng = groups(m);
+#pragma unroll 4
+    for (int i = threadIdx.x; i < s * PK; i += blockDim.x) t0[i] = ptab[(int64_t)(i / PK) * ng * PK + i % PK];
     __syncthreads();
   }
   // High parts of the group starting at `base` (a multiple of kChunk).
@@ -119,14 +136,7 @@ struct OddCoords {
     const int nh = (int)((base + kChunk - 1) / PK - hi0 + 1);
     for (int i = threadIdx.x; i < s * nh; i += blockDim.x) {
       const int j = i / nh, k = i - (i / nh) * nh;
-      uint32_t h = hi0 + k;
-      const uint64_t* t = ptab + (int64_t)j * m * P;
-      uint64_t acc = 0;
-      for (int c = K; c < m; ++c) {
-        acc = addmod_packed<P>(acc, t[c * P + h % P]);
-        h /= P;
-      }
-      u[j * NH + k] = acc;
+      u[j * NH + k] = upper(ptab, m, j, hi0 + k);
     }
   }
   // Index split of point n (n < 2^26) for X(): r = n mod PK, h - hi0.
@@ -163,6 +173,13 @@ __device__ __forceinline__ uint64_t eval_string_odd(uint64_t pk, int m) {
   uint64_t v = 0;
   for (int f = 0; f < m; ++f) v |= ((pk >> (4 * (m - 1 - f))) & 7ull) << (63 - B * (f + 1));
   return v;
+}
+
+// Workgroups for ngroups equal point groups: at most `most`, each with the
+// same number of groups (or one fewer).
+inline unsigned even_grid(int64_t ngroups, int64_t most) {
+  const int64_t per = (ngroups + most - 1) / most;
+  return (unsigned)((ngroups + per - 1) / per);
 }
 
 // Index t of the first non-zero digit (t = i - 1) of x_{n,j}, or m when

@@ -101,25 +101,17 @@ __global__ void __launch_bounds__(256) k_row_words_p2(const uint32_t* __restrict
   }
 }
 
-// p odd: the generator columns' multiples in LDS, one field-wise addition per
-// index digit.
 template <int P>
 __global__ void __launch_bounds__(256) k_row_words_odd(const uint64_t* __restrict__ ptab, int s, int m, int64_t nblk,
                                                        uint32_t* __restrict__ out) {
   using R = RowCfg<P>;
-  extern __shared__ __align__(16) uint64_t lt[];  // [s][m][P]
-  for (int i = threadIdx.x; i < s * m * P; i += blockDim.x) lt[i] = ptab[i];
-  __syncthreads();
+  using O = OddCoords<P>;
   const int64_t total = nblk * s;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    uint32_t h = (uint32_t)(i / s);
-    const uint32_t j = (uint32_t)(i - (int64_t)h * s);
-    const uint64_t* t = lt + (size_t)j * m * P;
-    uint64_t x = 0;
-    for (int c = 1; c < m; ++c) {
-      x = addmod_packed<P>(x, t[c * P + h % P]);
-      h /= P;
-    }
+    const uint32_t h = (uint32_t)(i / s), n = h * P;
+    const int j = (int)(i - (int64_t)h * s);
+    const uint64_t x = addmod_packed<P>(ptab[(int64_t)j * O::groups(m) * O::PK + n % O::PK],
+                                        O::upper(ptab, m, j, n / O::PK));
     // digit r + 1 of X_j at bits 4(m - 1 - r)
     uint32_t w = 1u + (uint32_t)((x >> (4 * (m - 1))) & 15u);
     for (int f = 1; f < m && f <= R::ND; ++f) w |= (uint32_t)((x >> (4 * (m - 1 - f))) & 15u) << (32 - R::DB * f);
@@ -199,14 +191,22 @@ __device__ __forceinline__ void mul_row(float* pr, uint32_t a, uint32_t off) {
 // [y bpc, (y + 1) bpc); a workgroup adds its sub-chunks' sums in order and
 // writes one partial sum per query.  SG: coordinates rounded up to 4.
 // Point words, c and the first digits are wave-uniform: scalar loads.
-// Factors are multiplied in the order of the coordinates, the float sums run
-// over 60 to 64 points and are then added as float pairs.
+// Factors are multiplied in the order of the coordinates; the float sums are
+// closed every 64 points (at multiples of 64 where a sub-chunk has more than
+// 128 points) and then added as float pairs, as in k_spline_eval.
+// Two workgroups of 1024 threads share a CU while a wave needs at most 64
+// vector and 80 scalar registers: asked of the compiler where the query words
+// leave room (p = 3, s = 10 without it: 86 scalar registers, 6.9 against
+// 4.75 ms).
+constexpr int row_waves(int p, int sg, int th) {
+  return sg <= (p == 2 ? 36 : (p == 3 ? 20 : 12)) ? 8 : th / 256;
+}
 template <int P, int SG, int TH>
-__global__ void __launch_bounds__(TH) k_eval_rows(const uint32_t* __restrict__ xw, const float* __restrict__ c, int nblk,
+__global__ void __launch_bounds__(TH, row_waves(P, SG, TH)) k_eval_rows(const uint32_t* __restrict__ xw, const float* __restrict__ c, int nblk,
                                                   int s, const void* __restrict__ qv, int64_t nq,
                                                   KernTab kt, int tqw, int bpc, df* __restrict__ partial) {
   using R = RowCfg<P>;
-  constexpr int B = R::B, NT = R::NT, JB = row_bytes<P>(), HB = 64 / B;
+  constexpr int B = R::B, NT = R::NT, JB = row_bytes<P>();
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x;
   float* tt = reinterpret_cast<float*>(smem + (size_t)s * JB);  // [s][kRowT]
@@ -332,39 +332,54 @@ __global__ void __launch_bounds__(TH) k_eval_rows(const uint32_t* __restrict__ x
       }
     }
   };
-  auto step = [&](int h, float& sum, auto& pr) {
+  // Points whose factors may need the exact path (NaN products).
+  auto mend = [&](int h, auto& pr) {
     constexpr int U = sizeof(pr) / sizeof(float) / B;
-    products(h, pr);
-    float next = sum;
 #pragma unroll
-    for (int u = 0; u < U * B; ++u) next += cs[(int64_t)h * B + u] * pr[u];
-    if (__builtin_isnan(next)) {
+    for (int v = 0; v < U; ++v) {
+      bool rare = false;
 #pragma unroll
-      for (int v = 0; v < U; ++v) {
-        bool rare = false;
-#pragma unroll
-        for (int u = 0; u < B; ++u) rare |= __builtin_isnan(pr[v * B + u]);
-        if (rare) exact(h + v, pr + v * B);
-      }
-      next = sum;
-#pragma unroll
-      for (int u = 0; u < U * B; ++u) next += cs[(int64_t)h * B + u] * pr[u];
+      for (int u = 0; u < B; ++u) rare |= __builtin_isnan(pr[v * B + u]);
+      if (rare) exact(h + v, pr + v * B);
     }
-    sum = next;
   };
+  int left = 64;  // points until the float sum is closed (wave-uniform)
+  float sum = 0.0f;
   for (int h = h0; h < h1;) {
-    float sum = 0.0f;
-    const int he = min(h1, h + HB);
-    for (; h + R::U <= he; h += R::U) {
+    const int he = h + min((left - 1) / (R::U * B), (h1 - h) / R::U) * R::U;
+    left -= (he - h) * B;
+    for (; h < he; h += R::U) {
       float pr[R::U * B];
-      step(h, sum, pr);
+      products(h, pr);
+      float next = sum;
+#pragma unroll
+      for (int u = 0; u < R::U * B; ++u) next += cs[(int64_t)h * B + u] * pr[u];
+      if (__builtin_isnan(next)) {
+        mend(h, pr);
+        next = sum;
+#pragma unroll
+        for (int u = 0; u < R::U * B; ++u) next += cs[(int64_t)h * B + u] * pr[u];
+      }
+      sum = next;
     }
-    if (R::U > 1) for (; h < he; ++h) {
+    if (h < h1) {  // one block, in which the sum may be closed
       float pr[B];
-      step(h, sum, pr);
+      products(h, pr);
+      mend(h, pr);
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        sum += cs[(int64_t)h * B + u] * pr[u];
+        if (u + 1 == left) {
+          acc = add(acc, df{sum, 0.0f});
+          sum = 0.0f;
+        }
+      }
+      left -= B;
+      if (left <= 0) left += 64;
+      ++h;
     }
-    acc = add(acc, df{sum, 0.0f});
   }
+  acc = add(acc, df{sum, 0.0f});
   // Sub-chunks of the workgroup in order (the rows are no longer needed).
   __syncthreads();
   df* red = reinterpret_cast<df*>(smem);
@@ -409,25 +424,34 @@ bool eval_rows_ok(const Net& net) {
 // p = 5, 7: three registers per coordinate) leave the loop its registers.
 constexpr int row_threads(int p, int sg) { return (p == 2 ? 1 : (p == 3 ? 2 : 3)) * sg > 80 ? 512 : 1024; }
 
-// Query groups of 64 tqw queries x gy workgroups, bpc blocks per sub-chunk;
-// a function of the shape alone, so that a result does not depend on where
-// it runs.  About two workgroups per CU and round, one round for small
-// problems, up to four where a sub-chunk keeps 64 blocks or more.
+// Query groups of 64 tqw queries x gy workgroups, bpc blocks per sub-chunk; a
+// function of the shape alone, so that a result does not depend on where it
+// runs.  Of the divisions into up to eight rounds of workgroups, the one with
+// the least work on the busiest slot (a workgroup's start counted as 12
+// blocks); sub-chunks of 128 points or more end at multiples of 64.
 void eval_rows_grid(int p, int s, int64_t N, int64_t nq, int* tqw_out, int* gy_out, int* bpc_out) {
-  const int waves = row_threads(p, (s + 3) / 4 * 4) / 64;
+  const int sg = (s + 3) / 4 * 4, th = row_threads(p, sg);
+  const int64_t slots = 256 * (row_waves(p, sg, th) * 256 / th);
   const int64_t nblk = N / (p == 2 ? 4 : p);
   const int tqw = nq <= 64 ? 1 : (nq <= 128 ? 2 : 4);
-  const int nsub = waves / tqw;
+  const int nsub = th / 64 / tqw;
   const int64_t qg = (nq + 64 * tqw - 1) / (64 * tqw);
-  int64_t gy = std::max<int64_t>(1, 512 / qg);
-  const int64_t per = nblk / (gy * nsub);
-  if (per >= 64) gy *= std::min<int64_t>(4, per / 64);
-  gy = std::max<int64_t>(1, std::min(gy, nblk / (8 * nsub)));
-  const int64_t bpc = (nblk + gy * nsub - 1) / (gy * nsub);
-  gy = (nblk + bpc * nsub - 1) / (bpc * nsub);
-  *tqw_out = tqw;
-  *gy_out = (int)gy;
-  *bpc_out = (int)bpc;
+  const int unit = p == 2 ? 16 : 64;  // blocks that end at a multiple of 64 points
+  int64_t best = -1;
+  for (int rounds = 1; rounds <= 8; ++rounds) {
+    int64_t gy = std::max<int64_t>(1, std::min(rounds * slots / qg, nblk / (8 * nsub)));
+    int64_t bpc = std::max<int64_t>(1, (nblk + gy * nsub - 1) / (gy * nsub));
+    if (bpc >= 2 * unit) bpc = (bpc + unit - 1) / unit * unit;
+    gy = std::max<int64_t>(1, (nblk + bpc * nsub - 1) / (bpc * nsub));
+    // (One round of long workgroups ends unevenly: p = 7, N = 7^6, 20000
+    // queries 1.18 ms in one, 1.03 ms in more.)
+    const int64_t cost = (gy * qg + slots - 1) / slots * (bpc + 12) + (rounds == 1 && bpc >= 256 ? bpc / 4 : 0);
+    if (best >= 0 && cost >= best) continue;
+    best = cost;
+    *tqw_out = tqw;
+    *gy_out = (int)gy;
+    *bpc_out = (int)bpc;
+  }
 }
 
 // The prefixes of every coordinate into kt.ix.
@@ -441,15 +465,14 @@ static unsigned rows_grid1(int64_t n) { return (unsigned)std::min<int64_t>((n + 
 int launch_row_words(const Net& net, uint32_t* out, hipStream_t st) {
   const int64_t nblk = net.N / (net.p == 2 ? 4 : net.p);
   const unsigned g = rows_grid1(nblk * net.s);
-  const size_t lds = net.p == 2 ? 0 : (size_t)net.s * net.m * net.p * 8;
   if (net.p == 2) {
     hipLaunchKernelGGL(k_row_words_p2, dim3(g), dim3(256), 0, st, net.d_xtab, net.nbytes, net.s, net.m, nblk, out);
   } else if (net.p == 3) {
-    hipLaunchKernelGGL(k_row_words_odd<3>, dim3(g), dim3(256), lds, st, net.d_ptab, net.s, net.m, nblk, out);
+    hipLaunchKernelGGL(k_row_words_odd<3>, dim3(g), dim3(256), 0, st, net.d_ptab, net.s, net.m, nblk, out);
   } else if (net.p == 5) {
-    hipLaunchKernelGGL(k_row_words_odd<5>, dim3(g), dim3(256), lds, st, net.d_ptab, net.s, net.m, nblk, out);
+    hipLaunchKernelGGL(k_row_words_odd<5>, dim3(g), dim3(256), 0, st, net.d_ptab, net.s, net.m, nblk, out);
   } else {
-    hipLaunchKernelGGL(k_row_words_odd<7>, dim3(g), dim3(256), lds, st, net.d_ptab, net.s, net.m, nblk, out);
+    hipLaunchKernelGGL(k_row_words_odd<7>, dim3(g), dim3(256), 0, st, net.d_ptab, net.s, net.m, nblk, out);
   }
   FDWT_HIP(hipGetLastError());
   return FDWT_OK;

@@ -80,8 +80,9 @@ struct Net {
   std::vector<uint8_t> C;   // the generators, [s][m][m] as given
   // p = 2: uint32 [s][nbytes][256], XOR of generator columns per byte of n.
   uint32_t* d_xtab = nullptr;
-  // p odd: uint64 [s][m][p]: packed digits (4-bit fields, digit y_{r+1} at
-  // bits 4(m-1-r)) of v * column c of C_j mod p.
+  // p odd: uint64 [s][groups][p^K], K = odd_digits(p): the packed digits
+  // (4-bit fields, digit y_{r+1} at bits 4(m-1-r)) of X_j for every value of
+  // every group of K index digits.
   uint64_t* d_ptab = nullptr;
   // Workspace and staging of the handle's own calls (grow-only).
   Scratch sc;
@@ -108,6 +109,8 @@ struct fdwt_net {
 namespace fdwt {
 
 int64_t ipow(int64_t b, int e);
+// Index digits per group of the odd-p tables.
+__host__ __device__ constexpr int odd_digits(int p) { return p == 3 ? 4 : 2; }
 
 // Makes a device current for the duration of a call.
 struct DeviceGuard {

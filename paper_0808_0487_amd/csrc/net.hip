@@ -98,12 +98,7 @@ __global__ void __launch_bounds__(256) k_sample_p2(const uint32_t* xtab, int nby
   const float inv = 1.0f / (float)(1u << m);
   for (int64_t base = (int64_t)blockIdx.x * kSampleBlock; base < N; base += (int64_t)gridDim.x * kSampleBlock) {
     __syncthreads();
-    for (int j = tid; j < s; j += 256) {
-      uint32_t v = 0;
-      const uint32_t* tj = xtab + (size_t)j * nbytes * 256;
-      for (int b = 1; b < nbytes; ++b) v ^= tj[b * 256 + (int)((base >> (8 * b)) & 255)];
-      ub[j] = v;
-    }
+    for (int j = tid; j < s; j += 256) ub[j] = upper_x(xtab, nbytes, j, base);
     __syncthreads();
     typename FamState<FAM>::T acc[16];
 #pragma unroll
@@ -159,8 +154,7 @@ __global__ void __launch_bounds__(kChunk) k_sample_odd(const uint64_t* ptab, Fam
 // Enough workgroups to fill the chip several times over, few enough that the
 // per-workgroup table staging is amortised over many point groups.
 static unsigned grid_for(int64_t N, int threads) {
-  int64_t b = (N + threads - 1) / threads;
-  return (unsigned)std::min<int64_t>(b, 2048);
+  return even_grid((N + threads - 1) / threads, 2048);
 }
 
 static double inv_pm(const Net& net) { return 1.0 / (double)net.N; }

@@ -42,7 +42,8 @@ struct NetArgs {
 };
 
 // ------------------------------------------------ kernel-data columns (f64)
-// Column layout: 0 = K, 1..s = U_d (d = 1..s), s+1..2s = Q_j (j = 1..s).
+// Column layout: 0 = K (alone, c0 = 0 and c1 = 1), 1..s = U_d (d = 1..s),
+// s+1..2s = Q_j (j = 1..s).
 // Writes columns [c0, c1) to out[(c - c0) * N + n].  The elementary symmetric
 // polynomials e_0..e_SMAX live in registers (updates unrolled, truncated per
 // chunk of coordinates where the higher ones are still zero).  p odd: the
@@ -77,19 +78,29 @@ __global__ void __launch_bounds__(kChunk) k_kernel_cols(NetArgs na, KernTab kt, 
     int orr = 0, ok = 0;
     if constexpr (P != 2) oc.split(nn, orr, ok);
     double K = 1.0, u = 0.0, held = 0.0;
+    // The columns come in ascending order: `o` runs along.  The empty asm makes
+    // the bounds opaque per group; otherwise the conditions and addresses of
+    // every column are kept in scalar registers across the loop, hundreds of
+    // them spilled.
+    int b0 = c0, b1 = c1, bs = s;
+    asm volatile("" : "+s"(b0), "+s"(b1), "+s"(bs));
+    double* o = out + (P == 2 ? n : 2 * n);
     auto emit = [&](int c, double v) {  // column c of [c0, c1)
       if constexpr (P == 2) {
-        if (n < N) out[(int64_t)(c - c0) * N + n] = v;
+        if (n < N) *o = v;
+        o += N;
       } else {
-        const int i = c - c0;
+        const int i = c - b0;
         if (i & 1) {
           v = ldexp(v, kt.ix[(c - 1) >> 1]);
         } else {
           held = v;
           v = 0.0;
         }
-        if (((i & 1) || c + 1 == c1) && n < N)
-          reinterpret_cast<double2*>(out)[(int64_t)(i >> 1) * N + n] = make_double2(held, v);
+        if ((i & 1) || c + 1 == b1) {
+          if (n < N) *reinterpret_cast<double2*>(o) = make_double2(held, v);
+          o += 2 * N;
+        }
       }
     };
     double e[SMAX + 1];
@@ -99,23 +110,35 @@ __global__ void __launch_bounds__(kChunk) k_kernel_cols(NetArgs na, KernTab kt, 
     // only e[1..4(q + 1)] can be non-zero, so the update of the symmetric
     // polynomials stops there (a compile-time bound per chunk).  The last
     // chunk runs to s: s > SMAX only when no symmetric polynomial is wanted
-    // (K and the U_d alone).
+    // (K and the U_d alone).  The four coordinates' table values are looked up
+    // together, so that their chains of LDS reads overlap.
 #pragma unroll
     for (int q = 0; q < SMAX / 4; ++q) {
       const int je = (q == SMAX / 4 - 1 || 4 * q + 4 > s) ? s : 4 * q + 4;
-      for (int j = 4 * q; j < je; ++j) {
-        int t;
-        if constexpr (P == 2) t = lead_p2(pc.X(j, nn), m);
-        else t = lead_odd(oc.X(j, orr, ok), m);
-        K *= ltk[j * kTab + t];
-        if (need_r) {
-          const double r = ltr[j * kTab + t];
-          u = u + r + u * r;  // (1 + u)(1 + r) - 1
-          const int c = 1 + j;
-          if (c >= c0 && c < c1) emit(c, u);
-          if (need_q) {
+      for (int j0 = 4 * q; j0 < je; j0 += 4) {
+        double kf[4], rf[4];
 #pragma unroll
-            for (int i = 4 * q + 4; i >= 1; --i) e[i] += r * e[i - 1];
+        for (int a = 0; a < 4; ++a) {
+          const int j = min(j0 + a, s - 1);
+          int t;
+          if constexpr (P == 2) t = lead_p2(pc.X(j, nn), m);
+          else t = lead_odd(oc.X(j, orr, ok), m);
+          kf[a] = ltk[j * kTab + t];
+          rf[a] = ltr[j * kTab + t];
+        }
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          if (j0 + a >= je) continue;
+          K *= kf[a];
+          if (need_r) {
+            const double r = rf[a];
+            u = u + r + u * r;  // (1 + u)(1 + r) - 1
+            const int c = 1 + j0 + a;
+            if (c >= b0 && c < b1) emit(c, u);
+            if (need_q) {
+#pragma unroll
+              for (int i = 4 * q + 4; i >= 1; --i) e[i] += r * e[i - 1];
+            }
           }
         }
       }
@@ -124,8 +147,8 @@ __global__ void __launch_bounds__(kChunk) k_kernel_cols(NetArgs na, KernTab kt, 
     if (need_q) {
 #pragma unroll
       for (int j = 1; j <= SMAX; ++j) {
-        const int c = s + j;
-        if (j <= s && c >= c0 && c < c1) emit(c, e[j]);
+        const int c = bs + j;
+        if (j <= bs && c >= b0 && c < b1) emit(c, e[j]);
       }
     }
   }
@@ -158,14 +181,13 @@ __global__ void __launch_bounds__(kChunk) k_kernel_cols2(NetArgs na, KernTab kt,
     __syncthreads();
     for (int i = threadIdx.x; i < 2 * s; i += blockDim.x) {
       const int h = i / s, j = i - h * s;
-      const int64_t b = base + 256 * h;
-      const uint32_t* tj = na.xtab + (int64_t)j * na.nbytes * 256;
-      uint32_t v = 0;
-      for (int bb = 1; bb < na.nbytes; ++bb) v ^= tj[bb * 256 + (int)((b >> (8 * bb)) & 255)];
-      lu[h * s + j] = v;
+      lu[h * s + j] = upper_x(na.xtab, na.nbytes, j, base + 256 * h);
     }
     __syncthreads();
     const int64_t n = base + 2 * threadIdx.x;
+    int b0 = c0, b1 = c1, bs = s;  // opaque per group, as in k_kernel_cols
+    asm volatile("" : "+s"(b0), "+s"(b1), "+s"(bs));
+    double* o = out + n;
     double K0 = 1.0, K1 = 1.0, u0 = 0.0, u1 = 0.0;
     double e0[SMAX + 1], e1[SMAX + 1];
 #pragma unroll
@@ -184,11 +206,9 @@ __global__ void __launch_bounds__(kChunk) k_kernel_cols2(NetArgs na, KernTab kt,
           u0 = u0 + r0 + u0 * r0;
           u1 = u1 + r1 + u1 * r1;
           const int c = 1 + j;
-          if (c >= c0 && c < c1) {
-            double2 w;
-            w.x = u0;
-            w.y = u1;
-            *reinterpret_cast<double2*>(out + (int64_t)(c - c0) * N + n) = w;
+          if (c >= b0 && c < b1) {
+            *reinterpret_cast<double2*>(o) = make_double2(u0, u1);
+            o += N;
           }
           if (need_q) {
 #pragma unroll
@@ -200,21 +220,14 @@ __global__ void __launch_bounds__(kChunk) k_kernel_cols2(NetArgs na, KernTab kt,
         }
       }
     }
-    if (c0 == 0) {
-      double2 w;
-      w.x = K0;
-      w.y = K1;
-      *reinterpret_cast<double2*>(out + n) = w;
-    }
+    if (c0 == 0) *reinterpret_cast<double2*>(out + n) = make_double2(K0, K1);
     if (need_q) {
 #pragma unroll
       for (int j = 1; j <= SMAX; ++j) {
-        const int c = s + j;
-        if (j <= s && c >= c0 && c < c1) {
-          double2 w;
-          w.x = e0[j];
-          w.y = e1[j];
-          *reinterpret_cast<double2*>(out + (int64_t)(c - c0) * N + n) = w;
+        const int c = bs + j;
+        if (j <= bs && c >= b0 && c < b1) {
+          *reinterpret_cast<double2*>(o) = make_double2(e0[j], e1[j]);
+          o += N;
         }
       }
     }
@@ -653,7 +666,7 @@ static int kcols_launch(const Net& net, const KernTab& kt, int c0, int c1, doubl
                           FDWT_TC_KCOLS, 8.0 * (double)net.N * (c1 - c0));
     }
   }
-  const unsigned grid = (unsigned)std::min<int64_t>((net.N + kChunk - 1) / kChunk, 2048);
+  const unsigned grid = even_grid((net.N + kChunk - 1) / kChunk, 8192);
   return launch_timed((const void*)k_kernel_cols<P, SMAX>, dim3(grid), dim3(kChunk), args, lds, st, FDWT_TC_KCOLS,
                       8.0 * (double)net.N * (c1 - c0));
 }
