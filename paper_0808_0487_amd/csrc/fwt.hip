@@ -187,73 +187,45 @@ __global__ void __launch_bounds__((PassShape<P, KMAX, sizeof(T)>::THREADS))
 // -------------------------------------------- p = 2 passes, static shape
 // (tile geometry, register groups and stages: p2_stages.h)
 
-template <class Tin, class T, class Tout, int LOGE, int WDIG, int EPI>
-__global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS))
-    fwt_p2(const Tin* __restrict__ in, Tout* out, PassDesc d) {
+// One pass that stores its coefficients: a workgroup per tile, so that the
+// hardware overlaps one tile's arithmetic with its neighbours' loads and
+// stores.  The pass is bound by memory (or the last-level cache), and at one
+// tile a workgroup the kernel needs 36 registers (float), so LDS alone limits
+// it: two 2^14-element float tiles per CU.  A persistent form that prefetched
+// the next tile into registers had one (its 100 scalar registers allow 7 waves
+// a SIMD), loads and stores of the whole device in step.  Forward + inverse, a
+// workgroup per tile against that form (us): float m = 20 20.0 / 22.6, m = 21
+// 28.7 / 36.6, m = 22 33.6 / 36.9, m = 24 95.4 / 106.2, m = 25 256 / 296, m =
+// 26 550 / 583; double m = 20 31.0 / 33.1, m = 23 106 / 115, m = 24 225 / 232.
+template <class T, int LOGE, int WDIG>
+__global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS), (sizeof(T) == 4 ? 8 : 4))
+    fwt_p2(const T* __restrict__ in, T* out, PassDesc d) {
   using S = P2Shape<LOGE, WDIG>;
   constexpr int EPT = S::EPT, TH = S::THREADS;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* lds = reinterpret_cast<T*>(smem_raw);
-  const int G = gridDim.x;
-  const int nb = d.ntiles * d.batch;
-  const int hw = blockIdx.x;
-  int lb = d.xcd ? xcd_first(hw, G) : hw;
+  const int lb = d.xcd ? xcd_first(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const int col = lb / d.ntiles, tile = lb % d.ntiles;
+  const int64_t base = (int64_t)(tile % d.nlo) * S::W + (int64_t)(tile / d.nlo) * d.shi;
   const int tid = threadIdx.x;
-  // Element e = tid + k*TH of a tile: row i = e >> WDIG, column e & (W-1);
+  // Element e = tid + k*TH of the tile: row i = e >> WDIG, column e & (W-1);
   // global offset goff0 + k*gstep, LDS index pad(tid) + pad(k*TH).
   const uint32_t sd0 = (uint32_t)d.sd0;
   const uint32_t goff0 = (uint32_t)(tid & (S::W - 1)) + (uint32_t)(tid >> WDIG) * sd0;
   const uint32_t gstep = (uint32_t)(TH >> WDIG) * sd0;
+  const gptr<const T> src =
+      to_global((d.in_tab ? col_ptr<const T>(d.in_tab, col) : in + (int64_t)col * d.col_in) + base);
+  T v[EPT];
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) v[k] = src[goff0 + k * gstep];
   T* lrow = lds + cpad(tid);
-  auto locate = [&](int l, int& col, int& tile) {
-    if (EPI == EPI_REDUCE && d.wkeep) {
-      const int r = l / G;
-      col = r % d.batch;
-      tile = (r / d.batch) * G + l % G;
-    } else if (EPI == EPI_REDUCE) {
-      col = l % d.batch;
-      tile = l / d.batch;
-    } else {
-      col = l / d.ntiles;
-      tile = l % d.ntiles;
-    }
-  };
-  auto tile_base = [&](int tile) {
-    const int lo = tile % d.nlo;
-    const int hi = tile / d.nlo;
-    return (int64_t)lo * S::W + (int64_t)hi * d.shi;
-  };
-  Tin pre[EPT];
-  // Converts the prefetched elements into the tile registers.  The empty asm
-  // is a use of each register, so the wait for the prefetch sits here.  A
-  // pass takes the next tile before it stores the current one (or its
-  // partial sum): the prefetch is then the newest memory operation, and its
-  // wait covers at most the stores of the tile before, issued a whole tile
-  // earlier.  With the wait at the top of the loop instead, it also waited
-  // for the stores of the tile just finished.
-  auto take = [&](T (&v)[EPT]) {
-#pragma unroll
-    for (int k = 0; k < EPT; ++k) {
-      v[k] = cvt_in<Tin, T>(pre[k]);
-      asm volatile("" : "+v"(v[k]));
-    }
-  };
-  auto prefetch = [&](int l) {
-    int col, tile;
-    locate(l, col, tile);
-    const Tin* colp = d.in_tab ? col_ptr<const Tin>(d.in_tab, col) : in + (int64_t)col * d.col_in;
-    const gptr<const Tin> src = to_global(colp + tile_base(tile) + goff0);
-#pragma unroll
-    for (int k = 0; k < EPT; ++k) pre[k] = src[k * gstep];
-  };
-  if (lb < nb) prefetch(lb);
   if constexpr (LOGE >= 10) {
-    // Three stage groups per tile.  The 16 elements a thread loads (e = tid +
-    // k TH) differ in the top 4 bits of e: those stages run in registers
-    // before the tile goes to LDS.  The stages of bits [WDIG, 6) run through
-    // LDS.  The store mapping e = lane + 64 k + 1024 w (still coalesced) puts
-    // bits 6..9 in the register index: the remaining stages run in registers
-    // after reading the tile back.
+    // Three stage groups.  The 16 elements a thread loads (e = tid + k TH)
+    // differ in the top 4 bits of e: those stages run in registers before the
+    // tile goes to LDS.  The stages of bits [WDIG, 6) run through LDS.  The
+    // store mapping e = lane + 64 k + 1024 w (still coalesced) puts bits 6..9
+    // in the register index: the remaining stages run in registers after
+    // reading the tile back.
     constexpr int NS = (LOGE - 10) < 4 ? (LOGE - 10) : 4;
     constexpr int RDL = 6 - WDIG;
     // The wave index is uniform in a wave: read as a scalar, the addresses
@@ -261,10 +233,106 @@ __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS))
     const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t goffS = (uint32_t)(lane & (S::W - 1)) + (uint32_t)((lane >> WDIG) + (1024 >> WDIG) * wv) * sd0;
     const uint32_t gstepS = (uint32_t)(64 >> WDIG) * sd0;
-    T* lrowS = lds + cpad(lane + 1024 * wv);
-    T v[EPT];
+    const T* lrowS = lds + cpad(lane + 1024 * wv);
+    reg_bfly<4>(v);
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) lrow[cpad(k * TH)] = v[k];
+    lds_barrier();
+    P2Groups<LOGE, WDIG, 0, T, 4, RDL>::run(lds, tid);
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) v[k] = lrowS[66 * k];
+    reg_bfly<NS>(v);
+    if (WDIG == 0 && d.oblk) {
+      // Blocked layout: e = lane + 64 k + 1024 w has row e >> 4 and column e & 15.
+      const int64_t rs = d.oblk;
+      const gptr<T> dst = to_global(out + (int64_t)col * d.col_out + ((lane >> 4) + 64 * wv) * rs +
+                                    (int64_t)tile * 16 + (lane & 15));
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) dst[k * 4 * rs] = cvt_out<T, T>(v[k], d.scale, d.scale64);
+    } else {
+      const gptr<T> dst = to_global((d.out_tab ? col_ptr<T>(d.out_tab, col) : out + (int64_t)col * d.col_out) + base);
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) dst[goffS + k * gstepS] = cvt_out<T, T>(v[k], d.scale, d.scale64);
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) lrow[cpad(k * TH)] = v[k];
+    lds_barrier();
+    P2Groups<LOGE, WDIG, 0, T>::run(lds, tid);
+    const gptr<T> dst = to_global((d.out_tab ? col_ptr<T>(d.out_tab, col) : out + (int64_t)col * d.col_out) + base);
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) dst[goff0 + k * gstep] = cvt_out<T, T>(lrow[cpad(k * TH)], d.scale, d.scale64);
+  }
+}
+
+// Last pass of the variance columns (double): the grouped sums instead of a
+// store.  Persistent, with the next tile prefetched: with wkeep a workgroup
+// takes every column of one tile and keeps the tile's weights in registers.
+template <int LOGE, int WDIG>
+__global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS))
+    fwt_p2_sums(const double* __restrict__ in, PassDesc d) {
+  using S = P2Shape<LOGE, WDIG>;
+  constexpr int EPT = S::EPT, TH = S::THREADS;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double* lds = reinterpret_cast<double*>(smem_raw);
+  const int G = gridDim.x;
+  const int nb = d.ntiles * d.batch;
+  const int hw = blockIdx.x;
+  int lb = d.xcd ? xcd_first(hw, G) : hw;
+  const int tid = threadIdx.x;
+  const uint32_t sd0 = (uint32_t)d.sd0;
+  const uint32_t goff0 = (uint32_t)(tid & (S::W - 1)) + (uint32_t)(tid >> WDIG) * sd0;
+  const uint32_t gstep = (uint32_t)(TH >> WDIG) * sd0;
+  double* lrow = lds + cpad(tid);
+  auto locate = [&](int l, int& col, int& tile) {
+    if (d.wkeep) {
+      const int r = l / G;
+      col = r % d.batch;
+      tile = (r / d.batch) * G + l % G;
+    } else {
+      col = l % d.batch;
+      tile = l / d.batch;
+    }
+  };
+  auto tile_base = [&](int tile) {
+    const int lo = tile % d.nlo;
+    const int hi = tile / d.nlo;
+    return (int64_t)lo * S::W + (int64_t)hi * d.shi;
+  };
+  double pre[EPT];
+  // Moves the prefetched elements into the tile registers.  The empty asm is
+  // a use of each register, so the wait for the prefetch sits here: a pass
+  // takes the next tile before it stores the current one's partial sum.
+  auto take = [&](double (&v)[EPT]) {
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+      v[k] = pre[k];
+      asm volatile("" : "+v"(v[k]));
+    }
+  };
+  auto prefetch = [&](int l) {
+    int col, tile;
+    locate(l, col, tile);
+    // The scalar pointer runs along, its step opaque per tile: otherwise the
+    // 16 multiples stay in scalar registers across the loop (105 spilled).
+    const double* src = in + (int64_t)col * d.col_in + tile_base(tile);
+    uint32_t gs = gstep;
+    asm volatile("" : "+s"(gs));
+#pragma unroll
+    for (int k = 0; k < EPT; ++k, src += gs) pre[k] = to_global(src)[goff0];
+  };
+  if (lb < nb) prefetch(lb);
+  if constexpr (LOGE >= 10) {
+    // The stage groups and the store mapping of fwt_p2.
+    constexpr int NS = (LOGE - 10) < 4 ? (LOGE - 10) : 4;
+    constexpr int RDL = 6 - WDIG;
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t goffS = (uint32_t)(lane & (S::W - 1)) + (uint32_t)((lane >> WDIG) + (1024 >> WDIG) * wv) * sd0;
+    const uint32_t gstepS = (uint32_t)(64 >> WDIG) * sd0;
+    double* lrowS = lds + cpad(lane + 1024 * wv);
+    double v[EPT];
     if (lb < nb) take(v);
-    float2 wcur[EPI == EPI_REDUCE ? EPT : 1];  // the grouped-sum weights of the tile
+    float2 wcur[EPT];  // the weights of the tile
     for (; lb < nb; lb += G) {
       reg_bfly<4>(v);
 #pragma unroll
@@ -273,52 +341,37 @@ __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS))
       int col, tile;
       locate(lb, col, tile);
       const int64_t base = tile_base(tile);
-      if constexpr (EPI == EPI_REDUCE) {
-        if (!d.wkeep || col == 0) {  // with wkeep, column 0 starts a new tile
-          const float2* wt = d.wts + base + goffS;
+      if (!d.wkeep || col == 0) {  // with wkeep, column 0 starts a new tile
+        const float2* wt = d.wts + base;
+        uint32_t gs = gstepS;
+        asm volatile("" : "+s"(gs));
 #pragma unroll
-          for (int k = 0; k < EPT; ++k) wcur[k] = wt[k * gstepS];
-        }
+        for (int k = 0; k < EPT; ++k, wt += gs) wcur[k] = wt[goffS];
       }
       prefetch(lb + G < nb ? lb + G : lb);  // unconditional: exact wait counts
-      P2Groups<LOGE, WDIG, 0, T, (EPI == EPI_REDUCE && sizeof(T) >= 8) ? 2 : 4, RDL>::run(lds, tid);
-      T y[EPT];
+      // 2-digit register groups: with the weights and the next tile live they
+      // keep the kernel within 128 registers.
+      P2Groups<LOGE, WDIG, 0, double, 2, RDL>::run(lds, tid);
+      double y[EPT];
 #pragma unroll
       for (int k = 0; k < EPT; ++k) y[k] = lrowS[66 * k];
       reg_bfly<NS>(y);
-      if constexpr (EPI == EPI_STORE) {
-        take(v);  // the next tile (the last round takes its own tile again)
-        if (WDIG == 0 && d.oblk) {
-          // Blocked layout: e = lane + 64 k + 1024 w has row e >> 4 and column e & 15.
-          const int64_t rs = d.oblk;
-          const gptr<Tout> dst = to_global(out + (int64_t)col * d.col_out + ((lane >> 4) + 64 * wv) * rs +
-                                           (int64_t)tile * 16 + (lane & 15));
+      double acc = 0.0;
 #pragma unroll
-          for (int k = 0; k < EPT; ++k) dst[k * 4 * rs] = cvt_out<T, Tout>(y[k], d.scale, d.scale64);
-        } else {
-          const gptr<Tout> dst =
-              to_global((d.out_tab ? col_ptr<Tout>(d.out_tab, col) : out + (int64_t)col * d.col_out) + base + goffS);
-#pragma unroll
-          for (int k = 0; k < EPT; ++k) dst[k * gstepS] = cvt_out<T, Tout>(y[k], d.scale, d.scale64);
-        }
-      } else {
-        double acc = 0.0;
-#pragma unroll
-        for (int k = 0; k < EPT; ++k) {
-          const double rho = fmin(fmax(real_of(y[k]) * (double)wcur[k].y, 0.0), 1.0);
-          const double term = (double)wcur[k].x * rho;
-          acc += term;
-          if (col == d.h0_col && base + goffS + (int64_t)k * gstepS == 0) *d.h0_out = term;
-        }
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-        take(v);
-        if (lane == 0) d.partial[((int64_t)col * d.ntiles + tile) * (TH / 64) + wv] = acc;
+      for (int k = 0; k < EPT; ++k) {
+        const double rho = fmin(fmax(y[k] * (double)wcur[k].y, 0.0), 1.0);
+        const double term = (double)wcur[k].x * rho;
+        acc += term;
+        if (col == d.h0_col && base + goffS + (int64_t)k * gstepS == 0) *d.h0_out = term;
       }
+      for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+      take(v);
+      if (lane == 0) d.partial[((int64_t)col * d.ntiles + tile) * (TH / 64) + wv] = acc;
       lds_barrier();
     }
     return;
   }
-  T v[EPT];
+  double v[EPT];
   if (lb < nb) take(v);
   for (; lb < nb; lb += G) {
 #pragma unroll
@@ -327,40 +380,28 @@ __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS))
     int col, tile;
     locate(lb, col, tile);
     const int64_t base = tile_base(tile);
-    // Grouped-sum weights of this tile: loaded now, used after the butterflies.
-    float2 wcur[EPI == EPI_REDUCE ? EPT : 1];
-    if constexpr (EPI == EPI_REDUCE) {
-      const float2* wt = d.wts + base + goff0;
+    // The tile's weights: loaded now, used after the butterflies.
+    float2 wcur[EPT];
+    const float2* wt = d.wts + base + goff0;
 #pragma unroll
-      for (int k = 0; k < EPT; ++k) wcur[k] = wt[k * gstep];
-    }
+    for (int k = 0; k < EPT; ++k) wcur[k] = wt[k * gstep];
     // Unconditional (the last round re-reads its own block): with no branch
     // around the loads the compiler's wait counts stay exact, so waiting for
     // this tile's weights does not wait for the next tile's elements.
     prefetch(lb + G < nb ? lb + G : lb);
-    // The grouped-sum variant keeps this tile's weights live across the
-    // butterflies: 2-digit register groups keep it within 128 registers.
-    P2Groups<LOGE, WDIG, 0, T, (EPI == EPI_REDUCE && sizeof(T) >= 8) ? 2 : 4>::run(lds, tid);
-    if constexpr (EPI == EPI_STORE) {
-      take(v);
-      const gptr<Tout> dst =
-          to_global((d.out_tab ? col_ptr<Tout>(d.out_tab, col) : out + (int64_t)col * d.col_out) + base + goff0);
+    P2Groups<LOGE, WDIG, 0, double, 2>::run(lds, tid);
+    double acc = 0.0;
 #pragma unroll
-      for (int k = 0; k < EPT; ++k) dst[k * gstep] = cvt_out<T, Tout>(lrow[cpad(k * TH)], d.scale, d.scale64);
-    } else {
-      double acc = 0.0;
-#pragma unroll
-      for (int k = 0; k < EPT; ++k) {
-        const float2 w2 = wcur[k];
-        const double rho = fmin(fmax(real_of(lrow[cpad(k * TH)]) * (double)w2.y, 0.0), 1.0);
-        const double term = (double)w2.x * rho;
-        acc += term;
-        if (col == d.h0_col && base + goff0 + (int64_t)k * gstep == 0) *d.h0_out = term;
-      }
-      for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-      take(v);
-      if ((tid & 63) == 0) d.partial[((int64_t)col * d.ntiles + tile) * (TH / 64) + (tid >> 6)] = acc;
+    for (int k = 0; k < EPT; ++k) {
+      const float2 w2 = wcur[k];
+      const double rho = fmin(fmax(lrow[cpad(k * TH)] * (double)w2.y, 0.0), 1.0);
+      const double term = (double)w2.x * rho;
+      acc += term;
+      if (col == d.h0_col && base + goff0 + (int64_t)k * gstep == 0) *d.h0_out = term;
     }
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    take(v);
+    if ((tid & 63) == 0) d.partial[((int64_t)col * d.ntiles + tile) * (TH / 64) + (tid >> 6)] = acc;
     lds_barrier();
   }
 }
@@ -873,17 +914,32 @@ static std::vector<P2Pass> plan_p2(int m, size_t bytes) {
 // a plan fixes; many columns fill the device with any tile.
 static std::vector<P2Pass> plan_p2_cols(int m) { return plan_p2_e(m, lds_budget(8) < 136 * 1024 ? 13 : 14, 8); }
 
-template <class Tin, class T, class Tout, int WDIG, int EPI>
-static const void* p2_kernel(int loge) {
+template <class T, int WDIG>
+static const void* p2_store_kernel(int loge) {
   switch (loge) {
-    case 7: return (const void*)fwt_p2<Tin, T, Tout, 7, WDIG, EPI>;
-    case 8: return (const void*)fwt_p2<Tin, T, Tout, 8, WDIG, EPI>;
-    case 9: return (const void*)fwt_p2<Tin, T, Tout, 9, WDIG, EPI>;
-    case 10: return (const void*)fwt_p2<Tin, T, Tout, 10, WDIG, EPI>;
-    case 11: return (const void*)fwt_p2<Tin, T, Tout, 11, WDIG, EPI>;
-    case 12: return (const void*)fwt_p2<Tin, T, Tout, 12, WDIG, EPI>;
-    case 13: return (const void*)fwt_p2<Tin, T, Tout, 13, WDIG, EPI>;
-    case 14: return (const void*)fwt_p2<Tin, T, Tout, 14, WDIG, EPI>;
+    case 7: return (const void*)fwt_p2<T, 7, WDIG>;
+    case 8: return (const void*)fwt_p2<T, 8, WDIG>;
+    case 9: return (const void*)fwt_p2<T, 9, WDIG>;
+    case 10: return (const void*)fwt_p2<T, 10, WDIG>;
+    case 11: return (const void*)fwt_p2<T, 11, WDIG>;
+    case 12: return (const void*)fwt_p2<T, 12, WDIG>;
+    case 13: return (const void*)fwt_p2<T, 13, WDIG>;
+    case 14: return (const void*)fwt_p2<T, 14, WDIG>;
+  }
+  return nullptr;
+}
+
+template <int WDIG>
+static const void* p2_sums_kernel(int loge) {
+  switch (loge) {
+    case 7: return (const void*)fwt_p2_sums<7, WDIG>;
+    case 8: return (const void*)fwt_p2_sums<8, WDIG>;
+    case 9: return (const void*)fwt_p2_sums<9, WDIG>;
+    case 10: return (const void*)fwt_p2_sums<10, WDIG>;
+    case 11: return (const void*)fwt_p2_sums<11, WDIG>;
+    case 12: return (const void*)fwt_p2_sums<12, WDIG>;
+    case 13: return (const void*)fwt_p2_sums<13, WDIG>;
+    case 14: return (const void*)fwt_p2_sums<14, WDIG>;
   }
   return nullptr;
 }
@@ -917,23 +973,22 @@ static bool wkeep_enabled() {
   return !(e && atoi(e) == 0);
 }
 
-template <class Tin, class T, class Tout>
-
 // layout: 0 natural; 1 the (contiguous first) pass stores in the blocked
 // layout of PassDesc::oblk; 2 the (strided) pass reads and writes that
 // blocked layout, where each of its tiles is one contiguous block.
+template <class T>
 static int launch_p2(const void* in, void* out, const P2Pass& g, int m, int batch, double scale,
                      const ReduceArgs* red, hipStream_t st, const void* const* in_tab = nullptr,
                      void* const* out_tab = nullptr, int layout = 0) {
   constexpr bool wide = sizeof(T) >= 8;
   const void* fn = nullptr;
   if (red) {
-    if constexpr (wide) fn = g.wdig ? p2_kernel<Tin, T, Tout, 4, EPI_REDUCE>(g.loge) : p2_kernel<Tin, T, Tout, 0, EPI_REDUCE>(g.loge);
+    if constexpr (wide) fn = g.wdig ? p2_sums_kernel<4>(g.loge) : p2_sums_kernel<0>(g.loge);
   } else {
     if (g.wdig == 5) {
-      if constexpr (!wide) fn = p2_kernel<Tin, T, Tout, 5, EPI_STORE>(g.loge);
+      if constexpr (!wide) fn = p2_store_kernel<T, 5>(g.loge);
     } else {
-      fn = g.wdig ? p2_kernel<Tin, T, Tout, 4, EPI_STORE>(g.loge) : p2_kernel<Tin, T, Tout, 0, EPI_STORE>(g.loge);
+      fn = g.wdig ? p2_store_kernel<T, 4>(g.loge) : p2_store_kernel<T, 0>(g.loge);
     }
   }
   if (!fn || (g.wdig != 0 && g.wdig != 4 && g.wdig != 5)) return fail(FDWT_EINVAL, "no static pass shape");
@@ -978,24 +1033,31 @@ static int launch_p2(const void* in, void* out, const P2Pass& g, int m, int batc
   }
   const size_t lds = ((size_t)cpad(E) * sizeof(T) + 15) / 16 * 16;
   if (int rc = allow_lds(fn, lds)) return rc;
-  int64_t G = (int64_t)occupancy(fn, threads, lds) * device_cus();
-  if (G >= nb) G = nb;
-  d.xcd = G >= 64 ? 1 : 0;
+  int64_t G = nb;
+  if (red) G = std::min(nb, (int64_t)occupancy(fn, threads, lds) * device_cus());
+  // Neighbouring tiles of a strided pass share 128-byte lines when its rows
+  // are shorter: they go to one XCD.  Rows of whole lines do better on the
+  // order of dispatch (float m = 21 28.7 against 31.3 us a pair, m = 23 49.7
+  // against 54.6; with short rows, m = 24, 120 against 95), contiguous tiles
+  // on one XCD (m = 24 95 against 97).
+  const bool lines = !red && g.wdig && layout == 0 && ((size_t)sizeof(T) << g.wdig) >= 128;
+  d.xcd = G >= 64 && !lines ? 1 : 0;
   // Grouped sums over several columns: a workgroup keeps one tile's weights
   // for all its columns when the tiles split evenly over the grid.
   d.wkeep = (red && g.loge >= 10 && batch > 1 && ntiles % G == 0 && wkeep_enabled()) ? 1 : 0;
   void* args[] = {(void*)&in, (void*)&out, (void*)&d};
+  void* sargs[] = {(void*)&in, (void*)&d};
   const double elems = (double)N * batch;
-  const double work = red ? elems * sizeof(Tin) + (double)N * sizeof(float2) : elems * (sizeof(Tin) + sizeof(Tout));
-  return launch_timed(fn, dim3((unsigned)G), dim3(threads), args, lds, st, wide ? FDWT_TC_PASS_F64 : FDWT_TC_PASS_F32,
+  const double work = red ? elems * sizeof(T) + (double)N * sizeof(float2) : elems * 2 * sizeof(T);
+  return launch_timed(fn, dim3((unsigned)G), dim3(threads), red ? sargs : args, lds, st, wide ? FDWT_TC_PASS_F64 : FDWT_TC_PASS_F32,
                       work);
 }
 
 static int p2_pass(Kind k, const void* in, void* out, const P2Pass& g, int m, int batch, double scale,
                    const ReduceArgs* red, hipStream_t st, int layout = 0) {
-  if (k == K_F32 && !red) return launch_p2<float, float, float>(in, out, g, m, batch, scale, nullptr, st);
-  if (k == K_U32 && !red) return launch_p2<uint32_t, uint32_t, uint32_t>(in, out, g, m, batch, scale, nullptr, st);
-  if (k == K_F64) return launch_p2<double, double, double>(in, out, g, m, batch, scale, red, st, nullptr, nullptr, layout);
+  if (k == K_F32 && !red) return launch_p2<float>(in, out, g, m, batch, scale, nullptr, st);
+  if (k == K_U32 && !red) return launch_p2<uint32_t>(in, out, g, m, batch, scale, nullptr, st);
+  if (k == K_F64) return launch_p2<double>(in, out, g, m, batch, scale, red, st, nullptr, nullptr, layout);
   return fail(FDWT_EINVAL, "unsupported p = 2 element type");
 }
 
@@ -1100,7 +1162,7 @@ int fwt_p2_group_pass(int m, int emax, int level, const void* const* in_tab, voi
   const bool last = level + 1 == (int)passes.size();
   const double scale = last ? std::ldexp(1.0, -m) : 1.0;
   const void* const* src = level == 0 ? in_tab : (const void* const*)out_tab;
-  return launch_p2<float, float, float>(nullptr, nullptr, passes[level], m, njobs, scale, nullptr, st, src, out_tab);
+  return launch_p2<float>(nullptr, nullptr, passes[level], m, njobs, scale, nullptr, st, src, out_tab);
 }
 
 // The p = 2 float64 transform of a batch of columns split after its first
