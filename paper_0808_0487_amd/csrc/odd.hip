@@ -75,14 +75,128 @@ struct OddGroups<P, LE, RD, KT, Q, INV, T, true> {
   static __device__ __forceinline__ void run(T*, int) {}
 };
 
-// EPI_REDUCE (complex double): the grouped sums of a pair of real columns
-// carried as one complex column (OddReduce below).
+// The KT top digits of a pass that come first, on the values as loaded.
+template <int P, int LE, int RD, int KT, class T>
+struct OddOrder {
+  static constexpr bool top_first = RD == KT || (P == 3 && LE == 8 && std::is_same<T, float2>::value);
+};
+
+// A tile's values from the loaded ones: the stages of the pass.  `between`
+// runs after the tile went to LDS (the wide tiles' prefetch).
+template <int P, int LE, int RD, int KT, bool INV, class T, int N, class F>
+__device__ __forceinline__ void odd_tile(T (&v)[N], T* lds, int tid, F between) {
+  using S = OddShape<P, LE, RD, KT>;
+  constexpr bool TOP_FIRST = OddOrder<P, LE, RD, KT, T>::top_first;
+  if constexpr (TOP_FIRST) dft_digits<P, KT, INV>(v);
+  if constexpr (RD > KT) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) lds[tid + k * S::TH] = v[k];
+    lds_barrier();
+    between();
+    OddGroups<P, LE, RD, KT, 0, INV, T>::run(lds, tid);
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = lds[tid + k * S::TH];
+  }
+  if constexpr (!TOP_FIRST) dft_digits<P, KT, INV>(v);
+}
+
+// Grouped sums of a tile (complex double: a pair of real columns carried as
+// one complex column, the imaginary one scaled by 2^pexp): the terms of the
+// thread's values, then the threads' sums in a fixed order.
+template <int TH, int N>
+__device__ __forceinline__ void odd_sums(const double2 (&v)[N], double2* red, const PassDesc& d, int col, int tile,
+                                         int64_t base, uint32_t gstep, int tid) {
+  const double us = ldexp(1.0, -d.pexp[col]);
+  double2 acc = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const float2 wt = d.wts[base + (int64_t)k * gstep];
+    const double2 y = v[k];
+    const double ra = fmin(fmax(y.x * (double)wt.y, 0.0), 1.0);
+    const double rb = fmin(fmax(y.y * us * (double)wt.y, 0.0), 1.0);
+    const double ta = (double)wt.x * ra, tb = (double)wt.x * rb;
+    acc.x += ta;
+    acc.y += tb;
+    if (base + (int64_t)k * gstep == 0) {
+      if (2 * col == d.h0_col) *d.h0_out = ta;
+      if (2 * col + 1 == d.h0_col) *d.h0_out = tb;
+    }
+  }
+  lds_barrier();
+  red[tid] = acc;
+  lds_barrier();
+  if (tid < 64) {
+    double2 t = red[tid];
+    for (int i = tid + 64; i < TH; i += 64) t = add(t, red[i]);
+    if constexpr (TH >= 64) {
+      for (int off = 32; off > 0; off >>= 1) {
+        t.x += __shfl_xor(t.x, off);
+        t.y += __shfl_xor(t.y, off);
+      }
+    } else if (tid == 0) {
+      for (int i = 1; i < TH; ++i) t = add(t, red[i]);
+    }
+    if (tid == 0) {
+      d.partial[(int64_t)(2 * col) * d.ntiles + tile] = t.x;
+      if (2 * col + 1 < d.ncols) d.partial[(int64_t)(2 * col + 1) * d.ntiles + tile] = t.y;
+    }
+  }
+}
+
+template <int W>
+__device__ __forceinline__ int64_t odd_base(const PassDesc& d, int tile) {
+  return (int64_t)(tile % d.nlo) * W + (int64_t)(tile / d.nlo) * d.shi;
+}
+
+// A tile that leaves room for a second one on its CU: a workgroup per tile,
+// so that the hardware overlaps one tile's arithmetic with the others' loads
+// and stores; bound by memory.  Forward + inverse against the persistent form
+// below (us): p = 3 float 3^13 35.4 / 37.6, 3^14 59.9 / 63.6, 3^15 210 / 245,
+// double 3^15 422 / 459; p = 5 double 5^10 302 / 326; p = 7 float 7^8
+// 102.6 / 106.5, double 7^8 172 / 206.
 template <int P, int LE, int RD, int KT, bool INV, class Tin, class T, class Tout, int EPI>
 __global__ void __launch_bounds__((OddShape<P, LE, RD, KT>::TH))
     fwt_odd(const Tin* __restrict__ in, Tout* out, PassDesc d) {
   using S = OddShape<P, LE, RD, KT>;
-  constexpr int TH = S::TH, EPT = S::EPT;
-  constexpr bool TOP_FIRST = RD == KT || (P == 3 && LE == 8 && std::is_same<T, float2>::value);
+  constexpr int EPT = S::EPT;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T* lds = reinterpret_cast<T*>(smem_raw);
+  const int lb = d.xcd ? xcd_first(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  // Sums: neighbours share a tile's weights.
+  const int col = EPI == EPI_REDUCE ? lb % d.batch : lb / d.ntiles;
+  const int tile = EPI == EPI_REDUCE ? lb / d.batch : lb % d.ntiles;
+  const int tid = threadIdx.x;
+  // Global offset of element tid + k TH: goff0 + k gstep.
+  const uint32_t sd0 = (uint32_t)d.sd0;
+  const uint32_t goff0 = (uint32_t)(tid % S::W) + (uint32_t)(tid / S::W) * sd0;
+  const uint32_t gstep = (uint32_t)S::RSTEP * sd0;
+  const int64_t base = odd_base<S::W>(d, tile);
+  const Tin* src = in + (int64_t)col * d.col_in + base;
+  Tin pre[EPT];
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) pre[k] = src[goff0 + k * gstep];
+  T v[EPT];
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) v[k] = cvt_in<Tin, T>(pre[k]);
+  odd_tile<P, LE, RD, KT, INV>(v, lds, tid, [] {});
+  if constexpr (EPI == EPI_STORE) {
+    Tout* dst = out + (int64_t)col * d.col_out + base;
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) dst[goff0 + k * gstep] = cvt_out<T, Tout>(v[k], d.scale, d.scale64);
+  } else {
+    odd_sums<S::TH>(v, reinterpret_cast<double2*>(smem_raw), d, col, tile, base + goff0, gstep, tid);
+  }
+}
+
+// A tile that takes its CU alone (3^8 elements in double, 5^6 in float):
+// persistent workgroups, the next tile prefetched into registers while this
+// one goes through LDS (a workgroup per tile: p = 5 float 5^10 152 against
+// 140 us a pair, 5^11 945 against 846; p = 3 double 3^14 131 against 114).
+template <int P, int LE, int RD, int KT, bool INV, class Tin, class T, class Tout, int EPI>
+__global__ void __launch_bounds__((OddShape<P, LE, RD, KT>::TH))
+    fwt_odd_wide(const Tin* __restrict__ in, Tout* out, PassDesc d) {
+  using S = OddShape<P, LE, RD, KT>;
+  constexpr int EPT = S::EPT;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* lds = reinterpret_cast<T*>(smem_raw);
   const int G = gridDim.x;
@@ -90,23 +204,12 @@ __global__ void __launch_bounds__((OddShape<P, LE, RD, KT>::TH))
   const int hw = blockIdx.x;
   int lb = d.xcd ? xcd_first(hw, G) : hw;
   const int tid = threadIdx.x;
-  // Global offset of element tid + k TH: goff0 + k gstep.
   const uint32_t sd0 = (uint32_t)d.sd0;
   const uint32_t goff0 = (uint32_t)(tid % S::W) + (uint32_t)(tid / S::W) * sd0;
   const uint32_t gstep = (uint32_t)S::RSTEP * sd0;
   auto locate = [&](int l, int& col, int& tile) {
-    if (EPI == EPI_REDUCE) {  // neighbours share a tile's weights
-      col = l % d.batch;
-      tile = l / d.batch;
-    } else {
-      col = l / d.ntiles;
-      tile = l % d.ntiles;
-    }
-  };
-  auto tile_base = [&](int tile) {
-    const int lo = tile % d.nlo;
-    const int hi = tile / d.nlo;
-    return (int64_t)lo * S::W + (int64_t)hi * d.shi;
+    col = EPI == EPI_REDUCE ? l % d.batch : l / d.ntiles;
+    tile = EPI == EPI_REDUCE ? l / d.batch : l % d.ntiles;
   };
   Tin pre[EPT];
   // live false: every load reads the tile's first element (one cache line), a
@@ -114,7 +217,7 @@ __global__ void __launch_bounds__((OddShape<P, LE, RD, KT>::TH))
   auto prefetch = [&](int l, bool live) {
     int col, tile;
     locate(l, col, tile);
-    const Tin* src = in + (int64_t)col * d.col_in + tile_base(tile) + (live ? goff0 : 0u);
+    const Tin* src = in + (int64_t)col * d.col_in + odd_base<S::W>(d, tile) + (live ? goff0 : 0u);
     const uint32_t st = live ? gstep : 0u;
 #pragma unroll
     for (int k = 0; k < EPT; ++k) pre[k] = src[k * st];
@@ -124,67 +227,20 @@ __global__ void __launch_bounds__((OddShape<P, LE, RD, KT>::TH))
     T v[EPT];
 #pragma unroll
     for (int k = 0; k < EPT; ++k) v[k] = cvt_in<Tin, T>(pre[k]);
-    if constexpr (TOP_FIRST) dft_digits<P, KT, INV>(v);  // the KT top digits of the pass
     int col, tile;
     locate(lb, col, tile);
-    const int64_t base = tile_base(tile) + goff0;
-    if constexpr (RD > KT) {
-#pragma unroll
-      for (int k = 0; k < EPT; ++k) lds[tid + k * TH] = v[k];
-      lds_barrier();
-    }
-    prefetch(lb + G < nb ? lb + G : lb, lb + G < nb);  // unconditional: exact wait counts
-    OddGroups<P, LE, RD, KT, 0, INV, T>::run(lds, tid);
-    if constexpr (RD > KT) {
-#pragma unroll
-      for (int k = 0; k < EPT; ++k) v[k] = lds[tid + k * TH];
-    }
-    if constexpr (!TOP_FIRST) dft_digits<P, KT, INV>(v);
+    const int64_t base = odd_base<S::W>(d, tile) + goff0;
+    odd_tile<P, LE, RD, KT, INV>(v, lds, tid, [&] {
+      prefetch(lb + G < nb ? lb + G : lb, lb + G < nb);  // unconditional: exact wait counts
+    });
     if constexpr (EPI == EPI_STORE) {
       Tout* dst = out + (int64_t)col * d.col_out + base;
 #pragma unroll
       for (int k = 0; k < EPT; ++k) dst[k * gstep] = cvt_out<T, Tout>(v[k], d.scale, d.scale64);
-      if constexpr (RD > KT) lds_barrier();
     } else {
-      const double us = ldexp(1.0, -d.pexp[col]);
-      double2 acc = make_double2(0.0, 0.0);
-#pragma unroll
-      for (int k = 0; k < EPT; ++k) {
-        const float2 wt = d.wts[base + (int64_t)k * gstep];
-        const T y = v[k];
-        const double ra = fmin(fmax(y.x * (double)wt.y, 0.0), 1.0);
-        const double rb = fmin(fmax(y.y * us * (double)wt.y, 0.0), 1.0);
-        const double ta = (double)wt.x * ra, tb = (double)wt.x * rb;
-        acc.x += ta;
-        acc.y += tb;
-        if (base + (int64_t)k * gstep == 0) {
-          if (2 * col == d.h0_col) *d.h0_out = ta;
-          if (2 * col + 1 == d.h0_col) *d.h0_out = tb;
-        }
-      }
-      // The threads' sums in a fixed order.
-      double2* red = reinterpret_cast<double2*>(smem_raw);
-      lds_barrier();
-      red[tid] = acc;
-      lds_barrier();
-      if (tid < 64) {
-        double2 t = red[tid];
-        for (int i = tid + 64; i < TH; i += 64) t = add(t, red[i]);
-        if constexpr (TH >= 64) {
-          for (int off = 32; off > 0; off >>= 1) {
-            t.x += __shfl_xor(t.x, off);
-            t.y += __shfl_xor(t.y, off);
-          }
-        } else if (tid == 0) {
-          for (int i = 1; i < TH; ++i) t = add(t, red[i]);
-        }
-        if (tid == 0) {
-          d.partial[(int64_t)(2 * col) * d.ntiles + tile] = t.x;
-          if (2 * col + 1 < d.ncols) d.partial[(int64_t)(2 * col + 1) * d.ntiles + tile] = t.y;
-        }
-      }
-      lds_barrier();
+      odd_sums<S::TH>(v, reinterpret_cast<double2*>(smem_raw), d, col, tile, base, gstep, tid);
     }
+    lds_barrier();
   }
 }
 
@@ -201,15 +257,16 @@ std::vector<PassGeom> odd_plan(int p, int m, Kind work) {
   };
   const bool f64 = work == K_CF64;
   // The largest net of one tile, and the exponent of every tile beyond it.
-  // Forward + inverse pairs, this choice against the generic passes before it
-  // (us): p = 3 double m = 9 20 / 30, m = 12 33 / 46, m = 14 111 / 153; p = 5
-  // float m = 8 26 / 55, m = 10 142 / 226, m = 11 845 / 1268 (5^5-element
-  // tiles and three passes: 1047); p = 5 double m = 10 309 / 519; p = 7 float
-  // m = 5 20 / 23 (one tile: 34), m = 8 104 / 154 (two passes of 7^5: 149),
-  // m = 9 846 / 1118 (7^4 and three passes: 921); double m = 8 200 / 250.
-  // (p = 3 float, 3^9..3^11 points: tiles of 3^8 elements, 17-20 us against
-  // 17 us with 3^7: their top-digits-first order is that of the larger nets,
-  // and float64 variances are computed from these float coefficients.)
+  // Forward + inverse pairs, this choice (us) against the generic passes
+  // before it, and against the next tile: p = 3 double m = 9 20 / 30, m = 12
+  // 33 / 46, m = 14 114 / 153 (3^7 and three passes: 139); p = 3 float m = 14
+  // 60 (3^7: 81); p = 5 float m = 8 25 / 55, m = 10 140 / 226 (5^5 and three
+  // passes: 154), m = 11 846 / 1268 (5^5: 932); p = 5 double m = 10 302 / 519;
+  // p = 7 float m = 5 20 / 23, m = 8 103 / 154, m = 9 802 / 1118 (two passes
+  // of 7^5, a CU each: 818); double m = 8 172 / 250.
+  // (p = 3 float, 3^9..3^11 points: tiles of 3^8 elements, their
+  // top-digits-first order is that of the larger nets, and float64 variances
+  // are computed from these float coefficients.)
   int single, le;
   if (p == 3) {
     single = 8;
@@ -219,7 +276,7 @@ std::vector<PassGeom> odd_plan(int p, int m, Kind work) {
     le = f64 ? (m <= 6 ? 4 : 5) : (m <= 9 ? 5 : 6);
   } else {
     single = 4;
-    le = m <= 5 ? 3 : (f64 || m <= 8 ? 4 : 5);
+    le = m <= 5 ? 3 : 4;
   }
   if (m <= single) {
     first(m);
@@ -245,7 +302,10 @@ template <int P, int LE, int RD, int KT, bool INV, class Tin, class T, class Tou
 static int launch_odd(const void* in, void* out, const PassGeom& g, int m, int batch, double scale,
                       const ReduceArgs* red, hipStream_t st) {
   using S = OddShape<P, LE, RD, KT>;
-  const void* fn = (const void*)fwt_odd<P, LE, RD, KT, INV, Tin, T, Tout, EPI>;
+  constexpr bool wide = RD > KT && 2 * S::E * sizeof(T) > 160 * 1024;  // one tile per CU
+  const void* fn;
+  if constexpr (wide) fn = (const void*)fwt_odd_wide<P, LE, RD, KT, INV, Tin, T, Tout, EPI>;
+  else fn = (const void*)fwt_odd<P, LE, RD, KT, INV, Tin, T, Tout, EPI>;
   const int64_t N = ipow(P, m);
   PassDesc d{};
   d.col_in = N;
@@ -274,8 +334,7 @@ static int launch_odd(const void* in, void* out, const PassGeom& g, int m, int b
   }
   const size_t lds = std::max<size_t>(RD > KT ? (size_t)S::E * sizeof(T) : 0, EPI == EPI_REDUCE ? S::TH * sizeof(double2) : 0);
   if (int rc = allow_lds(fn, lds)) return rc;
-  int64_t G = (int64_t)occupancy(fn, S::TH, lds) * device_cus();
-  if (G >= nb) G = nb;
+  const int64_t G = wide ? std::min(nb, (int64_t)occupancy(fn, S::TH, lds) * device_cus()) : nb;
   d.xcd = G >= 64 ? 1 : 0;
   const Tin* inp = (const Tin*)in;
   Tout* outp = (Tout*)out;
@@ -376,10 +435,6 @@ static int odd_shape(bool inv, bool in_real, bool out_real, const void* in, void
     FDWT_ODD(3, 2);
     FDWT_ODD(4, 2);
     FDWT_ODD(4, 3);
-    if constexpr (!D) {
-      FDWT_ODD(5, 5);
-      FDWT_ODD(5, 4);
-    }
   }
 #undef FDWT_ODD
 #undef FDWT_ODD_KT
