@@ -25,6 +25,7 @@
 #include "dev_math.h"
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -1129,6 +1130,33 @@ static size_t effdim_budget() {
   return b;
 }
 
+// Results a call waits for: n doubles in pinned memory, each stored once by the
+// call's last kernel.  They are set to a signalling NaN before that kernel is
+// launched (no arithmetic gives one: it would be quiet) and the host reads
+// them until all are replaced.  A wait through the stream returns well after
+// the kernel has ended (per call, such a wait against this one: a p = 2 step at
+// 2^10 points 70 to 82 / 64 us, eff_dim at 3^12, s = 10 99 / 95 us).
+// After kSpinUs, or where the kernel does not run (an error, a stream under
+// capture), the wait goes through the stream, which reports it.
+static constexpr uint64_t kPending = 0x7ff4504e44494e47ull;
+static constexpr int kSpinUs = 300;
+
+static void arm_results(double* r, int n) {
+  for (int i = 0; i < n; ++i) __atomic_store_n((uint64_t*)r + i, kPending, __ATOMIC_RELEASE);
+}
+
+static int wait_results(const double* r, int n, hipStream_t st) {
+  const auto end = std::chrono::steady_clock::now() + std::chrono::microseconds(kSpinUs);
+  int i = 0;
+  do {
+    for (int k = 0; k < 64 && i < n; ++k)
+      if (__atomic_load_n((const uint64_t*)r + i, __ATOMIC_ACQUIRE) != kPending) ++i;
+    if (i == n) return FDWT_OK;
+  } while (std::chrono::steady_clock::now() < end);
+  FDWT_HIP(hipStreamSynchronize(st));
+  return FDWT_OK;
+}
+
 int run_eff_dim(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* ft, fdwt_effdim* out, hipStream_t st) {
   const int ch = eff_dim_chunk(net, effdim_budget());
   const void* gk = nullptr;
@@ -1136,9 +1164,12 @@ int run_eff_dim(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* ft, 
   if (rc) return rc;
   rc = cached_spectrum(net, kern, &gk, st);
   if (rc) return rc;
+  const int n = 2 * net.s + 2;
+  arm_results(net.res_host, n);
+  net.res_host[2 * net.s - 1] = 0.0;  // not written
   rc = eff_dim_enqueue(net, sc, kern, gk, ft, ch, net.res_host, st);
   if (rc) return rc;
-  FDWT_HIP(hipStreamSynchronize(st));
+  if ((rc = wait_results(net.res_host, n, st))) return rc;
   eff_dim_finish(net.s, net.res_host, out);
   return FDWT_OK;
 }
@@ -1187,8 +1218,10 @@ int run_split_cost(Net& tr, Scratch& sc, const uint32_t* delta, const float* ft,
   KernTab kt = kern_tab(2, m2, kern);
   std::memcpy(kt.ix, delta, (size_t)s * 4);
   if (fwt_p2_split_tile_ok(tr.m)) {
+    arm_results(tr.res_host, 1);
     if ((rc = fwt_p2_split_tile(tr, kt, ft, fval, gk, sf_out, tr.res_host, st))) return rc;
-    FDWT_HIP(hipStreamSynchronize(st));
+    if (sf_out) FDWT_HIP(hipStreamSynchronize(st));  // the kernel's other output
+    else if ((rc = wait_results(tr.res_host, 1, st))) return rc;
     *cost = tr.res_host[0];
     return FDWT_OK;
   }
