@@ -227,7 +227,6 @@ __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS), (sizeof(T) == 
     // in the register index: the remaining stages run in registers after
     // reading the tile back.
     constexpr int NS = (LOGE - 10) < 4 ? (LOGE - 10) : 4;
-    constexpr int RDL = 6 - WDIG;
     // The wave index is uniform in a wave: read as a scalar, the addresses
     // derived from it stay in scalar registers.
     const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -238,7 +237,8 @@ __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS), (sizeof(T) == 
 #pragma unroll
     for (int k = 0; k < EPT; ++k) lrow[cpad(k * TH)] = v[k];
     lds_barrier();
-    P2Groups<LOGE, WDIG, 0, T, 4, RDL>::run(lds, tid);
+    if constexpr (WDIG == 0) p2_low6<LOGE>(lds, tid);
+    else P2Groups<LOGE, WDIG, 0, T, 4, 6 - WDIG>::run(lds, tid);
 #pragma unroll
     for (int k = 0; k < EPT; ++k) v[k] = lrowS[66 * k];
     reg_bfly<NS>(v);
@@ -464,7 +464,7 @@ __global__ void __launch_bounds__((P2Shape<LOGE, 0>::THREADS)) fwt_p2_gen(ColGen
 #pragma unroll
     for (int k = 0; k < EPT; ++k) lrow[cpad(k * TH)] = v[k];
     lds_barrier();
-    P2Groups<LOGE, 0, 0, double, 4, 6>::run(lds, tid);
+    p2_low6<LOGE>(lds, tid);
 #pragma unroll
     for (int k = 0; k < EPT; ++k) v[k] = lrowS[66 * k];
     reg_bfly<NS>(v);
@@ -585,7 +585,7 @@ __global__ void __launch_bounds__((P2Shape<LOGE, 0>::THREADS)) fwt_p2_split(Spli
 #pragma unroll
     for (int k = 0; k < EPT; ++k) lrow[cpad(k * TH)] = v[k];
     lds_barrier();
-    P2Groups<LOGE, 0, 0, double, 4, 6>::run(lds, tid);
+    p2_low6<LOGE>(lds, tid);
 #pragma unroll
     for (int k = 0; k < EPT; ++k) v[k] = lrowS[66 * k];
     reg_bfly<NS>(v);
@@ -689,7 +689,7 @@ __global__ void __launch_bounds__((P2Shape<LOGE, 0>::THREADS)) fwt_p2_fam(FamGen
 #pragma unroll
     for (int k = 0; k < EPT; ++k) lrow[cpad(k * TH)] = v[k];
     lds_barrier();
-    P2Groups<LOGE, 0, 0, float, 4, 6>::run(lds, tid);
+    p2_low6<LOGE>(lds, tid);
     float y[EPT];
 #pragma unroll
     for (int k = 0; k < EPT; ++k) y[k] = lrowS[66 * k];

@@ -4,6 +4,8 @@
 
 #include "pass_core.h"
 
+#include <type_traits>
+
 namespace fdwt {
 
 // -------------------------------------------- p = 2 passes, static shape
@@ -104,6 +106,57 @@ __device__ __forceinline__ void reg_bfly_bits(T (&v)[N]) {
       }
     }
   }
+}
+
+// The value of the lane whose index differs in bit B (0 or 1): a move inside
+// the four lanes of a quad.
+template <int B>
+__device__ __forceinline__ int quad_other(int v) {
+  constexpr int ctrl = B == 0 ? 0xB1 : 0x4E;  // quad_perm [1,0,3,2] / [2,3,0,1]
+  return __builtin_amdgcn_mov_dpp(v, ctrl, 0xF, 0xF, true);
+}
+template <int B>
+__device__ __forceinline__ float quad_other(float v) {
+  return __int_as_float(quad_other<B>(__float_as_int(v)));
+}
+template <int B>
+__device__ __forceinline__ uint32_t quad_other(uint32_t v) {
+  return (uint32_t)quad_other<B>((int)v);
+}
+template <int B>
+__device__ __forceinline__ double quad_other(double v) {
+  return __hiloint2double(quad_other<B>(__double2hiint(v)), quad_other<B>(__double2loint(v)));
+}
+// A butterfly's half in each lane: own + other, or other - own where the
+// lane's bit is set (sg = -1): the same sum, rounded once, as in registers.
+__device__ __forceinline__ float half_bfly(float own, float other, float sg) { return fmaf(own, sg, other); }
+__device__ __forceinline__ double half_bfly(double own, double other, double sg) { return fma(own, sg, other); }
+__device__ __forceinline__ uint32_t half_bfly(uint32_t own, uint32_t other, int sg) {
+  const uint32_t neg = (uint32_t)(sg >> 1);  // -1: all ones, 1: 0
+  return (own ^ neg) + other - neg;
+}
+
+// Stages of the digits 0..5 of a contiguous tile of LOGE >= 10 digits held in
+// LDS: 0..3 in registers (a thread's 16 consecutive elements), then 4 and 5,
+// which are bits 0 and 1 of the lane, between the lanes of a quad: one round
+// trip through LDS and one barrier less than with a second register group.
+template <int LOGE, class T>
+__device__ __forceinline__ void p2_low6(T* lds, int tid) {
+  static_assert(LOGE >= 10 && P2Shape<LOGE, 0>::THREADS * 16 == P2Shape<LOGE, 0>::E, "16 elements a thread");
+  using Sg = typename std::conditional<std::is_same<T, uint32_t>::value, int, T>::type;
+  T* base = lds + cpad(16 * tid);
+  T x[16];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) x[j] = base[cpad(j)];
+  reg_bfly<4>(x);
+  const Sg s0 = (tid & 1) ? (Sg)-1 : (Sg)1, s1 = (tid & 2) ? (Sg)-1 : (Sg)1;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) x[j] = half_bfly(x[j], quad_other<0>(x[j]), s0);
+#pragma unroll
+  for (int j = 0; j < 16; ++j) x[j] = half_bfly(x[j], quad_other<1>(x[j]), s1);
+#pragma unroll
+  for (int j = 0; j < 16; ++j) base[cpad(j)] = x[j];
+  lds_barrier();
 }
 
 }  // namespace fdwt
