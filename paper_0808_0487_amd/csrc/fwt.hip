@@ -222,10 +222,11 @@ __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS), (sizeof(T) == 
   if constexpr (LOGE >= 10) {
     // Three stage groups.  The 16 elements a thread loads (e = tid + k TH)
     // differ in the top 4 bits of e: those stages run in registers before the
-    // tile goes to LDS.  The stages of bits [WDIG, 6) run through LDS.  The
-    // store mapping e = lane + 64 k + 1024 w (still coalesced) puts bits 6..9
-    // in the register index: the remaining stages run in registers after
-    // reading the tile back.
+    // tile goes to LDS.  The stages of bits [WDIG, 6): of a strided tile,
+    // between the lanes (as its rows take the lower lane bits); of a
+    // contiguous tile, p2_low6.  The store mapping e = lane + 64 k + 1024 w
+    // (still coalesced) puts bits 6..9 in the register index: the remaining
+    // stages run in registers after reading the tile back.
     constexpr int NS = (LOGE - 10) < 4 ? (LOGE - 10) : 4;
     // The wave index is uniform in a wave: read as a scalar, the addresses
     // derived from it stay in scalar registers.
@@ -234,11 +235,13 @@ __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS), (sizeof(T) == 
     const uint32_t gstepS = (uint32_t)(64 >> WDIG) * sd0;
     const T* lrowS = lds + cpad(lane + 1024 * wv);
     reg_bfly<4>(v);
+    // Strided tiles: their digits below 6 are lane bits 4 and 5 (rows of 32: 5).
+    if constexpr (WDIG == 4) lane_bfly<16>(v);
+    if constexpr (WDIG > 0) lane_bfly<32>(v);
 #pragma unroll
     for (int k = 0; k < EPT; ++k) lrow[cpad(k * TH)] = v[k];
     lds_barrier();
     if constexpr (WDIG == 0) p2_low6<LOGE>(lds, tid);
-    else P2Groups<LOGE, WDIG, 0, T, 4, 6 - WDIG>::run(lds, tid);
 #pragma unroll
     for (int k = 0; k < EPT; ++k) v[k] = lrowS[66 * k];
     reg_bfly<NS>(v);
@@ -325,7 +328,6 @@ __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS))
   if constexpr (LOGE >= 10) {
     // The stage groups and the store mapping of fwt_p2.
     constexpr int NS = (LOGE - 10) < 4 ? (LOGE - 10) : 4;
-    constexpr int RDL = 6 - WDIG;
     const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t goffS = (uint32_t)(lane & (S::W - 1)) + (uint32_t)((lane >> WDIG) + (1024 >> WDIG) * wv) * sd0;
     const uint32_t gstepS = (uint32_t)(64 >> WDIG) * sd0;
@@ -335,6 +337,10 @@ __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS))
     float2 wcur[EPT];  // the weights of the tile
     for (; lb < nb; lb += G) {
       reg_bfly<4>(v);
+      if constexpr (WDIG == 4) {
+        lane_bfly<16>(v);
+        lane_bfly<32>(v);
+      }
 #pragma unroll
       for (int k = 0; k < EPT; ++k) lrow[cpad(k * TH)] = v[k];
       lds_barrier();
@@ -351,7 +357,7 @@ __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS))
       prefetch(lb + G < nb ? lb + G : lb);  // unconditional: exact wait counts
       // 2-digit register groups: with the weights and the next tile live they
       // keep the kernel within 128 registers.
-      P2Groups<LOGE, WDIG, 0, double, 2, RDL>::run(lds, tid);
+      if constexpr (WDIG == 0) P2Groups<LOGE, 0, 0, double, 2, 6>::run(lds, tid);
       double y[EPT];
 #pragma unroll
       for (int k = 0; k < EPT; ++k) y[k] = lrowS[66 * k];

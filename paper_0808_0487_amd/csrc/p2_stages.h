@@ -159,4 +159,48 @@ __device__ __forceinline__ void p2_low6(T* lds, int tid) {
   lds_barrier();
 }
 
+// Swaps of registers between lane halves (H = 32) or odd and even rows of 16
+// (H = 16): a's lanes with bit H set and b's lanes with it clear.
+template <int H>
+__device__ __forceinline__ void lane_swap(uint32_t& a, uint32_t& b) {
+  if constexpr (H == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+  } else {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+  }
+}
+template <int H>
+__device__ __forceinline__ void lane_swap(float& a, float& b) {
+  uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+  lane_swap<H>(x, y);
+  a = __uint_as_float(x);
+  b = __uint_as_float(y);
+}
+template <int H>
+__device__ __forceinline__ void lane_swap(double& a, double& b) {
+  uint32_t xl = (uint32_t)__double2loint(a), xh = (uint32_t)__double2hiint(a);
+  uint32_t yl = (uint32_t)__double2loint(b), yh = (uint32_t)__double2hiint(b);
+  lane_swap<H>(xl, yl);
+  lane_swap<H>(xh, yh);
+  a = __hiloint2double((int)xh, (int)xl);
+  b = __hiloint2double((int)yh, (int)yl);
+}
+// The butterfly stage of lane bit H on every value: a pair of registers is
+// swapped so that both halves of each butterfly meet in one lane, and back.
+template <int H, class T, int N>
+__device__ __forceinline__ void lane_bfly(T (&v)[N]) {
+#pragma unroll
+  for (int j = 0; j < N; j += 2) {
+    lane_swap<H>(v[j], v[j + 1]);
+    const T u = v[j], w = v[j + 1];
+    v[j] = add(u, w);
+    v[j + 1] = sub(u, w);
+    lane_swap<H>(v[j], v[j + 1]);
+  }
+}
+
 }  // namespace fdwt
