@@ -196,7 +196,8 @@ __global__ void __launch_bounds__((PassShape<P, KMAX, sizeof(T)>::THREADS))
 // a SIMD), loads and stores of the whole device in step.  Forward + inverse, a
 // workgroup per tile against that form (us): float m = 20 20.0 / 22.6, m = 21
 // 28.7 / 36.6, m = 22 33.6 / 36.9, m = 24 95.4 / 106.2, m = 25 256 / 296, m =
-// 26 550 / 583; double m = 20 31.0 / 33.1, m = 23 106 / 115, m = 24 225 / 232.
+// 26 550 / 583; double m = 20 29.6 / 33.1, m = 23 103 / 115, m = 24 221 / 232;
+// with the stages between lanes (p2_stages.h) float m = 24 then 93.2.
 template <class T, int LOGE, int WDIG>
 __global__ void __launch_bounds__((P2Shape<LOGE, WDIG>::THREADS), (sizeof(T) == 4 ? 8 : 4))
     fwt_p2(const T* __restrict__ in, T* out, PassDesc d) {
@@ -898,7 +899,8 @@ static std::vector<P2Pass> plan_p2_e(int m, int emax, size_t bytes = 4) {
 // transform fits one tile or needs it to stay at two passes, and smaller
 // tiles where two passes hold anyway: their workgroups are more than the CUs
 // at fewer points, and several share a CU (a 2^14-element float64 tile takes
-// a whole one).  Measured per call, 2^14 against this bound (us): float
+// a whole one).  Measured per call, 2^14 against this bound (us; with the
+// persistent form of the passes): float
 // m = 17 11.0 / 10.9, m = 19 12.1 / 11.3, m = 20 14.4 / 12.9, m = 22
 // 27.3 / 23.4 (m = 23 29.0 / 43.0: three passes); float64 m = 17 13.8 / 11.0,
 // m = 19 16.3 / 12.0, m = 20 21.0 / 16.1, m = 21 30.7 / 28.0 with 2^13

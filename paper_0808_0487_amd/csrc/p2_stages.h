@@ -139,7 +139,8 @@ __device__ __forceinline__ uint32_t half_bfly(uint32_t own, uint32_t other, int 
 // Stages of the digits 0..5 of a contiguous tile of LOGE >= 10 digits held in
 // LDS: 0..3 in registers (a thread's 16 consecutive elements), then 4 and 5,
 // which are bits 0 and 1 of the lane, between the lanes of a quad: one round
-// trip through LDS and one barrier less than with a second register group.
+// trip through LDS and one barrier less than with a second register group
+// (float 2^24 forward + inverse 94.7 -> 92.9 us, a split cost 41.6 -> 40.2).
 template <int LOGE, class T>
 __device__ __forceinline__ void p2_low6(T* lds, int tid) {
   static_assert(LOGE >= 10 && P2Shape<LOGE, 0>::THREADS * 16 == P2Shape<LOGE, 0>::E, "16 elements a thread");
@@ -191,6 +192,8 @@ __device__ __forceinline__ void lane_swap(double& a, double& b) {
 }
 // The butterfly stage of lane bit H on every value: a pair of registers is
 // swapped so that both halves of each butterfly meet in one lane, and back.
+// In place of a round trip through LDS (float 2^24 forward + inverse 94.0 ->
+// 93.2 us, a step at 2^24, s = 20 3653 -> 3630).
 template <int H, class T, int N>
 __device__ __forceinline__ void lane_bfly(T (&v)[N]) {
 #pragma unroll
