@@ -536,10 +536,10 @@ def interp_leg(torch, fdwt, inputs, reps=3):
     net.close()
     rate = work / (tot * 1e-3)
     return {"workload": "p=3 m=14 (N=%d) s=10, product family a_j=j^-2, 65536 queries of 20 base-3 digits" % N,
-            "eval_roofline": {"bound": "alu", "achieved": rate, "peak": VALU_LANE_OPS / 4.0,
-                              "unit": "coordinate evaluations/s", "frac": rate / (VALU_LANE_OPS / 4.0),
-                              "ops_per_evaluation": "4 VALU (xor, ffbh, shift-add, multiply) "
-                                                    "+ 1 LDS table read"},
+            "eval_roofline": {"bound": "alu", "achieved": rate, "peak": VALU_LANE_OPS,
+                              "unit": "coordinate evaluations/s", "frac": rate / VALU_LANE_OPS,
+                              "ops_per_evaluation": "1 VALU multiply + 4 bytes of a table row from LDS; "
+                                                    "row addresses are shared by a block of points"},
             "forward_inverse_ms": float(np.median(t_fi)), "points_per_s_fwd_inv": N / (np.median(t_fi) * 1e-3),
             "forward_inverse_ms_back_to_back": t_b2b,
             "forward_inverse_kernels": {"launches_per_pair": fn / 5, "kernel_ms_per_pair": ftot / 5,
