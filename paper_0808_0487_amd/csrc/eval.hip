@@ -33,8 +33,10 @@ namespace fdwt {
 //   A point word (one per block and coordinate, wave-uniform) holds the ND
 //   digits after the first K at the top, DB bits each; p = 2 puts b's share
 //   at bits 5..4 (the row's byte offset) and a one at bit 0; p odd puts
-//   1 + (first digit) in the low bits.  The low bits keep z non-zero, so its
-//   leading-zero count is at most 31 and no row index is out of range.
+//   1 + (first digit), 1..p, in the low bits.  FMASK covers these low bits
+//   alone: the ND digits end right above (p = 3: the 16th digit of 3^16 points
+//   lies at bits 3..2).  The low bits keep z non-zero, so its leading-zero
+//   count is at most 31 and no row index is out of range.
 //   Counts of ND DB or more mean that all ND digits agree.
 //   A row is 16 bytes (the factors r = 0..3); for p = 5, 7 the factors from
 //   r = 4 on lie in a second region of the coordinate (R2 bytes per row).
@@ -51,19 +53,29 @@ struct RowCfg;
 template <>
 struct RowCfg<2> {
   static constexpr int K = 2, B = 4, ND = 26, DB = 1, NT = 32, RPT = 4, R2 = 0, U = 1;
+  static constexpr uint32_t FMASK = 63;
 };
 template <>
 struct RowCfg<3> {
   static constexpr int K = 1, B = 3, ND = 15, DB = 2, NT = 16, RPT = 3, R2 = 0, U = 2;
+  static constexpr uint32_t FMASK = 3;
 };
 template <>
 struct RowCfg<5> {
   static constexpr int K = 1, B = 5, ND = 9, DB = 3, NT = 16, RPT = 5, R2 = 4, U = 1;
+  static constexpr uint32_t FMASK = 7;
 };
 template <>
 struct RowCfg<7> {
   static constexpr int K = 1, B = 7, ND = 9, DB = 3, NT = 16, RPT = 7, R2 = 16, U = 1;
+  static constexpr uint32_t FMASK = 7;
 };
+template <int P>
+constexpr bool low_bits_apart() {
+  return RowCfg<P>::FMASK >= P && RowCfg<P>::FMASK >> (32 - RowCfg<P>::ND * RowCfg<P>::DB) == 0;
+}
+static_assert(low_bits_apart<2>() && low_bits_apart<3>() && low_bits_apart<5>() && low_bits_apart<7>(),
+              "the low bits of a point word hold no digit after the first K");
 template <int P>
 constexpr int row_bytes() { return RowCfg<P>::NT * RowCfg<P>::RPT * (16 + RowCfg<P>::R2); }  // LDS per coordinate
 
@@ -282,7 +294,7 @@ __global__ void __launch_bounds__(TH, row_waves(P, SG, TH)) k_eval_rows(const ui
     uint32_t t;
     asm("v_ffbh_u32 %0, %1" : "=v"(t) : "v"(z));
     if constexpr (P == 2) return (t << 6) | (z & 48u);
-    const uint32_t sel = (x & 7u) | 0x0c0c0c00u;
+    const uint32_t sel = (x & R::FMASK) | 0x0c0c0c00u;
     const uint32_t w = __builtin_amdgcn_perm(a1, a0, sel);
     if constexpr (P == 3) return __umul24(t & 30u, 24) + w;
     return __umul24(__umul24(t, 43) >> 7, R::RPT * 16) + w;  // t / 3
@@ -323,7 +335,7 @@ __global__ void __launch_bounds__(TH, row_waves(P, SG, TH)) k_eval_rows(const ui
       const int pf = pfx[j];
       int b;
       if constexpr (P == 2) b = (int)((z >> 4) & 3u);
-      else b = ((int)(v.y & 255u) + P - (int)((x & 7u) - 1u)) % P;
+      else b = ((int)(v.y & 255u) + P - (int)((x & R::FMASK) - 1u)) % P;
 #pragma unroll
       for (int u = 0; u < B; ++u) {
         int k = lead_of_row<P>(pf, b, u);
