@@ -23,6 +23,7 @@
 //    of their XOR (p = 2) or of their packed-digit XOR (p odd).
 #include "coords.h"
 #include "dev_math.h"
+#include "pair_scale.h"
 
 #include <algorithm>
 #include <chrono>
@@ -602,32 +603,6 @@ KernTab kern_tab(int p, int digits, const fdwt_kernel* k) {
   return t;
 }
 
-// Pair exponents (p odd): the variance columns U_1..U_s, Q_1..Q_{s-1} are
-// transformed two to a complex column, and a power of two brings the second of
-// a pair to the first one's magnitude (both at x = 0, their maximum), so that
-// neither loses digits to the other's rounding.
-static void pair_exponents(int s, int m, KernTab& t) {
-  std::vector<double> col(2 * s, 0.0), e(s + 1, 0.0);  // U_d, Q_j at x = 0
-  e[0] = 1.0;
-  double u = 0.0;
-  for (int j = 0; j < s; ++j) {
-    const double r = t.gamma[j] * t.gamma[j] * t.rp[m];
-    u = u + r + u * r;
-    col[j] = u;
-    for (int i = j + 1; i >= 1; --i) e[i] += r * e[i - 1];
-  }
-  for (int j = 1; j <= s; ++j) col[s + j - 1] = e[j];
-  for (int i = 0; i < s; ++i) {
-    int ea = 0, eb = 0;
-    const double a = col[2 * i], b = col[2 * i + 1];
-    if (a > 0.0 && b > 0.0 && std::isfinite(a) && std::isfinite(b)) {
-      (void)std::frexp(a, &ea);
-      (void)std::frexp(b, &eb);
-    }
-    t.ix[i] = std::max(-1000, std::min(1000, ea - eb));
-  }
-}
-
 int ensure_res_host(Net& net) {
   if (net.res_host) return FDWT_OK;
   if (hipHostMalloc((void**)&net.res_host, (2 * kMaxS + 2) * sizeof(double), hipHostMallocDefault) != hipSuccess) {
@@ -1049,7 +1024,7 @@ int eff_dim_enqueue(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
     if (rc) return rc;
     GK = w.gk;
   }
-  if (p != 2) pair_exponents(s, net.m, kt);
+  if (p != 2) pair_exponents(p, net.m, s, kt.gamma, kt.rp, kt.ix);
   double* h0 = w.res + 2 * s + 1;  // h = 0 share of the total
   const double pm = (double)N;
   // p = 2 two-pass plans keep the intermediate columns in the blocked layout
