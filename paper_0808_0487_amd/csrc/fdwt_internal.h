@@ -96,6 +96,7 @@ struct Net {
   // Pinned host results of eff_dim and split_cost, written by their last
   // kernel (allocated on first use, 2 kMaxS + 2 doubles).
   double* res_host = nullptr;
+  hipEvent_t done = nullptr;  // behind a call's work, for calls that wait for it (on first use)
   // The split of the points in halves (tune.cpp; p = 2, on first use).
   std::shared_ptr<SplitPlan> split;
 };

@@ -759,6 +759,8 @@ void release_spectrum(Net& net) {
   if (net.spec || net.res_host) (void)hipDeviceSynchronize();
   if (net.spec) (void)hipFree(net.spec);
   if (net.spec_ready) (void)hipEventDestroy(net.spec_ready);
+  if (net.done) (void)hipEventDestroy(net.done);
+  net.done = nullptr;
   if (net.res_host) (void)hipHostFree(net.res_host);
   net.res_host = nullptr;
   net.spec = nullptr;
@@ -1105,29 +1107,27 @@ static size_t effdim_budget() {
   return b;
 }
 
-// Results a call waits for: n doubles in pinned memory, each stored once by the
-// call's last kernel.  They are set to a signalling NaN before that kernel is
-// launched (no arithmetic gives one: it would be quiet) and the host reads
-// them until all are replaced.  A wait through the stream returns well after
-// the kernel has ended (per call, such a wait against this one: a p = 2 step at
-// 2^10 points 70 to 82 / 64 us, eff_dim at 3^12, s = 10 99 / 95 us).
-// After kSpinUs, or where the kernel does not run (an error, a stream under
-// capture), the wait goes through the stream, which reports it.
-static constexpr uint64_t kPending = 0x7ff4504e44494e47ull;
+// Waits until all work enqueued on st is done and visible to the host: an
+// event behind it, polled for kSpinUs, then the stream.  A wait through the
+// stream at once also walks its whole list of commands: per call, the stream
+// against the event, a p = 2 step at 2^10 points 87 / 62 us, a split cost at
+// 2^14 points 37.5 / 37.5 us, eff_dim at 3^12, s = 10 101.5 / 100.5 us.  On a
+// stream under capture the wait through the stream reports the error.
 static constexpr int kSpinUs = 300;
 
-static void arm_results(double* r, int n) {
-  for (int i = 0; i < n; ++i) __atomic_store_n((uint64_t*)r + i, kPending, __ATOMIC_RELEASE);
-}
-
-static int wait_results(const double* r, int n, hipStream_t st) {
-  const auto end = std::chrono::steady_clock::now() + std::chrono::microseconds(kSpinUs);
-  int i = 0;
-  do {
-    for (int k = 0; k < 64 && i < n; ++k)
-      if (__atomic_load_n((const uint64_t*)r + i, __ATOMIC_ACQUIRE) != kPending) ++i;
-    if (i == n) return FDWT_OK;
-  } while (std::chrono::steady_clock::now() < end);
+static int wait_stream(Net& net, hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
+    if (!net.done) FDWT_HIP(hipEventCreateWithFlags(&net.done, hipEventDisableTiming));
+    FDWT_HIP(hipEventRecord(net.done, st));
+    const auto end = std::chrono::steady_clock::now() + std::chrono::microseconds(kSpinUs);
+    do {
+      const hipError_t e = hipEventQuery(net.done);
+      if (e == hipSuccess) return FDWT_OK;
+      if (e != hipErrorNotReady) FDWT_HIP(e);
+    } while (std::chrono::steady_clock::now() < end);
+    (void)hipGetLastError();  // not ready is no error
+  }
   FDWT_HIP(hipStreamSynchronize(st));
   return FDWT_OK;
 }
@@ -1139,12 +1139,9 @@ int run_eff_dim(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* ft, 
   if (rc) return rc;
   rc = cached_spectrum(net, kern, &gk, st);
   if (rc) return rc;
-  const int n = 2 * net.s + 2;
-  arm_results(net.res_host, n);
-  net.res_host[2 * net.s - 1] = 0.0;  // not written
   rc = eff_dim_enqueue(net, sc, kern, gk, ft, ch, net.res_host, st);
   if (rc) return rc;
-  if ((rc = wait_results(net.res_host, n, st))) return rc;
+  if ((rc = wait_stream(net, st))) return rc;
   eff_dim_finish(net.s, net.res_host, out);
   return FDWT_OK;
 }
@@ -1193,10 +1190,8 @@ int run_split_cost(Net& tr, Scratch& sc, const uint32_t* delta, const float* ft,
   KernTab kt = kern_tab(2, m2, kern);
   std::memcpy(kt.ix, delta, (size_t)s * 4);
   if (fwt_p2_split_tile_ok(tr.m)) {
-    arm_results(tr.res_host, 1);
     if ((rc = fwt_p2_split_tile(tr, kt, ft, fval, gk, sf_out, tr.res_host, st))) return rc;
-    if (sf_out) FDWT_HIP(hipStreamSynchronize(st));  // the kernel's other output
-    else if ((rc = wait_results(tr.res_host, 1, st))) return rc;
+    if ((rc = wait_stream(tr, st))) return rc;
     *cost = tr.res_host[0];
     return FDWT_OK;
   }
@@ -1214,7 +1209,7 @@ int run_split_cost(Net& tr, Scratch& sc, const uint32_t* delta, const float* ft,
   hipLaunchKernelGGL(k_sq_diff, dim3(kRedBlocks), dim3(256), 0, st, fval, g, N, partial, sf_out);
   hipLaunchKernelGGL(k_sum_rows, dim3(1), dim3(kSumThreads), 0, st, partial, kRedBlocks, tr.res_host);
   FDWT_HIP(hipGetLastError());
-  FDWT_HIP(hipStreamSynchronize(st));
+  if ((rc = wait_stream(tr, st))) return rc;
   *cost = tr.res_host[0];
   return FDWT_OK;
 }
