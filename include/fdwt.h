@@ -281,7 +281,10 @@ int fdwt_eff_dim_data(const fdwt_net* net, const fdwt_kernel* kern, const float*
  * fdwt_split_cost returns the cost (and, if sf_dev is not NULL, Sf at the
  * second half, float [N]); fdwt_kernel_tune minimises it by the Nelder-Mead
  * simplex method in (log(alpha - 1), log beta, q) from start = {alpha, beta,
- * q} with at most max_evals cost evaluations.  Both synchronise `stream`;
+ * q} with at most max_evals cost evaluations.  Both use the net's workspace
+ * (20 bytes per point of the first half) and leave the tables of the first
+ * half as a net of its own in the handle (1 KiB per coordinate and byte of the
+ * point index) until fdwt_net_free.  Both synchronise `stream`;
  * p odd gives FDWT_EUNSUPPORTED.  Errors: FDWT_EINVAL for alpha <= 1,
  * beta <= 0, a non-finite q or NULL pointers. */
 typedef struct {

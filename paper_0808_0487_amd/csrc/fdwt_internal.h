@@ -221,10 +221,12 @@ int run_eff_dim(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* ft, 
 // spline fitted on the first half (the m-digit net `tr`), as the inverse
 // transform of f~ G / K_u, and the cost sum (f - Sf)^2.  delta: the second
 // half's shift x_N, per coordinate as an (m+1)-digit integer (host array).
-// ft: forward transform of the first half's values; fval: second half's
-// values; sf_out (nullable) receives Sf there.  Synchronises st.
-int run_split_cost(Net& tr, Scratch& sc, const uint32_t* delta, const float* ft, const float* fval,
-                   const fdwt_kernel* kern, float* sf_out, double* cost, hipStream_t st);
+// ws: split_cost_ws_bytes, with the forward transform of the first half's
+// values in its first N floats; fval: second half's values; sf_out (nullable)
+// receives Sf there.  Synchronises st.
+size_t split_cost_ws_bytes(const Net& tr);
+int run_split_cost(Net& tr, void* ws, const uint32_t* delta, const float* fval, const fdwt_kernel* kern, float* sf_out,
+                   double* cost, hipStream_t st);
 
 // tune.cpp (Section 5.1): cost of (alpha, beta, q) = prm, and the
 // Nelder-Mead selection from `start`, for a p = 2 net of m + 1 digits.

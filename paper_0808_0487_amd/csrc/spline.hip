@@ -1170,21 +1170,37 @@ int lift_queries(const Net& net, const uint32_t* q, int64_t nq, int q_depth, uin
 }
 
 // ------------------------------------------------------- split cost
-int run_split_cost(Net& tr, Scratch& sc, const uint32_t* delta, const float* ft, const float* fval,
-                   const fdwt_kernel* kern, float* sf_out, double* cost, hipStream_t st) {
+struct SplitWs {
+  float* ft;  // forward transform of the first half's values (the caller's)
+  double* gk;
+  void* sw;
+  double* g;
+  double* partial;
+};
+static void split_layout(const Net& tr, Carve& cv, SplitWs& w) {
+  w.ft = (float*)cv.take((size_t)tr.N * sizeof(float));
+  w.gk = (double*)cv.take(spectrum_bytes(tr));
+  w.sw = cv.take(spectrum_ws_bytes(tr));
+  w.g = (double*)cv.take((size_t)tr.N * 8);
+  w.partial = (double*)cv.take(kRedBlocks * sizeof(double));
+}
+size_t split_cost_ws_bytes(const Net& tr) {
+  Carve cv(nullptr);
+  SplitWs w;
+  split_layout(tr, cv, w);
+  return cv.off;
+}
+
+int run_split_cost(Net& tr, void* ws, const uint32_t* delta, const float* fval, const fdwt_kernel* kern, float* sf_out,
+                   double* cost, hipStream_t st) {
   const int s = tr.s, m2 = tr.m + 1;
   const int64_t N = tr.N;
-  Carve need(nullptr);
-  need.take(spectrum_bytes(tr));
-  need.take(spectrum_ws_bytes(tr));
-  need.take((size_t)N * 8);
-  need.take(kRedBlocks * sizeof(double));
-  if (int rc = ensure_ws(sc, need.off, st)) return rc;
-  Carve cv(sc.ws);
-  double* gk = (double*)cv.take(spectrum_bytes(tr));
-  void* sw = cv.take(spectrum_ws_bytes(tr));
-  double* g = (double*)cv.take((size_t)N * 8);
-  double* partial = (double*)cv.take(kRedBlocks * sizeof(double));
+  Carve cv(ws);
+  SplitWs w;
+  split_layout(tr, cv, w);
+  const float* ft = w.ft;
+  double *gk = w.gk, *g = w.g, *partial = w.partial;
+  void* sw = w.sw;
   int rc = ensure_res_host(tr);
   if (rc) return rc;
   KernTab kt = kern_tab(2, m2, kern);

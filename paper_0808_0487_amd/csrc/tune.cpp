@@ -20,18 +20,13 @@
 namespace fdwt {
 
 // What the split of a net's points needs besides the data: the first half as
-// a net of its own, with its workspace, and the shift.  Kept in the handle of
-// the whole net (it depends on the generators alone), so that a call neither
-// builds tables nor allocates.
+// a net of its own, and the shift.  Kept in the handle of the whole net (it
+// depends on the generators alone), so that a call neither builds tables nor
+// allocates; what a call computes lies in the whole net's workspace.
 struct SplitPlan {
   fdwt_net* tr = nullptr;       // the first half as an m-digit net
   std::vector<uint32_t> delta;  // x_N per coordinate, (m + 1)-digit integers
-  float* ft = nullptr;          // forward transform of the first half's values
   ~SplitPlan() {
-    if (ft) {
-      (void)hipDeviceSynchronize();
-      (void)hipFree(ft);
-    }
     if (tr) fdwt_net_free(tr);
   }
 };
@@ -40,6 +35,7 @@ namespace {
 
 struct Split {
   SplitPlan* plan = nullptr;
+  void* ws = nullptr;           // split_cost_ws_bytes, the transform of the first half first
   const float* fval = nullptr;  // values at the second half
   hipStream_t st = nullptr;
 };
@@ -63,7 +59,6 @@ int split_plan(Net& n2) {
   for (int j = 0; j < s; ++j)
     for (int r = 0; r < m2; ++r)
       if (C(j, r, m)) plan->delta[j] |= 1u << (m2 - 1 - r);
-  FDWT_HIP(hipMalloc(&plan->ft, (size_t)plan->tr->n.N * sizeof(float)));
   n2.split = plan;
   return FDWT_OK;
 }
@@ -73,7 +68,9 @@ int split_setup(Net& n2, const float* f2, Split& sp, hipStream_t st) {
   sp.plan = n2.split.get();
   const int64_t N = sp.plan->tr->n.N;
   sp.st = st;
-  if (int rc = fwt_run(2, n2.m - 1, false, K_F32, f2, K_F32, K_F32, sp.plan->ft, 1, 1.0 / (double)N, st)) return rc;
+  if (int rc = ensure_ws(n2.sc, split_cost_ws_bytes(sp.plan->tr->n), st)) return rc;
+  sp.ws = n2.sc.ws;
+  if (int rc = fwt_run(2, n2.m - 1, false, K_F32, f2, K_F32, K_F32, sp.ws, 1, 1.0 / (double)N, st)) return rc;
   sp.fval = f2 + N;
   return FDWT_OK;
 }
@@ -83,7 +80,7 @@ int split_eval(Split& sp, const double prm[3], float* sf, double* cost) {
   std::vector<double> gam(tr.s);
   for (int j = 0; j < tr.s; ++j) gam[j] = prm[1] * std::pow((double)(j + 1), prm[2]);  // gamma_j = beta j^q
   const fdwt_kernel kern{prm[0], gam.data(), tr.s};
-  return run_split_cost(tr, tr.sc, sp.plan->delta.data(), sp.plan->ft, sp.fval, &kern, sf, cost, sp.st);
+  return run_split_cost(tr, sp.ws, sp.plan->delta.data(), sp.fval, &kern, sf, cost, sp.st);
 }
 
 std::array<double, 3> to_params(const std::array<double, 3>& th) {
