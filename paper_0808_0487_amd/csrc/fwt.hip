@@ -1280,8 +1280,8 @@ int fwt_p2_split_tile(const Net& tr, const KernTab& kt, const float* ft, const f
   SplitTile g{tr.d_xtab, tr.nbytes, tr.s, m, ft, fval, ku, sf, cost};
   KernTab k = kt;
   void* args[] = {(void*)&g, (void*)&k};
-  FDWT_HIP(hipLaunchKernel(fn, dim3(1), dim3(E / 16), args, lds, st));
-  return FDWT_OK;
+  // f~ and the second half read, K_u (and Sf) written.
+  return launch_timed(fn, dim3(1), dim3(E / 16), args, lds, st, FDWT_TC_PASS_F64, (double)E * (sf ? 20 : 16));
 }
 
 // The passes after the first of an unnormalised p = 2 float64 transform, in
