@@ -175,13 +175,6 @@ __device__ __forceinline__ uint64_t eval_string_odd(uint64_t pk, int m) {
   return v;
 }
 
-// Workgroups for ngroups equal point groups: at most `most`, each with the
-// same number of groups (or one fewer).
-inline unsigned even_grid(int64_t ngroups, int64_t most) {
-  const int64_t per = (ngroups + most - 1) / most;
-  return (unsigned)((ngroups + per - 1) / per);
-}
-
 // Index t of the first non-zero digit (t = i - 1) of x_{n,j}, or m when
 // x_{n,j} = 0.
 __device__ __forceinline__ int lead_p2(uint32_t X, int m) { return __clz(X) - (32 - m); }

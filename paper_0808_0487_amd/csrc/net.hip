@@ -152,9 +152,13 @@ __global__ void __launch_bounds__(kChunk) k_sample_odd(const uint64_t* ptab, Fam
 
 // ----------------------------------------------------------- launchers
 // Enough workgroups to fill the chip several times over, few enough that the
-// per-workgroup table staging is amortised over many point groups.
+// per-workgroup table staging is amortised over many point groups.  All of the
+// 2048, also where they get unequal numbers of groups: they are resident
+// together, so fewer of them with equal numbers only leave latency uncovered
+// (sample, us, equal numbers against this: 7^7, s = 10 17.1 / 14.3, 3^12,
+// s = 24 35.1 / 29.3, 5^9, s = 10 38.6 / 34.8).
 static unsigned grid_for(int64_t N, int threads) {
-  return even_grid((N + threads - 1) / threads, 2048);
+  return (unsigned)std::min<int64_t>((N + threads - 1) / threads, 2048);
 }
 
 static double inv_pm(const Net& net) { return 1.0 / (double)net.N; }

@@ -642,7 +642,7 @@ static int kcols_launch(const Net& net, const KernTab& kt, int c0, int c1, doubl
                           FDWT_TC_KCOLS, 8.0 * (double)net.N * (c1 - c0));
     }
   }
-  const unsigned grid = even_grid((net.N + kChunk - 1) / kChunk, 8192);
+  const unsigned grid = (unsigned)std::min<int64_t>((net.N + kChunk - 1) / kChunk, 8192);
   return launch_timed((const void*)k_kernel_cols<P, SMAX>, dim3(grid), dim3(kChunk), args, lds, st, FDWT_TC_KCOLS,
                       8.0 * (double)net.N * (c1 - c0));
 }
