@@ -1098,7 +1098,7 @@ static int run_passes(int p, int m, bool inverse, Kind in_kind, const void* in, 
     return fail(FDWT_EINVAL, "unsupported transform element types");
   const int64_t N = ipow(p, m);
   // p = 2 below 2^7 points: the generic pass; p odd: the static shapes of odd.hip.
-  std::vector<PassGeom> passes = p == 2 ? plan(p, m, kind_bytes(work_kind), work_kind) : odd_plan(p, m, work_kind);
+  std::vector<PassGeom> passes = p == 2 ? plan(p, m, kind_bytes(work_kind), work_kind) : odd_plan(p, m, work_kind == K_CF64);
   const size_t np = passes.size();
   if (last_parts) {
     const PassGeom& g = passes.back();
@@ -1348,7 +1348,7 @@ int fwt_p2_forward_family(const Net& net, int family, const FamilyArgs& fa, floa
 
 int64_t fwt_reduce_parts(int p, int m, size_t elem_bytes) {
   if (p == 2 && m >= 7) return p2_reduce_parts(m, plan_p2_cols(m).back());
-  const std::vector<PassGeom> passes = p == 2 ? plan(p, m, elem_bytes, K_F64) : odd_plan(p, m, K_CF64);
+  const std::vector<PassGeom> passes = p == 2 ? plan(p, m, elem_bytes, K_F64) : odd_plan(p, m, true);
   const PassGeom& g = passes.back();
   return ipow(p, m) / (ipow(p, g.r) * ipow(p, g.wdig));
 }

@@ -10,8 +10,9 @@
 // are odd multiples of the row length, so the tile needs no padding.  The
 // stages run in ascending order of the digits (the top digits on the values
 // read back for the store), so a transform's rounding does not depend on how
-// it is split into passes; the p = 3 float tiles of 3^8 elements take the top
-// digits first, on the values as loaded.
+// it is split into passes; the p = 3 float tiles of 3^8 elements take the KT
+// top digits first, on the values as loaded.  Tile sizes and KT follow from
+// p, m, the type and the number of columns alone (pass_geom.h).
 #include "pass_core.h"
 
 #include <algorithm>
@@ -244,59 +245,6 @@ __global__ void __launch_bounds__((OddShape<P, LE, RD, KT>::TH))
   }
 }
 
-// ----------------------------------------------------------------- planner
-// Tiles as small as two passes allow, with rows of at least 40 bytes: more
-// workgroups at few points, and several per CU, whose loads, arithmetic and
-// stores overlap.
-std::vector<PassGeom> odd_plan(int p, int m, Kind work) {
-  std::vector<PassGeom> out;
-  auto first = [&](int le) { out.push_back({0, le, 0, le}); };
-  auto strided = [&](int le, int r) {
-    const int d0 = out.back().d0 + out.back().r;
-    out.push_back({d0, r, le - r, le});
-  };
-  const bool f64 = work == K_CF64;
-  // The largest net of one tile, and the exponent of every tile beyond it.
-  // Forward + inverse pairs, this choice (us) against the generic passes
-  // before it, and against the next tile: p = 3 double m = 9 20 / 30, m = 12
-  // 33 / 46, m = 14 114 / 153 (3^7 and three passes: 139); p = 3 float m = 14
-  // 60 (3^7: 81); p = 5 float m = 8 25 / 55, m = 10 140 / 226 (5^5 and three
-  // passes: 154), m = 11 846 / 1268 (5^5: 932); p = 5 double m = 10 302 / 519;
-  // p = 7 float m = 5 20 / 23, m = 8 103 / 154, m = 9 802 / 1118 (two passes
-  // of 7^5, a CU each: 818); double m = 8 172 / 250.
-  // (p = 3 float, 3^9..3^11 points: tiles of 3^8 elements, their
-  // top-digits-first order is that of the larger nets, and float64 variances
-  // are computed from these float coefficients.)
-  int single, le;
-  if (p == 3) {
-    single = 8;
-    le = f64 ? (m <= 12 || m > 14 ? 7 : 8) : (m == 12 ? 7 : 8);
-  } else if (p == 5) {
-    single = f64 ? 5 : 6;
-    le = f64 ? (m <= 6 ? 4 : 5) : (m <= 9 ? 5 : 6);
-  } else {
-    single = 4;
-    le = m <= 5 ? 3 : 4;
-  }
-  if (m <= single) {
-    first(m);
-    return out;
-  }
-  first(le);
-  const int rest = m - le;
-  // Digits of a strided pass: rows of 9 (p = 3), 5 or 25 (p = 5) and 7
-  // (p = 7) elements at least.
-  const int cap = p == 3 ? le - 2 : le - 1;
-  if (p == 3 && rest == 1) le = 7;  // 3^9 points, float: one digit needs rows of 3^6
-  const int n = (rest + cap - 1) / cap;
-  for (int i = 0, done = 0; i < n; ++i) {
-    const int r = (rest - done + (n - i) - 1) / (n - i);
-    strided(le, r);
-    done += r;
-  }
-  return out;
-}
-
 // ----------------------------------------------------------------- launch
 template <int P, int LE, int RD, int KT, bool INV, class Tin, class T, class Tout, int EPI>
 static int launch_odd(const void* in, void* out, const PassGeom& g, int m, int batch, double scale,
@@ -369,75 +317,27 @@ static int odd_kinds(bool inv, bool in_real, bool out_real, const void* in, void
   return fail(FDWT_EINVAL, "unsupported transform element types");
 }
 
-// Register digits of a shape: two where the tile's p^(LE - 2) threads still
-// fill waves (p = 5 float, m = 9: 43 against 46 us a pair with one), but one
-// for p = 5 in double (25 complex values and as many prefetched leave few
-// waves: eff_dim at m = 9, s = 20 823 against 729 us).
-constexpr int odd_kt(int p, int le, int rd, bool f64) { return rd >= 2 && le >= 5 && !(p == 5 && f64) ? 2 : 1; }
-
 template <int P, class R, class C>
 static int odd_shape(bool inv, bool in_real, bool out_real, const void* in, void* out, const PassGeom& g, int m,
                      int batch, double scale, const ReduceArgs* red, hipStream_t st) {
   constexpr bool D = std::is_same<C, double2>::value;
-#define FDWT_ODD_KT(LE, RD, KT)  \
-  if (g.le == LE && g.r == RD) \
-  return odd_kinds<P, LE, RD, KT, R, C>(inv, in_real, out_real, in, out, g, m, batch, scale, red, st)
-#define FDWT_ODD(LE, RD) FDWT_ODD_KT(LE, RD, odd_kt(P, LE, RD, D))
   if (g.le < 1 || g.r > g.le || g.wdig != g.le - g.r || g.d0 < g.wdig || (g.d0 == 0) != (g.r == g.le))
     return fail(FDWT_EINVAL, "not an odd-p pass shape");
-  FDWT_ODD(1, 1);
-  FDWT_ODD(2, 2);
-  FDWT_ODD(3, 3);
-  FDWT_ODD(4, 4);
-  if constexpr (P == 3) {
-    FDWT_ODD(5, 5);
-    FDWT_ODD(6, 6);
-    FDWT_ODD(7, 7);
-    FDWT_ODD(7, 1);
-    FDWT_ODD(7, 2);
-    FDWT_ODD(7, 3);
-    FDWT_ODD(7, 4);
-    FDWT_ODD(7, 5);
-    if constexpr (D) {
-      FDWT_ODD(8, 8);
-      FDWT_ODD(8, 5);
-      FDWT_ODD(8, 6);
-    } else {
-      // Three register digits (243 threads, three workgroups per CU) pay
-      // when they let every tile run in one round and two (729 threads, two
-      // per CU) would not (3^14 points: 729 tiles).
-      const int64_t nb = ipow(3, m) / 6561 * batch;
-      const bool kt3 = g.le == 8 && nb > 2 * (int64_t)device_cus() && nb <= 3 * (int64_t)device_cus();
-#define FDWT_ODD8(RD) \
-  if (kt3) { FDWT_ODD_KT(8, RD, 3); } \
-  FDWT_ODD_KT(8, RD, 2)
-      FDWT_ODD8(8);
-      FDWT_ODD_KT(8, 2, 2);
-      FDWT_ODD8(4);
-      FDWT_ODD8(5);
-      FDWT_ODD8(6);
-      FDWT_ODD8(3);
-#undef FDWT_ODD8
-    }
-  } else if constexpr (P == 5) {
-    FDWT_ODD(5, 5);
-    FDWT_ODD(5, 2);
-    FDWT_ODD(5, 3);
-    FDWT_ODD(5, 4);
-    if constexpr (D) {
-      FDWT_ODD(4, 2);
-    } else {
-      FDWT_ODD(6, 6);
-      FDWT_ODD(6, 4);
-      FDWT_ODD(6, 5);
-    }
-  } else {
-    FDWT_ODD(3, 2);
-    FDWT_ODD(4, 2);
-    FDWT_ODD(4, 3);
+  const bool kt3 = odd_kt3(P, D, g.le, ipow(P, m - g.le) * batch);
+#define FDWT_ODD(LE, RD)                                                                                       \
+  if constexpr (odd_has_shape(P, D, LE, RD)) {                                                                 \
+    if (g.le == LE && g.r == RD) {                                                                             \
+      if constexpr (P == 3 && !D && odd_kt3_shape(LE, RD)) {                                                   \
+        if (kt3) return odd_kinds<P, LE, RD, 3, R, C>(inv, in_real, out_real, in, out, g, m, batch, scale, red, st); \
+      }                                                                                                        \
+      return odd_kinds<P, LE, RD, odd_kt(P, LE, RD, D), R, C>(inv, in_real, out_real, in, out, g, m, batch, scale, red, st); \
+    }                                                                                                          \
   }
+#define FDWT_ODD_LE(LE) \
+  FDWT_ODD(LE, 1) FDWT_ODD(LE, 2) FDWT_ODD(LE, 3) FDWT_ODD(LE, 4) FDWT_ODD(LE, 5) FDWT_ODD(LE, 6) FDWT_ODD(LE, 7) FDWT_ODD(LE, 8)
+  FDWT_ODD_LE(1) FDWT_ODD_LE(2) FDWT_ODD_LE(3) FDWT_ODD_LE(4) FDWT_ODD_LE(5) FDWT_ODD_LE(6) FDWT_ODD_LE(7) FDWT_ODD_LE(8)
+#undef FDWT_ODD_LE
 #undef FDWT_ODD
-#undef FDWT_ODD_KT
   return fail(FDWT_EINVAL, "not an odd-p pass shape");
 }
 

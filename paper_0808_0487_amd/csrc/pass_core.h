@@ -4,6 +4,7 @@
 #pragma once
 
 #include "dev_math.h"
+#include "pass_geom.h"
 
 namespace fdwt {
 
@@ -54,12 +55,6 @@ struct PassDesc {
   int16_t pexp[kMaxS];
 };
 
-// One pass of a plan: digits [d0, d0 + r), rows of p^wdig elements; le: the
-// tile exponent of an odd-p pass (wdig + r).
-struct PassGeom {
-  int d0, r, wdig, le;
-};
-
 // Optional grouped-sum epilogue of the last pass.
 struct ReduceArgs {
   const float2* wts;
@@ -74,9 +69,8 @@ struct ReduceArgs {
 // kernel (both cached).
 int device_cus();
 int occupancy(const void* fn, int threads, size_t lds);
-// odd.hip: the plan of a p = 3, 5, 7 transform in working type K_CF32 or
-// K_CF64, and one pass of it.
-std::vector<PassGeom> odd_plan(int p, int m, Kind work);
+// odd.hip: one pass of a p = 3, 5, 7 transform (odd_plan) in working type
+// K_CF32 or K_CF64.
 int odd_pass(int p, bool inv, Kind ik, Kind work, Kind ok, const void* in, void* out, const PassGeom& g, int m,
              int batch, double scale, const ReduceArgs* red, hipStream_t st);
 
