@@ -79,8 +79,8 @@ def parse():
 # valid only while these files are unchanged).
 CLASS_SOURCES = {
     "pass_f32": ["fwt.hip", "p2_stages.h", "pass_core.h", "dev_math.h"],
-    "pass_cf32": ["odd.hip", "pass_core.h", "dev_math.h"],
-    "pass_f64": ["fwt.hip", "odd.hip", "p2_stages.h", "pass_core.h", "dev_math.h"],
+    "pass_cf32": ["odd.hip", "pass_geom.h", "pass_core.h", "dev_math.h"],
+    "pass_f64": ["fwt.hip", "odd.hip", "p2_stages.h", "pass_geom.h", "pass_core.h", "dev_math.h"],
     "kcols": ["spline.hip", "coords.h", "dev_math.h"],
     "eval": ["eval.hip", "spline.hip", "coords.h", "dev_math.h"],
     "sample": ["net.hip", "coords.h", "dev_math.h"],

@@ -118,7 +118,6 @@ __device__ __forceinline__ void batch_tile(const BJob& J, const BItem I, int pre
   d.shi = int64_t(1) << (J.d0[ps] + d.r);
   d.nlo = 1 << (J.d0[ps] - d.wdig);
   d.E = 1 << (d.r + d.wdig);
-  d.kreg = 4;
   const int lo = I.tile % d.nlo, hi = I.tile / d.nlo;
   const int64_t base = (int64_t)lo * d.w + (int64_t)hi * d.shi;
   const gptr<const float> src = to_global((ps == 0 ? J.in : J.out) + base);
@@ -140,10 +139,10 @@ __device__ __forceinline__ void batch_tile(const BJob& J, const BItem I, int pre
   }
   for (int q = q0; q < d.r; q += 4) {
     const int kk = min(4, d.r - q);
-    if (kk == 4) run_group<2, false, float, 4>(blds, d, q);
-    else if (kk == 3) run_group<2, false, float, 3>(blds, d, q);
-    else if (kk == 2) run_group<2, false, float, 2>(blds, d, q);
-    else run_group<2, false, float, 1>(blds, d, q);
+    if (kk == 4) run_group<float, 4>(blds, d, q);
+    else if (kk == 3) run_group<float, 3>(blds, d, q);
+    else if (kk == 2) run_group<float, 2>(blds, d, q);
+    else run_group<float, 1>(blds, d, q);
     __syncthreads();
   }
   const float sc = (ps == J.npass - 1) ? J.scale : 1.0f;

@@ -6,10 +6,11 @@
 // commute, so the m stages are grouped into passes over HBM.  A pass
 // transforms r consecutive digits [d0, d0+r) of every column: a workgroup
 // loads a tile of p^r rows (the r digits) by w contiguous elements (the lowest
-// digits, w = p^wdig >= 64 bytes of data so that HBM reads and writes come in
-// full segments), stages it in LDS, runs the r stages in groups of k digits
-// held in registers (p^k values per thread, one LDS round trip per group),
-// and writes the tile back in place.  The output is in natural order
+// digits, so that HBM reads and writes come in full segments), stages it in
+// LDS, runs the r stages in groups of k digits held in registers (p^k values
+// per thread, one LDS round trip per group), and writes the tile back in
+// place.  This file has the passes of p = 2 and the plans of every p, odd.hip
+// the passes of p = 3, 5, 7.  The output is in natural order
 // (h = sum h_i p^i), as in Algorithm 1.
 #include "coords.h"
 #include "family.h"
@@ -21,7 +22,6 @@
 #include <map>
 #include <type_traits>
 #include <mutex>
-#include <unordered_set>
 
 namespace fdwt {
 
@@ -36,151 +36,30 @@ size_t kind_bytes(Kind k) {
   return 0;
 }
 
-// Per-thread geometry of the generic pass.  A register group holds R = p^KMAX
-// elements; each thread loads LPT elements of a tile (e = tid + k TH): one
-// group, except for p = 5, whose groups are one digit (a two-digit group of
-// 25 complex values, with as many prefetched, needs more registers than a
-// wave gets) and whose threads load 16 elements, so that 1024 threads cover
-// a 5^6-element tile.
-template <int P, int KMAX, int BYTES>
-struct PassShape {
-  static constexpr int R = PowC<P, KMAX>::v;
-  static constexpr int LPT = P == 5 ? 16 : R;
-  // Largest tile the planner can give this kernel (padded tile within
-  // 160 KiB of LDS, at most 1024 x LPT elements) and the threads it takes:
-  // the kernel is compiled for that many, which sets its register budget.
-  static constexpr int emax_elems() {
-    int E = 1;
-    while ((int64_t)E * P <= 1024 * LPT && ((int64_t)E * P + E * P / 32 + 1) * BYTES <= 160 * 1024) E *= P;
-    return E;
+// ------------------------------------------------- p = 2, up to 2^6 points
+// A wave per column, a point per lane, the stages between the lanes (too few
+// points for the tiles below).  The grouped sums (double) as in fwt_p2_sums.
+template <class T, int EPI>
+__global__ void __launch_bounds__(64) fwt_p2_small(const T* in, T* out, PassDesc d) {
+  const int e = threadIdx.x, col = blockIdx.x;
+  const bool on = e < d.E;
+  T v = on ? in[(int64_t)col * d.col_in + e] : T(0);
+  for (int b = 0; b < d.r; ++b) {
+    const T o = __shfl_xor(v, 1 << b);
+    v = (e >> b) & 1 ? sub(o, v) : add(v, o);
   }
-  static constexpr int THREADS_RAW = (emax_elems() + LPT - 1) / LPT;
-  static constexpr int THREADS = THREADS_RAW < 64 ? 64 : (THREADS_RAW + 63) / 64 * 64;
-};
-
-// A pass is a persistent kernel: each workgroup walks over logical blocks
-// (tile, column) with stride gridDim.x.  The next tile's elements are loaded
-// into registers right after the current tile is in LDS, so the HBM reads of
-// tile k+1 overlap the butterflies and stores of tile k.
-template <int P, bool INV, class Tin, class T, class Tout, int KMAX, int EPI>
-__global__ void __launch_bounds__((PassShape<P, KMAX, sizeof(T)>::THREADS))
-    fwt_pass(const Tin* __restrict__ in, Tout* out, PassDesc d) {
-  constexpr int LPT = PassShape<P, KMAX, sizeof(T)>::LPT;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* lds = reinterpret_cast<T*>(smem_raw);
-  const int G = gridDim.x;
-  const int nb = d.ntiles * d.batch;
-  const int tid = threadIdx.x, TH = blockDim.x;
-  // Workgroups are dispatched round-robin over the 8 XCDs; with xcd set, XCD x
-  // takes the contiguous logical range [x G/8, (x+1) G/8) of every round, so
-  // neighbouring tiles (which share cache lines and DRAM pages, and for the
-  // grouped-sum epilogue the weights of a tile) meet in the same L2.
-  const int hw = blockIdx.x;
-  int lb = d.xcd ? xcd_first(hw, G) : hw;
-
-  auto locate = [&](int l, int& col, int& tile) {
-    if (EPI == EPI_REDUCE) {
-      col = l % d.batch;
-      tile = l / d.batch;
-    } else {
-      col = l / d.ntiles;
-      tile = l % d.ntiles;
+  if constexpr (EPI == EPI_STORE) {
+    if (on) out[(int64_t)col * d.col_out + e] = cvt_out<T, T>(v, d.scale, d.scale64);
+  } else {
+    double acc = 0.0;
+    if (on) {
+      const float2 wt = d.wts[e];
+      const double rho = fmin(fmax(v * (double)wt.y, 0.0), 1.0);
+      acc = (double)wt.x * rho;
+      if (e == 0 && col == d.h0_col) *d.h0_out = acc;
     }
-  };
-  auto tile_base = [&](int tile) {
-    const int lo = tile % d.nlo;
-    const int hi = tile / d.nlo;
-    return (int64_t)lo * d.w + (int64_t)hi * d.shi;
-  };
-  // Element e = tid + k TH of a tile sits in row e / w, column e mod w, at
-  // global offset (e mod w) + (e / w) sd0 from the tile base.  The thread's
-  // (row, column) for k = 0 and the step TH are split once; each next k
-  // advances them with a carry, so no element needs a division.  Offsets
-  // within a column fit in 32 bits (N <= 2^26).
-  const float inv_w = 1.0f / (float)d.w;
-  int i0, c0, ti, tc;
-  divmod_small(tid, d.w, inv_w, i0, c0);
-  divmod_small(TH, d.w, inv_w, ti, tc);
-  const uint32_t sd0 = (uint32_t)d.sd0;
-  // f(k, e, offset) for the thread's elements; clamp: indices past the tile
-  // end take its last element (offset and index), so the loads of a tile
-  // are all in flight together.
-  const uint32_t last = (uint32_t)(d.w - 1) + (uint32_t)(d.E / d.w - 1) * sd0;
-  auto for_elems = [&](bool clamp, auto&& f) {
-    // The empty asm makes the counters opaque here, so the offsets are
-    // recomputed at each sweep (a few operations per element) instead of
-    // being hoisted out of the tile loop into LPT live registers.
-    int c = c0, i = i0;
-    asm volatile("" : "+v"(c), "+v"(i));
-#pragma unroll
-    for (int k = 0; k < LPT; ++k) {
-      const int e = tid + k * TH;
-      if (e < d.E) f(k, e, (uint32_t)c + (uint32_t)i * sd0);
-      else if (clamp) f(k, d.E - 1, last);
-      c += tc;
-      i += ti;
-      if (c >= d.w) {
-        c -= d.w;
-        ++i;
-      }
-    }
-  };
-  Tin pre[LPT];
-  auto prefetch = [&](int l) {
-    int col, tile;
-    locate(l, col, tile);
-    const Tin* src = in + (int64_t)col * d.col_in + tile_base(tile);
-    for_elems(true, [&](int k, int, uint32_t off) { pre[k] = src[off]; });
-  };
-  double* red = reinterpret_cast<double*>(smem_raw + (size_t)(d.E + d.E / 32 + 1) * sizeof(T) + 8 -
-                                          ((d.E + d.E / 32 + 1) * sizeof(T)) % 8);
-  if (lb < nb) prefetch(lb);
-  for (; lb < nb; lb += G) {
-    // Clamped indices write the tile's last element again, with its value.
-    for_elems(true, [&](int k, int e, uint32_t) { lds[pad(e)] = cvt_in<Tin, T>(pre[k]); });
-    lds_barrier();
-    prefetch(lb + G < nb ? lb + G : lb);  // unconditional: exact wait counts
-    for (int q = 0; q < d.r; q += d.kreg) {
-      const int kk = min(d.kreg, d.r - q);
-      if constexpr (KMAX >= 4) {
-        if (kk == 4) run_group<P, INV, T, 4>(lds, d, q, inv_w);
-      }
-      if constexpr (KMAX >= 3) {
-        if (kk == 3) run_group<P, INV, T, 3>(lds, d, q, inv_w);
-      }
-      if constexpr (KMAX >= 2) {
-        if (kk == 2) run_group<P, INV, T, 2>(lds, d, q, inv_w);
-      }
-      if (kk == 1) run_group<P, INV, T, 1>(lds, d, q, inv_w);
-      lds_barrier();
-    }
-    int col, tile;
-    locate(lb, col, tile);
-    const int64_t base = tile_base(tile);
-    if constexpr (EPI == EPI_STORE) {
-      Tout* dst = out + (int64_t)col * d.col_out + base;
-      for_elems(false, [&](int, int e, uint32_t off) { dst[off] = cvt_out<T, Tout>(lds[pad(e)], d.scale, d.scale64); });
-    } else {
-      double acc = 0.0;
-      for_elems(false, [&](int, int e, uint32_t off) {
-        const int64_t h = base + off;
-        const float2 wt = d.wts[h];
-        const double rho = fmin(fmax(real_of(lds[pad(e)]) * (double)wt.y, 0.0), 1.0);
-        const double term = (double)wt.x * rho;
-        acc += term;
-        if (h == 0 && col == d.h0_col) *d.h0_out = term;
-      });
-      // Wave sums by butterfly shuffles, then the waves in a fixed order.
-      for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-      if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-      lds_barrier();
-      if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += red[w];
-        d.partial[(int64_t)col * d.ntiles + tile] = t;
-      }
-    }
-    lds_barrier();
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    if (e == 0) d.partial[col] = acc;
   }
 }
 
@@ -710,61 +589,17 @@ __global__ void __launch_bounds__((P2Shape<LOGE, 0>::THREADS)) fwt_p2_fam(FamGen
 
 
 // ----------------------------------------------------------------- planner
-// LDS per workgroup: 80 KiB lets two workgroups share a CU (160 KiB of LDS).
-// Elements of 8 bytes or more take a whole CU so that m = 24 still needs only
-// two passes (measured faster at m = 24 than three passes with two
-// workgroups per CU); FDWT_LDS_KB_WIDE overrides that budget (KiB).
-static size_t lds_budget(size_t bytes) {
+// LDS of a float64 tile: a whole CU, so that m = 24 still needs only two
+// passes (measured faster than three passes with two workgroups per CU);
+// FDWT_LDS_KB_WIDE overrides that budget (KiB).
+static size_t wide_lds_budget() {
   static const size_t wide = [] {
     const char* e = getenv("FDWT_LDS_KB_WIDE");
     const long v = e ? atol(e) : 160;
     return (size_t)std::max(16L, std::min(160L, v)) * 1024;
   }();
-  return bytes >= 8 ? wide : (size_t)80 * 1024;
+  return wide;
 }
-
-// Digits per register group of the generic pass (PassShape's KMAX) and the
-// elements each thread loads per tile (PassShape's LPT).
-static int kreg_for(int p, Kind) {
-  if (p == 2) return 4;
-  if (p == 3) return 2;
-  return 1;
-}
-static int loads_per_thread(int p) { return p == 2 ? 16 : (p == 3 ? 9 : (p == 5 ? 16 : 7)); }
-
-static std::vector<PassGeom> plan(int p, int m, size_t bytes, Kind work) {
-  // Largest tile exponent e with the padded tile within the LDS budget and
-  // at most 1024 threads x the elements each thread loads.
-  (void)work;
-  const size_t budget = lds_budget(bytes);
-  const int64_t per_block = 1024 * loads_per_thread(p);
-  int emax = 0;
-  for (int e = 1; e <= 30; ++e) {
-    int64_t E = ipow(p, e);
-    if ((size_t)(E + E / 32 + 1) * bytes > budget || E > per_block) break;
-    emax = e;
-  }
-  int wpref = 0;
-  while ((size_t)ipow(p, wpref) * bytes < 64) ++wpref;
-  std::vector<PassGeom> out;
-  const int r1 = std::min(m, emax);
-  out.push_back({0, r1, 0});
-  const int rest = m - r1;
-  if (rest > 0) {
-    // Strided passes: split the remaining digits evenly.
-    const int cap = emax - std::min(wpref, r1);
-    const int nstr = (rest + cap - 1) / cap;
-    int d = r1;
-    for (int i = 0; i < nstr; ++i) {
-      const int r = (rest - (d - r1) + (nstr - i) - 1) / (nstr - i);
-      out.push_back({d, r, std::min(wpref, d)});
-      d += r;
-    }
-  }
-  return out;
-}
-
-static int set_lds_attr(const void* fn, size_t bytes) { return allow_lds(fn, bytes); }
 
 // Compute units of the current device (cached per device).
 int device_cus() {
@@ -782,78 +617,41 @@ int device_cus() {
   return cache[dev];
 }
 
-template <int P, bool INV, class Tin, class T, class Tout>
-static int launch_pass(const void* in, void* out, const PassGeom& g, int m, int batch, double scale,
-                       int64_t col_in, int64_t col_out, Kind work, const ReduceArgs* red, hipStream_t st) {
-  constexpr int KMAX = P == 2 ? 4 : (P == 3 ? 2 : 1);
-  using Shape = PassShape<P, KMAX, sizeof(T)>;
-  constexpr int LPT = Shape::LPT;
-  static_assert(PowC<P, KMAX>::v <= LPT, "a thread loads at least one register group");
+template <class T>
+static int launch_small(const void* in, void* out, int m, int batch, double scale, const ReduceArgs* red,
+                        hipStream_t st) {
   PassDesc d{};
-  d.col_in = col_in;
-  d.col_out = col_out;
-  d.sd0 = ipow(P, g.d0);
-  d.shi = ipow(P, g.d0 + g.r);
-  d.r = g.r;
-  d.wdig = g.wdig;
-  d.w = (int)ipow(P, g.wdig);
-  d.nlo = (int)ipow(P, g.d0 - g.wdig);
-  d.E = (int)ipow(P, g.r) * d.w;
-  d.kreg = std::min(kreg_for(P, work), KMAX);
+  const int E = 1 << m;
+  d.col_in = E;
+  d.col_out = E;
+  d.r = m;
+  d.E = E;
+  d.ntiles = 1;
+  d.batch = batch;
   d.scale = (float)scale;
   d.scale64 = scale;
-  const int64_t ntiles = ipow(P, m) / d.E;
-  const int64_t nb = ntiles * batch;
-  d.ntiles = (int)ntiles;
-  d.batch = batch;
+  d.h0_col = -1;
+  const void* fn = (const void*)fwt_p2_small<T, EPI_STORE>;
   if (red) {
+    if constexpr (std::is_same<T, double>::value) fn = (const void*)fwt_p2_small<T, EPI_REDUCE>;
+    else return fail(FDWT_EINVAL, "grouped sums are computed in double");
     d.wts = red->wts;
     d.partial = red->partial;
     d.h0_out = red->h0_out;
     d.h0_col = red->h0_col;
     d.ncols = red->ncols;
-  } else {
-    d.h0_col = -1;
   }
-  if (LPT != loads_per_thread(P)) return fail(FDWT_EINVAL, "pass geometry tables disagree");
-  int threads = std::max(64, std::min(1024, (d.E + LPT - 1) / LPT));
-  threads = (threads + 63) / 64 * 64;
-  // Every tile element is loaded by the per-thread prefetch; the index
-  // arithmetic (divmod_small) needs indices below 2^22.
-  if ((int64_t)threads * LPT < d.E || d.E >= (1 << 22) || threads > Shape::THREADS)
-    return fail(FDWT_EINVAL, "pass tile larger than one workgroup loads");
-  const size_t tile_bytes = (size_t)(d.E + d.E / 32 + 1) * sizeof(T);
-  const size_t lds = tile_bytes + 8 - tile_bytes % 8 + 16 * sizeof(double);
-  const void* fn = red ? (const void*)fwt_pass<P, INV, Tin, T, Tout, KMAX, EPI_REDUCE>
-                       : (const void*)fwt_pass<P, INV, Tin, T, Tout, KMAX, EPI_STORE>;
-  int rc = set_lds_attr(fn, lds);
-  if (rc) return rc;
-  // Persistent grid: as many workgroups as fit on the device at once.
-  int per_cu = 0;
-  FDWT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds));
-  int64_t G = (int64_t)std::max(1, per_cu) * device_cus();
-  if (G >= nb) G = nb;
-  d.xcd = G >= 64 ? 1 : 0;
-  const double elems = (double)ipow(P, m) * batch;
-  const double alg = red ? elems * sizeof(Tin) + (double)ipow(P, m) * sizeof(float2)
-                         : elems * (sizeof(Tin) + sizeof(Tout));
-  const int cls = sizeof(T) >= 16 || std::is_same<T, double>::value ? FDWT_TC_PASS_F64
-                  : (sizeof(T) == 8 ? FDWT_TC_PASS_CF32 : FDWT_TC_PASS_F32);
-  const Tin* inp = (const Tin*)in;
-  Tout* outp = (Tout*)out;
-  void* args[] = {(void*)&inp, (void*)&outp, (void*)&d};
-  return launch_timed(fn, dim3((unsigned)G), dim3(threads), args, lds, st, cls, alg);
+  void* args[] = {(void*)&in, (void*)&out, (void*)&d};
+  const double elems = (double)E * batch;
+  const double work = red ? elems * sizeof(T) + (double)E * sizeof(float2) : elems * 2 * sizeof(T);
+  return launch_timed(fn, dim3((unsigned)batch), dim3(64), args, 0, st, sizeof(T) == 8 ? FDWT_TC_PASS_F64 : FDWT_TC_PASS_F32, work);
 }
 
-// A generic pass of a small p = 2 transform (forward and inverse coincide up
-// to the scale).
-static int p2_generic(Kind k, const void* in, void* out, const PassGeom& g, int m, int batch, double scale,
-                      const ReduceArgs* red, hipStream_t st) {
-  const int64_t N = int64_t(1) << m;
-  if (k == K_F32 && !red) return launch_pass<2, false, float, float, float>(in, out, g, m, batch, scale, N, N, k, red, st);
-  if (k == K_U32 && !red)
-    return launch_pass<2, false, uint32_t, uint32_t, uint32_t>(in, out, g, m, batch, scale, N, N, k, red, st);
-  if (k == K_F64) return launch_pass<2, false, double, double, double>(in, out, g, m, batch, scale, N, N, k, red, st);
+static int run_small(int m, Kind k, const void* in, void* out, int batch, double scale, const ReduceArgs* red,
+                     hipStream_t st) {
+  if (k == K_F32) return launch_small<float>(in, out, m, batch, scale, red, st);
+  if (k == K_U32) return launch_small<uint32_t>(in, out, m, batch, scale, red, st);
+  if (k == K_F64) return launch_small<double>(in, out, m, batch, scale, red, st);
   return fail(FDWT_EINVAL, "unsupported transform element types");
 }
 
@@ -913,14 +711,14 @@ static int p2_emax(int m, size_t bytes) {
 
 static std::vector<P2Pass> plan_p2(int m, size_t bytes) {
   const int e = p2_emax(m, bytes);
-  return plan_p2_e(m, (bytes >= 8 && lds_budget(bytes) < 136 * 1024) ? std::min(e, 13) : e, bytes);
+  return plan_p2_e(m, (bytes >= 8 && wide_lds_budget() < 136 * 1024) ? std::min(e, 13) : e, bytes);
 }
 
 // Plan of the kernel spectrum and of the variance columns (float64): 2^14
 // first-pass tiles at every size.  The spectra's small bins are differences
 // of large sums, so their last digits follow the order of the stages, which
 // a plan fixes; many columns fill the device with any tile.
-static std::vector<P2Pass> plan_p2_cols(int m) { return plan_p2_e(m, lds_budget(8) < 136 * 1024 ? 13 : 14, 8); }
+static std::vector<P2Pass> plan_p2_cols(int m) { return plan_p2_e(m, wide_lds_budget() < 136 * 1024 ? 13 : 14, 8); }
 
 template <class T, int WDIG>
 static const void* p2_store_kernel(int loge) {
@@ -1069,17 +867,12 @@ static int p2_pass(Kind k, const void* in, void* out, const P2Pass& g, int m, in
   return fail(FDWT_EINVAL, "unsupported p = 2 element type");
 }
 
-// p = 2 transforms of one element type through the static-shape passes
-// (forward and inverse coincide up to the scale for p = 2).
-static bool p2_static_ok(int p, int m, Kind ik, Kind wk, Kind ok) {
-  return p == 2 && m >= 7 && ik == wk && ok == wk && (wk == K_F32 || wk == K_U32 || wk == K_F64);
-}
-
+// p = 2: forward and inverse coincide up to the scale.
 static int run_p2(int m, Kind k, const void* in, void* out, void* tmp, int batch, double scale,
-                  const ReduceArgs* red, int64_t* last_parts, hipStream_t st) {
+                  const ReduceArgs* red, hipStream_t st) {
+  if (m < 7) return run_small(m, k, in, out, batch, scale, red, st);
   const std::vector<P2Pass> passes = red ? plan_p2_cols(m) : plan_p2(m, kind_bytes(k));
   const size_t np = passes.size();
-  if (last_parts) *last_parts = p2_reduce_parts(m, passes.back());
   if (np == 1) return p2_pass(k, in, out, passes[0], m, batch, scale, red, st);
   void* mid = red ? tmp : out;
   if (!mid) return fail(FDWT_EINVAL, "transform needs a workspace for its intermediate passes");
@@ -1091,22 +884,14 @@ static int run_p2(int m, Kind k, const void* in, void* out, void* tmp, int batch
 
 static int run_passes(int p, int m, bool inverse, Kind in_kind, const void* in, Kind work_kind,
                       Kind out_kind, void* out, void* tmp, int batch, double scale, const ReduceArgs* red,
-                      int64_t* last_parts, hipStream_t st) {
-  if (p2_static_ok(p, m, in_kind, work_kind, out_kind))
-    return run_p2(m, work_kind, in, out, tmp, batch, scale, red, last_parts, st);
-  if (p == 2 && (in_kind != work_kind || out_kind != work_kind))
-    return fail(FDWT_EINVAL, "unsupported transform element types");
-  const int64_t N = ipow(p, m);
-  // p = 2 below 2^7 points: the generic pass; p odd: the static shapes of odd.hip.
-  std::vector<PassGeom> passes = p == 2 ? plan(p, m, kind_bytes(work_kind), work_kind) : odd_plan(p, m, work_kind == K_CF64);
-  const size_t np = passes.size();
-  if (last_parts) {
-    const PassGeom& g = passes.back();
-    *last_parts = N / (ipow(p, g.r) * ipow(p, g.wdig));
+                      hipStream_t st) {
+  if (p == 2) {
+    if (in_kind != work_kind || out_kind != work_kind) return fail(FDWT_EINVAL, "unsupported transform element types");
+    return run_p2(m, work_kind, in, out, tmp, batch, scale, red, st);
   }
-  auto one = [&](Kind ik, Kind ok, const void* src, void* dst, const PassGeom& g, double sc,
-                 const ReduceArgs* rd) {
-    if (p == 2) return p2_generic(work_kind, src, dst, g, m, batch, sc, rd, st);
+  const std::vector<PassGeom> passes = odd_plan(p, m, work_kind == K_CF64);
+  const size_t np = passes.size();
+  auto one = [&](Kind ik, Kind ok, const void* src, void* dst, const PassGeom& g, double sc, const ReduceArgs* rd) {
     return odd_pass(p, inverse, ik, work_kind, ok, src, dst, g, m, batch, sc, rd, st);
   };
   if (np == 1) return one(in_kind, out_kind, in, out, passes[0], scale, red);
@@ -1124,8 +909,7 @@ static int run_passes(int p, int m, bool inverse, Kind in_kind, const void* in, 
 
 int fwt_run_tmp(int p, int m, bool inverse, Kind in_kind, const void* in, Kind work_kind,
                 Kind out_kind, void* out, void* tmp, int batch, double scale, hipStream_t st) {
-  return run_passes(p, m, inverse, in_kind, in, work_kind, out_kind, out, tmp, batch, scale, nullptr,
-                    nullptr, st);
+  return run_passes(p, m, inverse, in_kind, in, work_kind, out_kind, out, tmp, batch, scale, nullptr, st);
 }
 
 int fwt_run(int p, int m, bool inverse, Kind in_kind, const void* in, Kind work_kind,
@@ -1139,13 +923,12 @@ int fwt_run(int p, int m, bool inverse, Kind in_kind, const void* in, Kind work_
 // columns as complex ones, column 2 i as the real part and column 2 i + 1
 // times 2^pexp[i] as the imaginary part (both spectra are real: the
 // kernel columns are even functions of the point index), and is overwritten;
-// tmp is not used.  partial receives [ncols][parts] partial sums, parts
-// (fwt_reduce_parts) returned in *parts.
+// tmp is not used.  partial receives [ncols][fwt_reduce_parts] partial sums.
 int fwt_reduce_f64(int p, int m, void* in, void* tmp, int ncols, const float2* wts, const int32_t* pexp,
-                   double* partial, double* h0_out, int h0_col, int64_t* parts, hipStream_t st) {
+                   double* partial, double* h0_out, int h0_col, hipStream_t st) {
   ReduceArgs red{wts, partial, h0_out, h0_col, pexp, ncols};
-  if (p == 2) return run_passes(p, m, false, K_F64, in, K_F64, K_F64, tmp, tmp, ncols, 1.0, &red, parts, st);
-  return run_passes(p, m, false, K_CF64, in, K_CF64, K_CF64, in, in, (ncols + 1) / 2, 1.0, &red, parts, st);
+  if (p == 2) return run_passes(p, m, false, K_F64, in, K_F64, K_F64, tmp, tmp, ncols, 1.0, &red, st);
+  return run_passes(p, m, false, K_CF64, in, K_CF64, K_CF64, in, in, (ncols + 1) / 2, 1.0, &red, st);
 }
 
 // Plans of p = 2 float transforms for the batch tuner: the first pass takes
@@ -1346,11 +1129,10 @@ int fwt_p2_forward_family(const Net& net, int family, const FamilyArgs& fa, floa
   return FDWT_OK;
 }
 
-int64_t fwt_reduce_parts(int p, int m, size_t elem_bytes) {
-  if (p == 2 && m >= 7) return p2_reduce_parts(m, plan_p2_cols(m).back());
-  const std::vector<PassGeom> passes = p == 2 ? plan(p, m, elem_bytes, K_F64) : odd_plan(p, m, true);
-  const PassGeom& g = passes.back();
-  return ipow(p, m) / (ipow(p, g.r) * ipow(p, g.wdig));
+// Partial sums per column of fwt_reduce_f64 and fwt_p2_f64_reduce_rest.
+int64_t fwt_reduce_parts(int p, int m) {
+  if (p == 2) return m < 7 ? 1 : p2_reduce_parts(m, plan_p2_cols(m).back());
+  return ipow(p, m - odd_plan(p, m, true).back().le);
 }
 
 }  // namespace fdwt

@@ -1,5 +1,5 @@
-// Device building blocks shared by the transform passes (fwt.hip) and the
-// batched persistent kernel (batch.hip): pass descriptor, element-type
+// Device building blocks shared by the transform passes (fwt.hip, odd.hip) and
+// the batched persistent kernel (batch.hip): pass descriptor, element-type
 // conversions, the padded LDS index and the runtime-geometry register groups.
 #pragma once
 
@@ -18,7 +18,6 @@ struct PassDesc {
   int32_t w;
   int32_t nlo;      // p^d0 / w tiles side by side along the low digits
   int32_t E;        // tile size p^r * w
-  int32_t kreg;     // digits per register group
   int32_t xcd;      // 1: consecutive tiles are kept on one XCD
   int32_t ntiles;   // tiles per column
   int32_t batch;    // columns
@@ -26,9 +25,9 @@ struct PassDesc {
   double scale64;   // the same factor for double-based outputs
   // Grouped-sum epilogue (EPI_REDUCE): instead of storing, accumulate
   // sum_h wts[h].x * clamp(value(h) * wts[h].y, 0, 1) per column into
-  // partial sums: partial[col * ntiles + tile] (generic pass) or one per wave,
-  // partial[(col * ntiles + tile) * waves + wave] (static p = 2 pass); the
-  // value at h = 0 of column h0_col goes to *h0_out as well.
+  // partial sums: partial[col * ntiles + tile], or one per wave of a tile,
+  // partial[(col * ntiles + tile) * waves + wave] (p = 2 from 2^7 points on);
+  // the value at h = 0 of column h0_col goes to *h0_out as well.
   const float2* wts;
   double* partial;
   double* h0_out;
@@ -131,46 +130,9 @@ template <> __device__ __forceinline__ double cvt_out<double, double>(double v, 
 template <> __device__ __forceinline__ double2 cvt_out<double2, double2>(double2 v, float, double sc) { return make_double2(v.x * sc, v.y * sc); }
 template <> __device__ __forceinline__ double cvt_out<double2, double>(double2 v, float, double sc) { return v.x * sc; }
 
-// Real part as double (the grouped-sum epilogue).
-__device__ __forceinline__ double real_of(double v) { return v; }
-__device__ __forceinline__ double real_of(double2 v) { return v.x; }
-__device__ __forceinline__ double real_of(float v) { return v; }
-__device__ __forceinline__ double real_of(float2 v) { return v.x; }
-__device__ __forceinline__ double real_of(uint32_t v) { return (double)v; }
-
 // LDS index with one padding element per 32 (spreads the stride-p^k
 // register-group accesses over the banks).
 __device__ __forceinline__ int pad(int e) { return e + (e >> 5); }
-
-template <int P>
-struct Ix {
-  // a / p^k and a % p^k for powers of p given by their exponent and value.
-  static __device__ __forceinline__ int div(int a, int k, int pk) {
-    if constexpr (P == 2) return a >> k; else return a / pk;
-  }
-  static __device__ __forceinline__ int mod(int a, int k, int pk) {
-    if constexpr (P == 2) return a & (pk - 1); else return a % pk;
-  }
-};
-
-// Quotient and remainder of 0 <= a < 2^22 by 1 <= dv < 2^22 given
-// inv = 1.0f / dv (correctly rounded): a * inv is within 0.5 of a / dv (a
-// relative error below 2^-23 on a value below 2^22), so its truncation is
-// the quotient or one off, and one correction step makes it exact.  The
-// emulation of these float operations on the host checks every (a, dv) the
-// pass geometries use.  Replaces the integer division (a long instruction
-// sequence) on the passes' per-group index arithmetic.
-__host__ __device__ __forceinline__ void divmod_small(int a, int dv, float inv, int& q, int& r) {
-  q = (int)((float)a * inv);
-  r = a - q * dv;
-  if (r < 0) {
-    --q;
-    r += dv;
-  } else if (r >= dv) {
-    ++q;
-    r -= dv;
-  }
-}
 
 template <int P, int K>
 struct PowC {
@@ -181,49 +143,31 @@ struct PowC<P, 0> {
   static constexpr int v = 1;
 };
 
-__device__ __forceinline__ int ipow_d(int b, int e) {
-  int r = 1;
-  for (int i = 0; i < e; ++i) r *= b;
-  return r;
-}
-
-// One register group: the KK digits [q, q+KK) of the tile row index.  Each
-// thread takes p^KK elements that differ only in those digits, applies the
-// KK radix-p stages in registers and writes them back.  inv_w = 1.0f / w
-// (odd p: see divmod_small).
-template <int P, bool INV, class T, int KK>
-__device__ __forceinline__ void run_group(T* lds, const PassDesc& d, int q, float inv_w = 0.0f) {
-  constexpr int R = PowC<P, KK>::v;
-  const int pq = ipow_d(P, q);
+// One register group (p = 2): the KK digits [q, q+KK) of the tile row index.
+// Each thread takes 2^KK elements that differ only in those digits, applies
+// the KK stages in registers and writes them back.
+template <class T, int KK>
+__device__ __forceinline__ void run_group(T* lds, const PassDesc& d, int q) {
+  constexpr int R = 1 << KK;
   const int ng = d.E / R;
-  const int stq = d.w * pq;  // LDS stride of digit q
-  const float inv_pq = P == 2 ? 0.0f : 1.0f / (float)pq;
+  const int stq = d.w << q;  // LDS stride of digit q
   for (int g = threadIdx.x; g < ng; g += blockDim.x) {
-    int c, rem, il, ih;
-    if constexpr (P == 2) {
-      c = Ix<P>::mod(g, d.wdig, d.w);
-      rem = Ix<P>::div(g, d.wdig, d.w);
-      il = Ix<P>::mod(rem, q, pq);
-      ih = Ix<P>::div(rem, q, pq);
-    } else {
-      divmod_small(g, d.w, inv_w, rem, c);
-      divmod_small(rem, pq, inv_pq, ih, il);
-    }
-    const int e0 = c + d.w * (il + pq * R * ih);
+    const int c = g & (d.w - 1), rem = g >> d.wdig;
+    const int il = rem & ((1 << q) - 1), ih = rem >> q;
+    const int e0 = c + d.w * (il + (ih << (q + KK)));
     T x[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) x[j] = lds[pad(e0 + j * stq)];
 #pragma unroll
-    for (int t = 0, st = 1; t < KK; ++t, st *= P) {
+    for (int t = 0, st = 1; t < KK; ++t, st *= 2) {
 #pragma unroll
       for (int j0 = 0; j0 < R; ++j0) {
-        if ((j0 / st) % P == 0) Dft<P, INV>::run(x + j0, st);
+        if ((j0 / st) % 2 == 0) Dft<2, false>::run(x + j0, st);
       }
     }
 #pragma unroll
     for (int j = 0; j < R; ++j) lds[pad(e0 + j * stq)] = x[j];
   }
 }
-
 
 }  // namespace fdwt

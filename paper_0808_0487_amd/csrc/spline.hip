@@ -672,8 +672,8 @@ static int launch_kernel_cols(const Net& net, const KernTab& kt, int c0, int c1,
 static unsigned grid1(int64_t n) { return (unsigned)std::min<int64_t>((n + 255) / 256, 4096); }
 
 int fwt_reduce_f64(int p, int m, void* in, void* tmp, int ncols, const float2* wts, const int32_t* pexp,
-                   double* partial, double* h0_out, int h0_col, int64_t* parts, hipStream_t st);
-int64_t fwt_reduce_parts(int p, int m, size_t elem_bytes);
+                   double* partial, double* h0_out, int h0_col, hipStream_t st);
+int64_t fwt_reduce_parts(int p, int m);
 bool fwt_p2_split_ok(int m);
 bool fwt_p2_blocked_ok(int m);
 int fwt_p2_first_loge(int m);
@@ -984,8 +984,7 @@ static int effdim_cols(int s) { return 2 * s - 1; }
 
 static void eff_layout(const Net& net, bool have_gk, int ch, Carve& cv, EffWs& w) {
   const int ncols = effdim_cols(net.s);
-  const size_t wb = (net.p == 2) ? sizeof(double) : sizeof(double2);
-  const int64_t parts = fwt_reduce_parts(net.p, net.m, wb);
+  const int64_t parts = fwt_reduce_parts(net.p, net.m);
   w.gk = have_gk ? nullptr : cv.take(spectrum_bytes(net));
   w.sw = have_gk ? nullptr : cv.take(spectrum_ws_bytes(net));
   w.wts = (float2*)cv.take((size_t)net.N * sizeof(float2));
@@ -1011,9 +1010,8 @@ int eff_dim_enqueue(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
                     double* res_host, hipStream_t st) {
   const int p = net.p, s = net.s;
   const int64_t N = net.N;
-  const size_t wb = (p == 2) ? sizeof(double) : sizeof(double2);
   const int ncols = effdim_cols(s);  // U_1..U_s, Q_1..Q_{s-1} (generator columns 1..2s-1)
-  const int64_t parts = fwt_reduce_parts(p, net.m, wb);  // partial sums per column
+  const int64_t parts = fwt_reduce_parts(p, net.m);  // partial sums per column
   int rc = ensure_ws(sc, eff_dim_ws_bytes(net, gk_given != nullptr, ch), st);
   if (rc) return rc;
   Carve cv(sc.ws);
@@ -1057,9 +1055,8 @@ int eff_dim_enqueue(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
     } else {
       rc = launch_kernel_cols(net, kt, c0 + 1, c1 + 1, w.A, st);
       if (rc) return rc;
-      int64_t t = 0;
       rc = fwt_reduce_f64(p, net.m, w.A, w.B, c1 - c0, w.wts, p == 2 ? nullptr : kt.ix + c0 / 2,
-                          w.partial + (size_t)c0 * parts, h0, h0_col, &t, st);
+                          w.partial + (size_t)c0 * parts, h0, h0_col, st);
     }
     if (rc) return rc;
   }
