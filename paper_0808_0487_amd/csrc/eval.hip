@@ -424,7 +424,7 @@ static int row_prefix(const Net& net, int j) {
 // Nets the rows serve: the first K columns of every generator matrix as
 // above, the points have no digits
 // beyond the words' K + ND (p = 5: m <= 10; the other primes' largest nets
-// fit), and the rows of all coordinates fit a CU's LDS (p = 7: s <= 43).
+// fit), and the rows of all coordinates fit a CU's LDS (p = 7: s <= 44).
 bool eval_rows_ok(const Net& net) {
   if (net.m < row_k(net.p) || (net.p == 5 && net.m > 10) || rows_lds(net.p, net.s) > 160 * 1024) return false;
   for (int j = 0; j < net.s; ++j)
@@ -441,29 +441,41 @@ constexpr int row_threads(int p, int sg) { return (p == 2 ? 1 : (p == 3 ? 2 : 3)
 // runs.  Of the divisions into up to eight rounds of workgroups, the one with
 // the least work on the busiest slot (a workgroup's start counted as 12
 // blocks); sub-chunks of 128 points or more end at multiples of 64.
+// No more partial sums per query than k_spline_eval makes of the shape
+// (eval_grid), so that the workspace does not depend on the kernel: where 256
+// queries a workgroup would need more, fewer queries share it, and more of
+// its waves divide the points.
 void eval_rows_grid(int p, int s, int64_t N, int64_t nq, int* tqw_out, int* gy_out, int* bpc_out) {
   const int sg = (s + 3) / 4 * 4, th = row_threads(p, sg);
   const int64_t slots = 256 * (row_waves(p, sg, th) * 256 / th);
   const int64_t nblk = N / (p == 2 ? 4 : p);
-  const int tqw = nq <= 64 ? 1 : (nq <= 128 ? 2 : 4);
-  const int nsub = th / 64 / tqw;
-  const int64_t qg = (nq + 64 * tqw - 1) / (64 * tqw);
   const int unit = p == 2 ? 16 : 64;  // blocks that end at a multiple of 64 points
-  int64_t best = -1;
-  for (int rounds = 1; rounds <= 8; ++rounds) {
-    int64_t gy = std::max<int64_t>(1, std::min(rounds * slots / qg, nblk / (8 * nsub)));
-    int64_t bpc = std::max<int64_t>(1, (nblk + gy * nsub - 1) / (gy * nsub));
-    if (bpc >= 2 * unit) bpc = (bpc + unit - 1) / unit * unit;
-    gy = std::max<int64_t>(1, (nblk + bpc * nsub - 1) / (bpc * nsub));
-    // (One round of long workgroups ends unevenly: p = 7, N = 7^6, 20000
-    // queries 1.18 ms in one, 1.03 ms in more.)
-    const int64_t cost = (gy * qg + slots - 1) / slots * (bpc + 12) + (rounds == 1 && bpc >= 256 ? bpc / 4 : 0);
-    if (best >= 0 && cost >= best) continue;
-    best = cost;
-    *tqw_out = tqw;
-    *gy_out = (int)gy;
-    *bpc_out = (int)bpc;
-  }
+  int gy_most;
+  int64_t ppc, best = -1;
+  eval_grid(N, nq, &gy_most, &ppc);
+  auto consider = [&](int tqw, int64_t most) {
+    const int nsub = th / 64 / tqw;
+    const int64_t qg = (nq + 64 * tqw - 1) / (64 * tqw);
+    for (int rounds = 1; rounds <= 8; ++rounds) {
+      int64_t gy = std::max<int64_t>(1, std::min({rounds * slots / qg, nblk / (8 * nsub), most}));
+      int64_t bpc = std::max<int64_t>(1, (nblk + gy * nsub - 1) / (gy * nsub));
+      if (bpc >= 2 * unit) bpc = (bpc + unit - 1) / unit * unit;
+      gy = std::max<int64_t>(1, (nblk + bpc * nsub - 1) / (bpc * nsub));
+      // (One round of long workgroups ends unevenly: p = 7, N = 7^6, 20000
+      // queries 1.18 ms in one, 1.03 ms in more.)
+      const int64_t cost = (gy * qg + slots - 1) / slots * (bpc + 12) + (rounds == 1 && bpc >= 256 ? bpc / 4 : 0);
+      if (best >= 0 && cost >= best) continue;
+      best = cost;
+      *tqw_out = tqw;
+      *gy_out = (int)gy;
+      *bpc_out = (int)bpc;
+    }
+  };
+  const int tqw = nq <= 64 ? 1 : (nq <= 128 ? 2 : 4);
+  consider(tqw, nblk);
+  if (*gy_out <= gy_most) return;
+  best = -1;
+  for (int t = tqw; t >= 1; t /= 2) consider(t, gy_most);
 }
 
 // The prefixes of every coordinate into kt.ix.

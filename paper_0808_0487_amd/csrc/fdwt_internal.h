@@ -197,6 +197,7 @@ size_t spline_coef_ws_bytes(const Net& net, bool have_spectrum);
 int run_spline_coef(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* gk, const void* ft, float* c,
                     hipStream_t st);
 size_t packed_bytes(const Net& net);       // packed coordinates of all points (launch_net_packed)
+void eval_grid(int64_t N, int64_t nq, int* gy, int64_t* ppc);
 // eval.hip: evaluation by table rows, for the nets eval_rows_ok accepts.
 bool eval_rows_ok(const Net& net);
 void eval_rows_grid(int p, int s, int64_t N, int64_t nq, int* tqw, int* gy, int* bpc);

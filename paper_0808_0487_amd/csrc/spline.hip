@@ -842,7 +842,7 @@ size_t packed_bytes(const Net& net) { return (size_t)net.s * net.N * (net.p == 2
 // Grid of the evaluation: query blocks x point chunks, >= ~2048 workgroups in
 // total; it depends on (N, nq) only, so a result never depends on where or
 // alongside what it runs.
-static void eval_grid(int64_t N, int64_t nq, int* gy_out, int64_t* ppc_out) {
+void eval_grid(int64_t N, int64_t nq, int* gy_out, int64_t* ppc_out) {
   const int64_t qb = (nq + 255) / 256;
   int gy = (int)std::max<int64_t>(1, std::min<int64_t>((2048 + qb - 1) / qb, (N + kNSMax - 1) / kNSMax));
   int64_t ppc = (N + gy - 1) / gy;
@@ -860,12 +860,11 @@ struct EvalWs {
 };
 static void eval_layout(const Net& net, int64_t nq, bool have_packed, Carve& cv, EvalWs& w) {
   const int p = net.p, s = net.s;
-  // Sized for either kernel (a shape does not tell which one its net takes).
-  int gy, gyr, tqw, bpc;
+  // Enough for either kernel (a shape does not tell which one its net takes):
+  // eval_rows_grid makes no more partial sums than eval_grid.
+  int gy;
   int64_t ppc;
   eval_grid(net.N, nq, &gy, &ppc);
-  eval_rows_grid(p, s, net.N, nq, &tqw, &gyr, &bpc);
-  gy = std::max(gy, gyr);
   w.tl = (float*)cv.take(eval_tables_bytes(net));
   w.Xp = have_packed ? nullptr : cv.take(packed_bytes(net));
   w.qs = p == 2 ? nullptr : (uint64_t*)cv.take((size_t)s * nq * 8);
@@ -949,12 +948,14 @@ int run_spline_eval(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
 // -------------------------------------------------- effective dimension
 // Columns of kernel data per chunk so that they stay within `budget` bytes:
 // p = 2, data and intermediate, 16 B per column and point; p odd, whole pairs
-// of 16 B, transformed in place.  The variances do not depend on the
-// chunking: every column (pair) is transformed and reduced on its own.
+// of 16 B, transformed in place, as many as fit whole multiples of 24 B per
+// point (the unit of the budget for p odd: a budget that admits a job keeps
+// admitting it).  The variances do not depend on the chunking: every column
+// (pair) is transformed and reduced on its own.
 int eff_dim_chunk(const Net& net, size_t budget) {
-  const size_t per_col = (size_t)net.N * 16;
-  if (net.p != 2) return 2 * (int)std::max<size_t>(1, std::min<size_t>((size_t)net.s, budget / per_col));
-  return (int)std::max<size_t>(1, std::min<size_t>((size_t)2 * net.s, budget / per_col));
+  const size_t N = (size_t)net.N;
+  if (net.p != 2) return 2 * (int)std::max<size_t>(1, std::min<size_t>((size_t)net.s, budget / (24 * N) * 24 / 16));
+  return (int)std::max<size_t>(1, std::min<size_t>((size_t)2 * net.s, budget / (16 * N)));
 }
 
 size_t eff_dim_res_bytes(const Net& net) { return (size_t)(2 * net.s + 2) * sizeof(double); }
