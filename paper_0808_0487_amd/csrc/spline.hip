@@ -885,8 +885,10 @@ int run_spline_eval(Net& net, Scratch& sc, const fdwt_kernel* kern, const void* 
   const bool rows = eval_rows_ok(net);
   int gy, tqw, bpc;
   int64_t ppc;
+  eval_grid(N, nq, &gy, &ppc);
+  const int most = gy;  // partial sums per query in the workspace
   if (rows) eval_rows_grid(p, s, N, nq, &tqw, &gy, &bpc);
-  else eval_grid(N, nq, &gy, &ppc);
+  if (gy > most) return fail(FDWT_EBUDGET, "evaluation grid exceeds its workspace");
   int rc = ensure_ws(sc, spline_eval_ws_bytes(net, nq, packed != nullptr), st);
   if (rc) return rc;
   Carve cv(sc.ws);
