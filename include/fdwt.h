@@ -30,9 +30,9 @@
  *     process, the last two at each call): FDWT_EFFDIM_CHUNK_MB, the
  *     workspace budget of fdwt_eff_dim's kernel-data columns in MiB
  *     (default 12288; smaller budgets process the columns in chunks, with
- *     bit-identical results); FDWT_LDS_KB_WIDE, the
- *     LDS budget in KiB of the float64 pass tiles (default 160: 2^14-element
- *     tiles; other budgets change the pass plan and so the rounding);
+ *     bit-identical results); FDWT_LDS_KB_WIDE, the LDS budget in KiB of the
+ *     p = 2 float64 pass tiles (default 160: 2^14-element tiles; below 136:
+ *     2^13; another budget changes the pass plan and so the rounding);
  *     FDWT_EFFDIM_BLOCKED = 0 keeps fdwt_eff_dim's p = 2 intermediate
  *     columns in natural order instead of the blocked layout (the variances
  *     are bit-identical; var_qmc is summed in another order);

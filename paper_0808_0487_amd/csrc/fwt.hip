@@ -697,12 +697,13 @@ static std::vector<P2Pass> plan_p2_e(int m, int emax, size_t bytes = 4) {
 // transform fits one tile or needs it to stay at two passes, and smaller
 // tiles where two passes hold anyway: their workgroups are more than the CUs
 // at fewer points, and several share a CU (a 2^14-element float64 tile takes
-// a whole one).  Measured per call, 2^14 against this bound (us; with the
-// persistent form of the passes): float
-// m = 17 11.0 / 10.9, m = 19 12.1 / 11.3, m = 20 14.4 / 12.9, m = 22
-// 27.3 / 23.4 (m = 23 29.0 / 43.0: three passes); float64 m = 17 13.8 / 11.0,
-// m = 19 16.3 / 12.0, m = 20 21.0 / 16.1, m = 21 30.7 / 28.0 with 2^13
-// (m = 22 31.0 / 32.9).
+// a whole one).  Forward + inverse pairs (us), 2^14 / this bound: float
+// m = 18 15.0 / 14.6, m = 19 16.2 / 15.0 (2^12: 14.7), m = 20 20.2 / 18.8
+// (2^12: 20.1), m = 22 32.3 / 32.0 (m = 23 47.6, with 2^13 three passes and
+// 62.6; m = 15 to 17 within 0.4 for every bound); float64 m = 16 15.8 / 14.6,
+// m = 17 21.8 / 14.7, m = 19 27.4 / 20.2, m = 20 35.5 / 28.4, m = 21
+// 37.0 / 33.6 with 2^13 (2^12: three passes, 43.9), m = 22 53.5 with 2^14
+// (2^13: 48.9, not taken yet).
 static int p2_emax(int m, size_t bytes) {
   if (bytes < 8) return m >= 18 && m <= 22 ? 13 : 14;
   if (m <= 14) return 14;
