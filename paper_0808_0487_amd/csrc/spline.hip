@@ -4,8 +4,9 @@
 //    variances, U_d = R_d - 1 with R_d = prod_{j<=d} (1 + gamma_j^2 R'(x_{n,j}, 0))
 //    and Q_j = e_j(gamma_1^2 R'_1, ..., gamma_s^2 R'_s) (elementary symmetric
 //    polynomials), all in float64.  K' and R' depend only on the index of the
-//    first non-zero digit of x_{n,j}, so per-coordinate tables (computed on
-//    the host) are indexed by a leading-zero count.
+//    first non-zero digit of x_{n,j}, so per-coordinate tables (formed in LDS
+//    from the kernel's values by index, an argument) are indexed by a
+//    leading-zero count.
 //  * their DWTs (the kernel spectra) are taken in float64: their dynamic
 //    range exceeds what float resolves (the small bins would lose all their
 //    digits, and K~ must stay positive for the spectral solve).  On MI355X
