@@ -1127,7 +1127,6 @@ static int wait_stream(Net& net, hipStream_t st) {
       if (e == hipSuccess) return FDWT_OK;
       if (e != hipErrorNotReady) FDWT_HIP(e);
     } while (std::chrono::steady_clock::now() < end);
-    (void)hipGetLastError();  // not ready is no error
   }
   FDWT_HIP(hipStreamSynchronize(st));
   return FDWT_OK;
